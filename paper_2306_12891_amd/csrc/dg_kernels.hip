@@ -63,21 +63,14 @@ constexpr BasisLayout BL(n1);
 constexpr int NB_STAGE = 2 * n1 * n1 + 3 * n1 + 1;  // Dhat, Dw, winv, xi, edge
 
 // Tuning: minimum waves per SIMD requested from the register allocator for
-// the stage kernel (0 = compiler default), and whether the volume loop skips
-// the zero diagonal of Dhat.
+// the stage kernel (0 = compiler default).
 #ifndef DG_STAGE_MIN_WAVES
 #define DG_STAGE_MIN_WAVES 0
-#endif
-#ifndef DG_SKIP_DIAG
-#define DG_SKIP_DIAG 0
 #endif
 // Accumulate the BR1 gradient inside the split-form volume loop, reusing its
 // partner values and coefficients (1), or in a separate pass (0).  The fused
 // loop is kept rolled: fully unrolled, the partner loads in flight need more
 // than 200 registers.
-#ifndef DG_VDIV_LINES
-#define DG_VDIV_LINES 0
-#endif
 #ifndef DG_FUSED_GRAD
 #define DG_FUSED_GRAD 1
 #endif
@@ -406,60 +399,66 @@ __device__ __forceinline__ void surface_flux_dir(int d, int sf, const double L[5
 // ---------------------------------------------------------------------------
 // Volume integral along direction D for node n (index id along D).
 // ---------------------------------------------------------------------------
-// Dhat has a zero diagonal, so partner l = id is skipped: the loop visits
-// l = id + 1, ..., id + N (mod N + 1).
-__device__ __forceinline__ int partner(int id, int k) {
-  if (!DG_SKIP_DIAG) return k - 1;
-  const int l = id + k;
-  return l >= n1 ? l - n1 : l;
-}
-constexpr int kPartners = DG_SKIP_DIAG ? N : N + 1;
-
-// Calls body(l, m) for the partners l of node n (index id along a line of
-// stride ST starting at node base) in the order above.  ROLLED: a rolled loop
-// with the partner index and node advanced incrementally (one wrap test per
-// partner instead of the modulo and two address products).
-template <bool ROLLED, int ST, class F>
-__device__ __forceinline__ void partner_loop(int id, int n, int base, F&& body) {
-  if (!DG_SKIP_DIAG) {  // every l; the zero diagonal term is evaluated too
+// ROT: the N partners l != id of a node in a rotated order, fully unrolled, so
+// that step m adds a compile-time offset to the node: l = id ^ m where N + 1
+// is a power of two, else l = (id + m) mod (N + 1), i.e. node n + m st or,
+// past the line's end, n + (m - N - 1) st.  The coefficients Dhat_{id l} lie in
+// LDS in the same order (sDhat[m][id], see dhat_index).  Before each partner
+// tie(k, ic) makes the next indices depend on all running sums (an empty asm),
+// so that a partner's values are loaded only once the sums of the one before
+// are formed: else the unrolled loop takes more than 200 registers.
+// Otherwise (the mixed operator and the blended kernels): every l in order, the
+// zero diagonal term included, sDhat as in the basis; rolled with the gradient
+// (unrolled, its loads in flight need more than 200 registers).
+// Measured at 32^3: the Euler N = 7 step 3213 -> 3155 us, the N = 5
+// Navier-Stokes stage 370 -> 363 us with ROT (one partner in N + 1 less, no
+// loop); the blended N = 5 step 290 -> 298 us, so those keep the plain order.
+constexpr bool kPow2 = (n1 & (n1 - 1)) == 0;
+template <bool ROT, bool ROLLED, int ST, class R, class F, class T>
+__device__ __forceinline__ void partner_loop(int id, int n, const R* sDhat, F&& body, T&& tie) {
+  if (ROT) {
+    const int nw = n - n1 * ST;
+    int ic = id;
+#pragma unroll
+    for (int m = 1; m <= N; ++m) {
+      int k;
+      if (kPow2) k = n ^ (m * ST);
+      else k = (id >= n1 - m ? nw : n) + m * ST;
+      if (m == 1) asm volatile("" : "+v"(k), "+v"(ic));
+      else tie(k, ic);
+      body(sDhat[m * n1 + ic], k);
+    }
+    int k = n;
+    tie(k, ic);
+  } else {
+    const int base = n - id * ST;
+    const R* crow = sDhat + id * n1;
     if (ROLLED) {
 #pragma unroll 1
-      for (int l = 0; l < n1; ++l) body(l, base + l * ST);
+      for (int l = 0; l < n1; ++l) body(crow[l], base + l * ST);
     } else {
 #pragma unroll
-      for (int l = 0; l < n1; ++l) body(l, base + l * ST);
-    }
-  } else if (ROLLED) {
-    int l = id, m = n;
-#pragma unroll 1
-    for (int k = 1; k <= kPartners; ++k) {
-      ++l;
-      m += ST;
-      if (l == n1) {
-        l = 0;
-        m = base;
-      }
-      body(l, m);
-    }
-  } else {
-#pragma unroll
-    for (int k = 1; k <= kPartners; ++k) {
-      const int l = partner(id, k);
-      body(l, base + l * ST);
+      for (int l = 0; l < n1; ++l) body(crow[l], base + l * ST);
     }
   }
+}
+// Entry of the basis' Dhat block that belongs at position t < (N + 1)^2 of the
+// rotated table.
+__device__ __forceinline__ int dhat_index(int t) {
+  const int m = t / n1, id = t - m * n1;
+  if (kPow2) return id * n1 + (id ^ m);
+  const int l = id + m;
+  return id * n1 + (l >= n1 ? l - n1 : l);
 }
 
 // With GRAD, also returns gs[c] = sum_{l != id} Dw_{id l} q_c(l) along the line
 // (q = u, v, w, theta): the off-diagonal part of the BR1 gradient, which
 // reuses the partner values and coefficients the flux loop reads anyway
 // (off the diagonal Dw = D = Dhat / 2 exactly).
-template <int VF, int D, class R, bool GRAD = false>
+template <int VF, int D, class R, bool GRAD, bool ROT>
 __device__ __forceinline__ void volume_dir(const R (*sP)[nnp], const R* sDhat, R wb, int n, int id, const R me[7],
                                            R invJ, R gm1, R acc[5], const R* sDw = nullptr, R* gs = nullptr) {
   constexpr int st = D == 0 ? 1 : (D == 1 ? n1 : nf);
-  const int base = n - id * st;
-  const R* crow = sDhat + id * n1;
   R g0 = 0, g1 = 0, g2 = 0, g3 = 0;
   auto grad_acc = [&](R c, int m) {
     if (GRAD) {
@@ -481,8 +480,7 @@ __device__ __forceinline__ void volume_dir(const R (*sP)[nnp], const R* sDhat, R
     // compile-time offset from the line start.
     const R und_n = me[1 + D];
     R s_A = 0, s_u = 0, s_v = 0, s_w = 0, s_x = 0, s_p = 0, s_E2 = 0;
-    auto pair = [&](int l, int m) {
-      const R c = crow[l];
+    auto pair = [&](R c, int m) {
       grad_acc(c, m);
       const R rl = sP[0][m], ul = sP[1][m], vl = sP[2][m], wl = sP[3][m], pl = sP[4][m], xl = sP[5][m];
       const R undl = D == 0 ? ul : (D == 1 ? vl : wl);
@@ -501,7 +499,12 @@ __device__ __forceinline__ void volume_dir(const R (*sP)[nnp], const R* sDhat, R
         s_p = fmaR(c, pl, s_p);
       }
     };
-    partner_loop<GRAD, st>(id, n, base, pair);
+    auto tie = [&](int& k, int& ic) {
+      if (VF == VF_KG) asm volatile("" : "+v"(k), "+v"(ic), "+v"(s_A), "+v"(s_u), "+v"(s_v), "+v"(s_w), "+v"(s_x), "+v"(s_p), "+v"(s_E2));
+      else asm volatile("" : "+v"(k), "+v"(ic), "+v"(s_A), "+v"(s_u), "+v"(s_v), "+v"(s_w), "+v"(s_x), "+v"(s_p));
+      if (GRAD) asm volatile("" : "+v"(k), "+v"(g0), "+v"(g1), "+v"(g2), "+v"(g3));
+    };
+    partner_loop<ROT, GRAD, st>(id, n, sDhat, pair, tie);
     const R q4 = (R)0.25, q8 = (R)0.125, h2 = (R)0.5;
     R P = s_p;
     if (VF != VF_KG) {
@@ -518,8 +521,7 @@ __device__ __forceinline__ void volume_dir(const R (*sP)[nnp], const R* sDhat, R
     // with the node's own terms taken out of the sums (rowsum as above)
     const R mA = me[0] * me[1 + D];
     R s0 = 0, s1 = 0, s2 = 0, s3 = 0, s4 = 0, sp = 0;
-    auto pair = [&](int l, int m) {
-      const R c = crow[l];
+    auto pair = [&](R c, int m) {
       grad_acc(c, m);
       const R cB = c * (sP[0][m] * sP[1 + D][m]);
       s0 += cB;
@@ -529,7 +531,11 @@ __device__ __forceinline__ void volume_dir(const R (*sP)[nnp], const R* sDhat, R
       s4 = fmaR(cB, sP[5][m], s4);
       sp = fmaR(c, sP[4][m], sp);
     };
-    partner_loop<GRAD, st>(id, n, base, pair);
+    auto tie = [&](int& k, int& ic) {
+      asm volatile("" : "+v"(k), "+v"(ic), "+v"(s0), "+v"(s1), "+v"(s2), "+v"(s3), "+v"(s4), "+v"(sp));
+      if (GRAD) asm volatile("" : "+v"(k), "+v"(g0), "+v"(g1), "+v"(g2), "+v"(g3));
+    };
+    partner_loop<ROT, GRAD, st>(id, n, sDhat, pair, tie);
     const R rowsum = id == 0 ? wb : (id == N ? -wb : (R)0);
     const R mr = mA * rowsum;
     s0 += mr;
@@ -549,11 +555,7 @@ __device__ __forceinline__ void volume_dir(const R (*sP)[nnp], const R* sDhat, R
     double s[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     RotState<double> a;
     a.r = me[0]; a.un = me[1 + D]; a.u1 = me[1 + (D + 1) % 3]; a.u2 = me[1 + (D + 2) % 3]; a.p = me[4];
-#pragma unroll
-    for (int k = 1; k <= kPartners; ++k) {
-      const int l = partner(id, k);
-      const int m = base + l * st;
-      const double c = crow[l];
+    auto pair = [&](double c, int m) {
       grad_acc((R)c, m);
       RotState<double> b;
       b.r = sP[0][m]; b.un = sP[1 + D][m]; b.u1 = sP[1 + (D + 1) % 3][m]; b.u2 = sP[1 + (D + 2) % 3][m];
@@ -565,7 +567,9 @@ __device__ __forceinline__ void volume_dir(const R (*sP)[nnp], const R* sDhat, R
       s[1 + (D + 1) % 3] = fma(c, f[2], s[1 + (D + 1) % 3]);
       s[1 + (D + 2) % 3] = fma(c, f[3], s[1 + (D + 2) % 3]);
       s[4] = fma(c, f[4], s[4]);
-    }
+    };
+    auto tie = [&](int& k, int& ic) { asm volatile("" : "+v"(k), "+v"(ic), "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]), "+v"(s[4])); };
+    partner_loop<ROT, GRAD, st>(id, n, sDhat, pair, tie);
     for (int v = 0; v < 5; ++v) acc[v] -= invJ * (R)s[v];
   }
   if (GRAD) {
@@ -1292,6 +1296,46 @@ __device__ __forceinline__ void own_part_by_lines(const StageArgs& A, int e, int
   }
 }
 
+// Line pass of the viscous divergence: sV[4 d + c][padded node] (component c
+// of the viscous flux in direction d) becomes sum_l Dw_il sV_l along the lines
+// of direction d, in place.  One task per (line, pair of components).  The
+// coefficients come with uniform loads from the constant address space, so a
+// value is read from LDS and written back once per line instead of being read
+// by all n1 nodes of its line together with a coefficient.
+template <class R, int NTHR>
+__device__ __forceinline__ void divergence_lines(const StageArgs& A, R (*sV)[SQP], int tid) {
+  const cdouble_ptr Dw = (cdouble_ptr)(uintptr_t)A.basis + BL.Dw();
+  const int q = tid;
+  static_assert(6 * nf <= NTHR, "one task per thread");
+  if (q < 6 * nf) {
+    const int cp = q >= 3 * nf ? 1 : 0, ql = q - cp * 3 * nf;
+    const int d = ql / nf, a = ql - d * nf;
+    const int st = pstride(d);
+    const int base = (a % n1) * pstride(d == 0 ? 1 : 0) + (a / n1) * pstride(d == 2 ? 1 : 2);
+    R* r0 = sV[4 * d + 2 * cp] + base;
+    R* r1 = r0 + SQP;
+    R v0[n1], v1[n1];
+#pragma unroll
+    for (int l = 0; l < n1; ++l) {
+      v0[l] = r0[l * st];
+      v1[l] = r1[l * st];
+    }
+#pragma unroll
+    for (int i = 0; i < n1; ++i) {
+      R s0 = 0, s1 = 0;
+#pragma unroll
+      for (int l = 0; l < n1; ++l) {
+        if (l == i && i != 0 && i != N) continue;  // Dw_ii = 0 inside
+        const R c = (R)Dw[i * n1 + l];
+        s0 = fmaR(c, v0[l], s0);
+        s1 = fmaR(c, v1[l], s1);
+      }
+      r0[i * st] = s0;
+      r1[i * st] = s1;
+    }
+  }
+}
+
 // Split BR1 lifting: the own part of the normal viscous flux at every face
 // node of the element (into StageArgs.Fvf), from the element's own nodes
 // only; one element per workgroup.  The stage kernel's epilogue does the same
@@ -1323,16 +1367,19 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
   constexpr bool NS = (EQ >= 1);
   constexpr bool LES = (EQ == 2);
   constexpr bool MX = sizeof(R) == 4;
+  constexpr bool ROT = !MX && !BLEND;  // partner order of the volume loop
+  constexpr bool LINES = N >= 5 && N % 2 == 1;  // viscous divergence by lines
+  constexpr int SVP = LINES ? SQP : nnp;        // its LDS row
   static_assert(!(BLEND && MX), "the blended operator is FP64 only");
   static_assert(!WALL || (NS && !MX), "walls: FP64 Navier-Stokes");
   // LDS pool: primitives sP[7][nnp], face fluxes sF[6][5][nf], and for
   // Navier-Stokes the interface values sQ[6][4][nf] and the neighbours' normal
   // viscous fluxes sFn[6][4][nf].  The twelve viscous-flux components of all
-  // nodes are later exchanged through sV[12][nnp], which overlays sP, sF and sQ
+  // nodes are later exchanged through sV[12][SVP], which overlays sP, sF and sQ
   // (all consumed by then) but not sFn.
-  constexpr int oF = 7 * nnp, oQ = oF + 30 * nf, oFn = std::max(oQ + 24 * nf, 12 * nnp);
+  constexpr int oF = 7 * nnp, oQ = oF + 30 * nf, oFn = std::max(oQ + 24 * nf, 12 * SVP);
   constexpr int POOL = NS ? oFn + 24 * nf : oQ;
-  static_assert(!NS || 12 * nnp <= oFn, "viscous exchange must not overlay sFn");
+  static_assert(!NS || 12 * SVP <= oFn, "viscous exchange must not overlay sFn");
   constexpr int EPB = PS::EPB, TPE = PS::TPE, FI = PS::FI;
   __shared__ R sPoolAll[EPB][POOL];
   __shared__ R sB[NB_STAGE];
@@ -1349,7 +1396,7 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
   R (*sF)[5][nf] = reinterpret_cast<R (*)[5][nf]>(sPool + oF);
   R (*sQ)[4][nf] = reinterpret_cast<R (*)[4][nf]>(sPool + (NS ? oQ : 0));
   R (*sFn)[4][nf] = reinterpret_cast<R (*)[4][nf]>(sPool + (NS ? oFn : 0));
-  R (*sV)[nnp] = reinterpret_cast<R (*)[nnp]>(sPool);
+  R (*sV)[SVP] = reinterpret_cast<R (*)[SVP]>(sPool);
   const double gm1 = A.gamma - 1.0;
   // Memory round trip 1: neighbour indices of the thread's face items, the
   // node state and the basis.
@@ -1373,7 +1420,7 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
     for (int v = 0; v < 5; ++v) u[v] = Ue[v * nn + t];
   }
   static_assert(NB_STAGE <= PS::NTB, "one basis entry per thread");
-  const double bval = tid < NB_STAGE ? A.basis[tid] : 0.0;
+  const double bval = tid < NB_STAGE ? A.basis[ROT && tid < nf ? dhat_index(tid) : tid] : 0.0;
   // V^-1 for the indicator of the stage output (blended Euler runs)
   const double vval = (BLEND && !NS && kFusedAlpha1 && tid >= NB_STAGE && tid < NB_STAGE + nf) ? A.basis[tid] : 0.0;
   const Ref ref = MX ? reference_state(A.U, gm1) : Ref{0.0, 0.0, 0.0};
@@ -1413,9 +1460,9 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
   if (t < nn) {
     constexpr bool FG = NS && DG_FUSED_GRAD && !BLEND;
     R gs[3][4];
-    volume_dir<VF, 0, R, FG>(sP, sDhat, swinv[0], t, ijk[0], me, invJ[0], (R)gm1, acc, sDw, gs[0]);
-    volume_dir<VF, 1, R, FG>(sP, sDhat, swinv[0], t, ijk[1], me, invJ[1], (R)gm1, acc, sDw, gs[1]);
-    volume_dir<VF, 2, R, FG>(sP, sDhat, swinv[0], t, ijk[2], me, invJ[2], (R)gm1, acc, sDw, gs[2]);
+    volume_dir<VF, 0, R, FG, ROT>(sP, sDhat, swinv[0], t, ijk[0], me, invJ[0], (R)gm1, acc, sDw, gs[0]);
+    volume_dir<VF, 1, R, FG, ROT>(sP, sDhat, swinv[0], t, ijk[1], me, invJ[1], (R)gm1, acc, sDw, gs[1]);
+    volume_dir<VF, 2, R, FG, ROT>(sP, sDhat, swinv[0], t, ijk[2], me, invJ[2], (R)gm1, acc, sDw, gs[2]);
     // advective surface terms
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
@@ -1546,73 +1593,54 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
     for (int v = 0; v < 5; ++v) gprev[v] = __builtin_nontemporal_load(&A.G[(size_t)e * 5 * nn + t + v * nn]);
   }
   if (NS && !(BLEND && A.mode == MODE_DIFF)) {  // uniform over the workgroup
-    // viscous divergence: all twelve flux components exchanged through LDS
-    // once; with DG_VDIV_LINES a line pass (one thread per line of each
-    // direction, 3 (N+1)^2 lines) replaces the n1 values of every line and
-    // component by sum_l Dw_il Fv_l, in place (lines of one direction are
-    // disjoint and each direction owns four rows), with the coefficients
-    // uniform over the workgroup; each node then reads its 12 sums, instead
-    // of reading n1 partners and coefficients per component.
+    // Viscous divergence: all twelve flux components go through LDS once.
+    // LINES (N = 5, 7; padded rows): one task per (line, pair of components),
+    // 6 (N+1)^2 of them, at most one per thread, replaces the n1 values of its line by
+    // sum_l Dw_il Fv_l in place (the lines of one direction are disjoint and
+    // each direction owns four rows), and every node reads its 12 sums.
+    // Otherwise each node sums its own lines.  Measured, stage kernel with node
+    // sums -> lines: N = 5 380 -> 366 us and N = 7 854 -> 814 us at 32^3; N = 4
+    // (150 tasks for 128 threads) 460 -> 477 us; the mixed N = 6 step on a small
+    // mesh 71 -> 74 us.
     __syncthreads();
+    const int tp = LINES ? padded(t) : t;
     if (t < nn) {
 #pragma unroll
       for (int d = 0; d < 3; ++d)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) sV[4 * d + c][t] = Fv[d][c];
+        for (int c = 0; c < 4; ++c) sV[4 * d + c][tp] = Fv[d][c];
     }
     __syncthreads();
-#if DG_VDIV_LINES
-    // one task per (line, pair of components): 6 (N+1)^2 tasks
-    for (int q = tid; q < 6 * nf; q += PS::NTB) {
-      const int cp = q & 1, ql = q >> 1;
-      const int d = ql / nf, a = ql - d * nf;
-      const int st = d == 0 ? 1 : (d == 1 ? n1 : nf);
-      const int base = face_node(d, 0, a);
-      R* r0 = sV[4 * d + 2 * cp];
-      R* r1 = sV[4 * d + 2 * cp + 1];
-      R v0[n1], v1[n1];
-#pragma unroll
-      for (int l = 0; l < n1; ++l) {
-        v0[l] = r0[base + l * st];
-        v1[l] = r1[base + l * st];
-      }
-#pragma unroll
-      for (int i = 0; i < n1; ++i) {
-        R s0 = 0, s1 = 0;
-#pragma unroll
-        for (int l = 0; l < n1; ++l) {
-          const R c = sDw[i * n1 + l];  // the same address in every lane (broadcast)
-          s0 = fmaR(c, v0[l], s0);
-          s1 = fmaR(c, v1[l], s1);
-        }
-        r0[base + i * st] = s0;
-        r1[base + i * st] = s1;
-      }
+    if constexpr (LINES) {
+      divergence_lines<R, PS::NTB>(A, sV, tid);
+      __syncthreads();
     }
-    __syncthreads();
-#endif
     if (t < nn) {
       const R h2 = (R)0.5;
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
         const int id = ijk[d];
-#if DG_VDIV_LINES
-        R s0 = sV[4 * d + 0][t], s1 = sV[4 * d + 1][t], s2 = sV[4 * d + 2][t], s3 = sV[4 * d + 3][t];
-#else
-        const int st = d == 0 ? 1 : (d == 1 ? n1 : nf);
-        const int base = t - id * st;
-        const R* crow = sDw + id * n1;
-        R s0 = 0, s1 = 0, s2 = 0, s3 = 0;
+        R s0, s1, s2, s3;
+        if constexpr (LINES) {
+          s0 = sV[4 * d + 0][tp];
+          s1 = sV[4 * d + 1][tp];
+          s2 = sV[4 * d + 2][tp];
+          s3 = sV[4 * d + 3][tp];
+        } else {
+          const int st = axis_stride(d);
+          const int base = tp - id * st;
+          const R* crow = sDw + id * n1;
+          s0 = s1 = s2 = s3 = 0;
 #pragma unroll
-        for (int l = 0; l < n1; ++l) {
-          const int m = base + l * st;
-          const R c = crow[l];
-          s0 = fmaR(c, sV[4 * d + 0][m], s0);
-          s1 = fmaR(c, sV[4 * d + 1][m], s1);
-          s2 = fmaR(c, sV[4 * d + 2][m], s2);
-          s3 = fmaR(c, sV[4 * d + 3][m], s3);
+          for (int l = 0; l < n1; ++l) {
+            const int m = base + l * st;
+            const R c = crow[l];
+            s0 = fmaR(c, sV[4 * d + 0][m], s0);
+            s1 = fmaR(c, sV[4 * d + 1][m], s1);
+            s2 = fmaR(c, sV[4 * d + 2][m], s2);
+            s3 = fmaR(c, sV[4 * d + 3][m], s3);
+          }
         }
-#endif
         const int a = d == 0 ? ijk[1] + n1 * ijk[2] : (d == 1 ? ijk[0] + n1 * ijk[2] : ijk[0] + n1 * ijk[1]);
         if (id == 0 || id == N) {  // F*v = mean with the neighbour's normal viscous flux (sFn)
           const int f = 2 * d + (id == N);
@@ -2590,8 +2618,7 @@ __device__ __forceinline__ void volume_vjp_dir(const double (*sP)[nn], const dou
   constexpr int st = D == 0 ? 1 : (D == 1 ? n1 : nf);
   const int base = n - id * st;
 #pragma unroll 1
-  for (int k = 1; k <= kPartners; ++k) {
-    const int l = partner(id, k);
+  for (int l = 0; l < n1; ++l) {
     const int m = base + l * st;
     const double c1 = -invJ * sDhat[id * n1 + l], c2 = -invJ * sDhat[l * n1 + id];
     double w[5];
@@ -3572,12 +3599,9 @@ __device__ __forceinline__ void volume_dir_curved(const double (*sP)[nnp], const
                                                   const double* sDhat, int n, int id, const double me[7],
                                                   const double jo[3], double acc[5], double* gs) {
   constexpr int st = D == 0 ? 1 : (D == 1 ? n1 : nf);
-  const int base = n - id * st;
-  const double* crow = sDhat + id * n1;
   double g0 = 0, g1 = 0, g2 = 0, g3 = 0;
   double s0 = 0, s1 = 0, s2 = 0, s3 = 0, s4 = 0, px = 0, py = 0, pz = 0, s5 = 0;
-  auto pair = [&](int l, int m) {
-    const double c = crow[l];
+  auto pair = [&](double c, int m) {
     if (GRAD) {
       g0 = fma(c, sP[1][m], g0);
       g1 = fma(c, sP[2][m], g1);
@@ -3617,7 +3641,11 @@ __device__ __forceinline__ void volume_dir_curved(const double (*sP)[nnp], const
       if (VF == VF_KG) s5 = fma(cp, un, s5);
     }
   };
-  partner_loop<true, st>(id, n, base, pair);
+  auto tie = [&](int& k, int& ic) {
+    asm volatile("" : "+v"(k), "+v"(ic), "+v"(s0), "+v"(s1), "+v"(s2), "+v"(s3), "+v"(s4), "+v"(px), "+v"(py), "+v"(pz), "+v"(s5));
+    if (GRAD) asm volatile("" : "+v"(k), "+v"(g0), "+v"(g1), "+v"(g2), "+v"(g3));
+  };
+  partner_loop<true, true, st>(id, n, sDhat, pair, tie);
   if (VF == VF_STD) {
     acc[0] -= 0.25 * s0;
     acc[1] -= 0.25 * (s1 + px);
@@ -3680,7 +3708,7 @@ __global__ __launch_bounds__(NT, DG_N == 5 ? 3 : 1) void k_stage_curved(StageArg
 #pragma unroll
     for (int k = 0; k < MS; ++k) mt[k] = Me[k * nn + t];
   }
-  const double bval = t < NB_STAGE ? A.basis[t] : 0.0;
+  const double bval = t < NB_STAGE ? A.basis[t < nf ? dhat_index(t) : t] : 0.0;
 #pragma unroll
   for (int k = 0; k < FIC; ++k)
     if (t + k * NT < 6 * nf) curved_face_issue<NS>(A, e, cf[k]);
@@ -4110,8 +4138,7 @@ __device__ __forceinline__ void volume_vjp_dir_curved(const double (*sP)[nn], co
   constexpr int st = D == 0 ? 1 : (D == 1 ? n1 : nf);
   const int base = n - id * st;
 #pragma unroll 1
-  for (int k = 1; k <= kPartners; ++k) {
-    const int l = partner(id, k);
+  for (int l = 0; l < n1; ++l) {
     const int m = base + l * st;
     const double c1 = -sDhat[id * n1 + l], c2 = -sDhat[l * n1 + id];
     double w[5];
