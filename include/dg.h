@@ -81,12 +81,13 @@ enum { DG_FP64 = 0, DG_MIXED = 1 };
  * p/rho) on every face).
  *   TWO_PASS: every stage first lifts the normal viscous flux at all face
  *     nodes (one kernel), then evaluates the operator.
- *   SPLIT: the same operator up to rounding, with the lifting split into each
- *     element's own half of q*, which the stage kernel of a Runge-Kutta stage
- *     writes for the next stage, and the rest, which the stage kernel adds
- *     where it reads the neighbour's face data; a step lifts only before its
- *     first stage.  Applies to the FP64 operator without the eddy viscosity,
- *     blending, walls or curved geometry; elsewhere TWO_PASS runs. */
+ *   SPLIT: the same operator up to rounding, with the viscous surface term
+ *     split into the element's own half, which the stage kernel adds and
+ *     leaves at its face nodes, and the neighbour's half, which the next stage
+ *     adds where it reads the state and the register (at the end of a call a
+ *     completion kernel does).  Runs for every FP64 Navier-Stokes operator; with
+ *     the eddy viscosity, blending, walls or curved geometry both choices run
+ *     it, and the mixed operator always runs TWO_PASS. */
 enum { DG_LIFT_TWO_PASS = 0, DG_LIFT_SPLIT = 1 };
 
 typedef struct dg_ctx dg_ctx; /* opaque, library-owned */

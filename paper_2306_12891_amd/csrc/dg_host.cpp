@@ -189,7 +189,7 @@ struct dg_ctx {
   double* alpha1b = nullptr;  // the other of the pair the fused indicator ping-pongs
   double* alpha = nullptr;
   double* Fvf = nullptr;
-  double* Fvf2 = nullptr;  // split BR1: the own part of the next stage state (allocated on first use)
+  double* Fvf2 = nullptr;  // deferred viscous exchange: the other of the pair (allocated on first use)
   double* cs_field = nullptr;  // per-element Smagorinsky coefficients (dg_set_cs_field)
   int has_cs_field = 0;
   double* M = nullptr;         // curved mesh metrics [nelem][10][nn] (dg_set_geometry), NULL: box
@@ -279,7 +279,6 @@ StageArgs stage_args(const dg_ctx* c) {
   a.nbr = c->nbr;
   a.basis = c->basis;
   a.alpha1 = c->alpha1;
-  a.Fvf = c->Fvf;
   for (int d = 0; d < 3; ++d) a.invJ[d] = c->invJ[d];
   a.gamma = c->gamma;
   a.mu = c->mu;
@@ -368,40 +367,85 @@ hipError_t timed(dg_ctx* c, int kind, F&& launch) {
   return e;
 }
 
-// Split BR1 (see StageArgs.split): used for the FP64 Navier-Stokes operator
-// without the eddy viscosity, blending, walls or curved geometry when the
-// options ask for it.
-bool split_on(const dg_ctx* c) {
-  return c->opt.lifting == DG_LIFT_SPLIT && eq_code(c) == 1 && c->opt.precision == DG_FP64 && !c->opt.blending &&
-         c->wall_dir < 0 && !c->M && !c->conn;
+// Deferred viscous exchange (see StageArgs.Fcarry): the FP64 Navier-Stokes
+// operator, unless the options ask for the two-pass lifting and it is built
+// (no eddy viscosity, blending, walls or curved geometry).
+bool deferred_on(const dg_ctx* c) {
+  const int eq = eq_code(c);
+  if (eq == 0 || c->opt.precision != DG_FP64) return false;
+  return c->opt.lifting == DG_LIFT_SPLIT || eq == 2 || c->opt.blending || c->wall_dir >= 0 || c->M;
 }
 
-// Chaining of the split lifting through the stages of one Runge-Kutta step:
-// CHAIN_IN: c->Fvf already holds the own part of X_in (the previous stage
-// wrote it), so no lifting launch; CHAIN_OUT: the stage kernel writes the own
-// part of X_out for the next stage.  Ignored unless split_on.
-enum { CHAIN_IN = 1, CHAIN_OUT = 2 };
+// What a state and the register still await from the stage that wrote them:
+// the neighbours' halves of the viscous surface terms, from that stage's face
+// fluxes F (NULL: nothing) with its B_k dt; state: the state awaits it too (it
+// does until a kernel completes it, the register until the next stage reads it).
+struct Carry {
+  double* F = nullptr;
+  double B = 0.0;
+  bool state = false;
+};
 
-// Chain flags of stage k of a step whose last stage that chains is klast.
-int chain_flags(int k, int klast) { return (k > 0 ? CHAIN_IN : 0) | (k < klast ? CHAIN_OUT : 0); }
-
-int ensure_split_buffer(dg_ctx* c) {
-  if (!split_on(c) || c->Fvf2) return DG_OK;
-  const hipError_t e = hipMalloc((void**)&c->Fvf2, (size_t)c->nelem * 6 * 4 * c->nf * sizeof(double));
-  if (e != hipSuccess) {
+// The second face buffer, which lets a stage read the fluxes of the stage
+// before while it writes its own.  Without it (no memory, or the stream is
+// being captured and the first call did not come before) every stage completes
+// its state and register by a pass of its own: the same results.
+void ensure_carry_buffer(dg_ctx* c) {
+  if (!deferred_on(c) || c->Fvf2) return;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return;
+  }
+  if (hipMalloc((void**)&c->Fvf2, (size_t)c->nelem * 6 * 4 * c->nf * sizeof(double)) != hipSuccess) {
     (void)hipGetLastError();
     c->Fvf2 = nullptr;
-    return fail(c, (e == hipErrorOutOfMemory) ? DG_ENOMEM : DG_EHIP, "split lifting buffer: %s", hipGetErrorString(e));
+  }
+}
+
+// X = Xin + B S (X may be Xin), and G += S where given.
+int complete_state(dg_ctx* c, const double* Xin, double* X, const double* F, double B, double* G) {
+  StageArgs a = stage_args(c);
+  a.U = Xin;
+  a.G = G;
+  a.Fcarry = F;
+  a.Bcarry = B;
+  const hipError_t e = timed(c, DG_K_LIFT, [&] { return c->kt->complete(a, X, c->stream); });
+  return e != hipSuccess ? hip_fail(c, e, "completion kernel") : DG_OK;
+}
+
+// The state that a chain of stages left in cur, complete, in U.
+int settle(dg_ctx* c, const Carry& k, const double* cur, double* U, const char* where) {
+  if (k.state) return complete_state(c, cur, U, k.F, k.B, nullptr);
+  if (cur != U) {
+    const hipError_t e = hipMemcpyAsync(U, cur, c->nstate * sizeof(double), hipMemcpyDeviceToDevice, c->stream);
+    if (e != hipSuccess) return hip_fail(c, e, where);
   }
   return DG_OK;
 }
 
-// One evaluation of the operator on X_in: [indicator], [BR1 lifting], stage.
+// One evaluation of the operator on X_in: [indicator], [two-pass lifting or
+// wall fluxes], stage, and with the deferred exchange and U_t its completion.
 // alpha1_next (blending, MODE_RK): the stage kernel writes the coefficients of
 // X_out there, and the indicator of X_in is taken as already in c->alpha1.
-// chain: CHAIN_* flags (split BR1, MODE_RK; needs ensure_split_buffer).
+// carry (MODE_RK with the deferred exchange): what X_in and the register await;
+// on return what X_out and the register await.  X_in is completed in place
+// where the stage kernel does not do it on the fly (blended, curved).  Yout:
+// the stage kernel also writes the completed X_in there (deferred box only).
 int run_stage(dg_ctx* c, const double* Xin, double* Xout, double* Ut, int mode, double A, double Bdt, int writeG,
-              double* alpha_out, double* alpha1_next = nullptr, int chain = 0) {
+              double* alpha_out, double* alpha1_next = nullptr, Carry* carry = nullptr, double* Yout = nullptr) {
+  const int eq = eq_code(c);
+  const bool deferred = deferred_on(c);
+  Carry none;
+  Carry& k = carry ? *carry : none;
+  if (k.F && (!c->Fvf2 || (k.state && c->M))) {
+    if (k.state || !c->Fvf2) {
+      const int rc = complete_state(c, Xin, const_cast<double*>(Xin), k.F, k.B, c->Fvf2 ? nullptr : c->G);
+      if (rc) return rc;
+    }
+    k.state = false;
+    if (!c->Fvf2) k.F = nullptr;
+  }
   StageArgs a = stage_args(c);
   a.U = Xin;
   a.Uout = Xout;
@@ -413,34 +457,26 @@ int run_stage(dg_ctx* c, const double* Xin, double* Xout, double* Ut, int mode, 
   a.writeG = writeG;
   a.alpha_out = alpha_out;
   a.alpha1_next = alpha1_next;
+  if (deferred) {
+    a.Fcarry = k.F;
+    a.Bcarry = k.B;
+    a.carryU = k.state ? 1 : 0;
+    a.Fvf_out = k.F == c->Fvf ? c->Fvf2 : c->Fvf;
+    a.Yout = Yout;
+  }
   hipError_t e;
   if (c->opt.blending && !alpha1_next) {
     e = timed(c, DG_K_INDICATOR, [&] { return c->kt->alpha1(a, c->stream); });
     if (e != hipSuccess) return hip_fail(c, e, "indicator kernel");
+    a.carryU = 0;  // completed in place
   }
-  const int eq = eq_code(c);
   if (c->conn && !c->M)
     return fail(c, DG_ESTATE, "general connectivity needs curved elements: call dg_set_geometry first");
   if (c->wall_dir >= 0 && (eq == 0 || c->opt.precision != DG_FP64 || c->M))
     return fail(c, DG_ESTATE, "wall-modelled boundaries need the FP64 Navier-Stokes operator on the box");
-  if (c->M) {  // curved mesh (FP64, no blending: checked when set)
-    if (eq >= 1) {
-      e = timed(c, DG_K_LIFT, [&] { return c->kt->lift_curved(a, eq, c->stream); });
-      if (e != hipSuccess) return hip_fail(c, e, "lifting kernel (curved)");
-    }
-    e = timed(c, DG_K_STAGE, [&] { return c->kt->stage_curved(a, eq, c->stream); });
-    if (e != hipSuccess) return hip_fail(c, e, "stage kernel (curved)");
-    return DG_OK;
-  }
   const bool mixed = c->opt.precision == DG_MIXED;
-  const bool split = split_on(c);
-  if (!split || mode != MODE_RK) chain = 0;
-  if (split) {
-    a.split = 1;
-    if ((chain & CHAIN_OUT) && !c->Fvf2) return fail(c, DG_ESTATE, "split lifting buffer missing");
-    a.Fvf_next = (chain & CHAIN_OUT) ? c->Fvf2 : nullptr;
-  }
-  if (eq >= 1 && !(chain & CHAIN_IN)) {
+  if (eq >= 1 && !deferred) {
+    a.Fvf = c->Fvf;
     e = timed(c, DG_K_LIFT,
               [&] { return mixed ? c->kt->lift_mixed(a, eq, c->stream) : c->kt->lift(a, eq, c->stream); });
     if (e != hipSuccess) return hip_fail(c, e, "lifting kernel");
@@ -449,10 +485,17 @@ int run_stage(dg_ctx* c, const double* Xin, double* Xout, double* Ut, int mode, 
     e = timed(c, DG_K_LIFT, [&] { return c->kt->wall_flux(a, c->stream); });
     if (e != hipSuccess) return hip_fail(c, e, "wall-model kernel");
   }
-  e = timed(c, DG_K_STAGE,
-            [&] { return mixed ? c->kt->stage_mixed(a, eq, c->stream) : c->kt->stage(a, eq, c->stream); });
+  e = timed(c, DG_K_STAGE, [&] {
+    if (c->M) return c->kt->stage_curved(a, eq, c->stream);  // FP64, no blending: checked when set
+    return mixed ? c->kt->stage_mixed(a, eq, c->stream) : c->kt->stage(a, eq, c->stream);
+  });
   if (e != hipSuccess) return hip_fail(c, e, "stage kernel");
-  if (a.Fvf_next) std::swap(c->Fvf, c->Fvf2);  // the own part of X_out is now c->Fvf
+  if (deferred && mode == MODE_UT) return complete_state(c, Ut, Ut, a.Fvf_out, 1.0, nullptr);
+  if (deferred && mode == MODE_RK) {
+    k.F = a.Fvf_out;
+    k.B = Bdt;
+    k.state = true;
+  }
   return DG_OK;
 }
 
@@ -953,8 +996,9 @@ int dg_rk_steps(dg_ctx* c, double* U, double dt, int nsteps) {
   if (!is_device_ptr(U)) return fail(c, DG_EINVAL, "rk_step: U must be a device pointer");
   if (!finite_pos(dt)) return fail(c, DG_EINVAL, "rk_step: dt must be finite and > 0");
   if (nsteps < 0) return fail(c, DG_EINVAL, "rk_step: nsteps < 0");
-  if (const int rc = ensure_split_buffer(c)) return rc;
+  ensure_carry_buffer(c);
   double* cur = U;
+  Carry carry;
   // blended Euler operator: the indicator of the start state once, then each
   // stage kernel writes that of its output for the next stage (alpha1 /
   // alpha1b ping-pong); Navier-Stokes keeps the separate indicator launch
@@ -969,19 +1013,13 @@ int dg_rk_steps(dg_ctx* c, double* U, double dt, int nsteps) {
     for (int k = 0; k < 5; ++k) {
       double* nxt = (cur == U) ? c->U2 : U;
       const int writeG = (k < 4) ? 1 : 0;  // the last stage's register is never read again
-      // every step starts from a lifting of its start state, so that n steps
-      // in one call and n calls of one step agree bitwise
       const int rc = run_stage(c, cur, nxt, nullptr, MODE_RK, kA[k], kB[k] * dt, writeG, nullptr,
-                               fuse ? c->alpha1b : nullptr, chain_flags(k, 4));
+                               fuse ? c->alpha1b : nullptr, &carry);
       if (rc) return rc;
       if (fuse) std::swap(c->alpha1, c->alpha1b);
       cur = nxt;
     }
-  if (cur != U) {
-    hipError_t e = hipMemcpyAsync(U, cur, c->nstate * sizeof(double), hipMemcpyDeviceToDevice, c->stream);
-    if (e != hipSuccess) return hip_fail(c, e, "rk_step copy");
-  }
-  return DG_OK;
+  return settle(c, carry, cur, U, "rk_step copy");
 }
 
 int rk_step(dg_ctx* c, double* U, double dt) { return dg_rk_steps(c, U, dt, 1); }
@@ -1056,15 +1094,29 @@ int rk_step_record(dg_ctx* c, double* U, double dt, double* Y) {
   if (!finite_pos(dt)) return fail(c, DG_EINVAL, "rk_step_record: dt must be finite and > 0");
   const size_t n = c->nstate;
   if (overlaps(U, n, Y, 5 * n)) return fail(c, DG_EINVAL, "rk_step_record: Y overlaps U");
-  if (const int rc = ensure_split_buffer(c)) return rc;
+  ensure_carry_buffer(c);
+  Carry carry;
+  if (deferred_on(c) && !c->M && c->Fvf2) {
+    // the chain runs through U and the scratch state; each stage kernel writes
+    // the completed state it reads to the record
+    double* cur = U;
+    for (int k = 0; k < 5; ++k) {
+      double* nxt = (cur == U) ? c->U2 : U;
+      const int rc = run_stage(c, cur, nxt, nullptr, MODE_RK, kA[k], kB[k] * dt, k < 4 ? 1 : 0, nullptr, nullptr, &carry,
+                               Y + k * n);
+      if (rc) return rc;
+      cur = nxt;
+    }
+    return settle(c, carry, cur, U, "rk_step_record copy");
+  }
   hipError_t e = hipMemcpyAsync(Y, U, n * sizeof(double), hipMemcpyDeviceToDevice, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "rk_step_record copy");
-  for (int k = 0; k < 4; ++k) {
-    const int rc = run_stage(c, Y + k * n, Y + (k + 1) * n, nullptr, MODE_RK, kA[k], kB[k] * dt, 1, nullptr, nullptr,
-                             chain_flags(k, 4));
+  for (int k = 0; k < 5; ++k) {
+    const int rc = run_stage(c, Y + k * n, k < 4 ? Y + (k + 1) * n : U, nullptr, MODE_RK, kA[k], kB[k] * dt,
+                             k < 4 ? 1 : 0, nullptr, nullptr, &carry);
     if (rc) return rc;
   }
-  return run_stage(c, Y + 4 * n, U, nullptr, MODE_RK, kA[4], kB[4] * dt, 0, nullptr, nullptr, chain_flags(4, 4));
+  return settle(c, carry, U, U, "rk_step_record copy");
 }
 
 int rk_step_vjp_recorded(dg_ctx* c, const double* Y, double dt, const double* U_bar_np1, double* U_bar_n) {
@@ -1091,15 +1143,27 @@ int rk_step_vjp(dg_ctx* c, const double* U_n, double dt, const double* U_bar_np1
   int rc = vjp_supported(c);
   if (rc) return rc;
   if ((rc = ensure_reverse_buffers(c, true))) return rc;
-  if ((rc = ensure_split_buffer(c))) return rc;
-  const size_t bytes = c->nstate * sizeof(double);
-  hipError_t e = hipMemcpyAsync(c->Y[0], U_n, bytes, hipMemcpyDeviceToDevice, c->stream);
-  if (e != hipSuccess) return hip_fail(c, e, "rk_step_vjp copy");
+  ensure_carry_buffer(c);
+  Carry carry;
   // forward: stage states Y_1..Y_4 (Y_5 = U_{n+1} is not needed)
-  for (int k = 0; k < 4; ++k)
-    if ((rc = run_stage(c, c->Y[k], c->Y[k + 1], nullptr, MODE_RK, kA[k], kB[k] * dt, 1, nullptr, nullptr,
-                        chain_flags(k, 3))))
-      return rc;
+  if (deferred_on(c) && !c->M && c->Fvf2) {
+    // the chain alternates between the scratch state and Y_4's array; the stage
+    // kernels write the completed states
+    const double* cur = U_n;
+    for (int k = 0; k < 4; ++k) {
+      double* nxt = (k % 2 == 0) ? c->U2 : c->Y[4];
+      if ((rc = run_stage(c, cur, nxt, nullptr, MODE_RK, kA[k], kB[k] * dt, 1, nullptr, nullptr, &carry, c->Y[k])))
+        return rc;
+      cur = nxt;
+    }
+  } else {
+    hipError_t e = hipMemcpyAsync(c->Y[0], U_n, c->nstate * sizeof(double), hipMemcpyDeviceToDevice, c->stream);
+    if (e != hipSuccess) return hip_fail(c, e, "rk_step_vjp copy");
+    for (int k = 0; k < 4; ++k)
+      if ((rc = run_stage(c, c->Y[k], c->Y[k + 1], nullptr, MODE_RK, kA[k], kB[k] * dt, 1, nullptr, nullptr, &carry)))
+        return rc;
+  }
+  if ((rc = settle(c, carry, c->Y[4], c->Y[4], "rk_step_vjp copy"))) return rc;
   const double* Ys[5] = {c->Y[0], c->Y[1], c->Y[2], c->Y[3], c->Y[4]};
   return rk_reverse(c, Ys, dt, U_bar_np1, U_bar_n, "rk_step_vjp");
 }

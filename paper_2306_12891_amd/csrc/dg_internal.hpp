@@ -35,7 +35,9 @@ struct StageArgs {
   const double* basis;  // BasisLayout
   const double* alpha1; // per element, clipped coefficient before spreading
   double* alpha_out;    // optional: final blending coefficient per element
-  double* Fvf;          // NS: [nelem][6][4][nf] normal viscous flux on own faces
+  // two-pass lifting: [nelem][6][4][nf] normal viscous flux at the face nodes
+  // of the input state (FP32 in the mixed operator); NULL: deferred exchange
+  double* Fvf;
   double invJ[3];       // 2 / dx_d
   double gamma, mu, kappa;  // kappa = mu gamma / ((gamma - 1) Pr)
   double A, Bdt;        // RK stage coefficients (A_k, B_k dt)
@@ -66,19 +68,19 @@ struct StageArgs {
   // first-stage coefficient of its output state per element here (NULL: not;
   // only where KernelTable.fused_alpha1 is set)
   double* alpha1_next;
-  // Split BR1 (FP64 Navier-Stokes without the eddy viscosity, walls or
-  // blending, on the box): split != 0 makes Fvf hold each element's "own
-  // part" of its normal viscous flux at its face nodes -- the flux of the
-  // lifted gradient whose interface values q* = (q- + q+)/2 keep only the
-  // element's own half -- and the stage kernel adds the neighbour-dependent
-  // rest itself (it is linear in the other halves: the own element's face
-  // values and, at the face's edges, those of the diagonal elements).  In
-  // MODE_RK the stage kernel then also writes the own part of its output
-  // state into Fvf_next (NULL: not), so that a Runge-Kutta run needs the
-  // lifting kernel only before its first stage.  The lifting kernel with
-  // split != 0 writes the own part.
-  double* Fvf_next;
-  int split;
+  // Deferred viscous exchange (FP64 Navier-Stokes; Fvf NULL): the stage kernel
+  // adds its own half of the viscous surface term and writes its normal viscous
+  // flux at its face nodes to Fvf_out, laid out as Fvf (wall faces: the wall
+  // model's flux, written there by wall_flux before it).  Fcarry: the fluxes the
+  // stage that wrote the input state and the register left there (NULL: both
+  // are complete); the register is completed with them, and with carryU != 0
+  // the input state too, Bcarry being that stage's B_k dt.  Yout (or NULL):
+  // the completed input state is also written there.
+  const double* Fcarry;
+  double* Fvf_out;
+  double* Yout;
+  double Bcarry;
+  int carryU;
 };
 
 struct ReduceArgs {
@@ -136,6 +138,9 @@ struct KernelTable {
   hipError_t (*stage_mixed)(const StageArgs&, int eq, hipStream_t);
   hipError_t (*lift)(const StageArgs&, int eq, hipStream_t);
   hipError_t (*lift_mixed)(const StageArgs&, int eq, hipStream_t);
+  // X = U + Bcarry S with the carry S of Fcarry (X may be U), and G += S where
+  // G is set; box or curved
+  hipError_t (*complete)(const StageArgs&, double* X, hipStream_t);
   hipError_t (*alpha1)(const StageArgs&, hipStream_t);
   hipError_t (*spread)(const StageArgs&, hipStream_t);
   hipError_t (*max_rate)(const ReduceArgs&, hipStream_t);
@@ -162,12 +167,11 @@ struct KernelTable {
   hipError_t (*metrics)(const double* X, const double* basis, double* M, int* bad, double* d2, int nelem,
                         int chunk, hipStream_t);
   hipError_t (*stage_curved)(const StageArgs&, int eq, hipStream_t);
-  hipError_t (*lift_curved)(const StageArgs&, int eq, hipStream_t);
   // reverse mode on curved elements (FP64, no blending; eq as for vjp, the
   // pass-1 variant per VjpArgs.les)
   hipError_t (*vjp_curved)(const VjpArgs&, int eq, hipStream_t);
   hipError_t (*vjp_lift_curved)(const VjpArgs&, hipStream_t);
-  // wall-model flux at the wall face nodes into Fvf (FP64, after the lift)
+  // wall-model flux at the wall face nodes into Fvf_out (FP64, before the stage)
   hipError_t (*wall_flux)(const StageArgs&, hipStream_t);
 };
 

@@ -840,12 +840,6 @@ __device__ __forceinline__ void wall_face_loads(const double* U, int e, const Fa
   else L[1] = -X[1];
 }
 
-template <bool WALL>
-__device__ __forceinline__ void face_loads_w(const double* U, int e, const FaceItem& it, double L[5], double R[5]) {
-  if (WALL && it.nb < 0) wall_face_loads(U, e, it, L, R);
-  else face_loads(U, e, it, L, R);
-}
-
 // Elements per workgroup (EPB) of the stage and lifting kernels.  With one
 // element per workgroup, N = 5 fills 216 of 256 lanes (the last wave is 3/8
 // full) and a wave instruction costs the same whatever its active lanes; two
@@ -893,130 +887,159 @@ __device__ __forceinline__ Slot slot_of_thread(int e0, int nelem) {
   return r;
 }
 
-// Loads of one face item, issued together before any of them is used: both
-// rotated states and (Navier-Stokes) the neighbour's normal viscous flux.
-// At a wall (WALL variant, neighbour -1) fn is the wall-model flux, read from
-// the element's own slot of the wall face.
-// Split BR1 (StageArgs.split): at a face node of the element's face f (normal
-// direction d, side s), the neighbour n's lifted gradient differs from its own
-// part (the one n's Fvf holds) by the other halves of the interface values at
-// that node: across the shared face the element's own q (normal derivative,
-// weight c_d), and across n's lateral faces where the node lies on an edge
-// of the face, the q of the diagonal element (n's neighbour there; weight
-// c_g).  On the structured periodic box the diagonal element across n's
-// lateral face is n shifted as the element is by its own neighbour there
-// (n + nbr(e, lateral) - e; the shift along the lateral direction does not
-// depend on the coordinate along d), and its node is n's face node moved to
-// the other side along the lateral direction; each edge face item loads the
-// density and momenta of its one or two diagonal nodes with the face states.
-struct Lateral {
-  int dir, side;  // n's lateral face (direction, side) through the node
-};
-template <bool SPLIT>
-struct SplitLoads {
-  int nlat = 0;
-  Lateral lat[2];
-  double dg[2][3];  // rho, m_d, m_dg of the diagonal nodes (d: the face normal)
-};
-template <>
-struct SplitLoads<false> {};
-
-// The (up to two) lateral faces of the neighbour across face item it, and the
-// loads of the diagonal nodes (element e with the neighbours nb6).
-__device__ __forceinline__ void split_issue(const StageArgs& A, const FaceItem& it, const Nbr6& nb6, int e,
-                                            SplitLoads<true>& sp) {
-  const int da = it.d == 0 ? 1 : 0, db = it.d == 2 ? 1 : 2;  // tangential directions, t1 along da
-  const int t1 = it.a % n1, t2 = it.a / n1;
-  // slots filled with fixed indices (selects, no indexed scratch array)
-  const bool e1 = t1 == 0 || t1 == N, e2 = t2 == 0 || t2 == N;
-  sp.nlat = (e1 ? 1 : 0) + (e2 ? 1 : 0);
-  sp.lat[0] = Lateral{e1 ? da : db, e1 ? (t1 == N ? 1 : 0) : (t2 == N ? 1 : 0)};
-  sp.lat[1] = Lateral{db, t2 == N ? 1 : 0};
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    if (j >= sp.nlat) break;
-    const int dg = sp.lat[j].dir, sg = sp.lat[j].side;
-    const int diag = it.nb + nb6.pick(2 * dg + sg) - e;
-    const int node = it.nnb + (sg ? -N : N) * (dg == 0 ? 1 : (dg == 1 ? n1 : nf));
-    const double* Ud = A.U + (size_t)diag * 5 * nn + node;
-    sp.dg[j][0] = Ud[0];
-    sp.dg[j][1] = Ud[(1 + it.d) * nn];
-    sp.dg[j][2] = Ud[(1 + dg) * nn];
-  }
-}
-
+// Deferred viscous exchange (FP64 Navier-Stokes, box).  The viscous surface
+// term at a face node is w (F_own + F_nb) / 2 in the normal viscous fluxes of
+// both elements, and F_nb needs the neighbour's full lifted gradient.  Instead
+// of a pass that lifts every element before each stage, the stage kernel adds
+// its own half only and writes F_own at its face nodes (StageArgs.Fvf_out);
+// the neighbour's half
+//   S_c(node) = sum over the faces with the node  c_d F_nb,c,  c_d = +-(2/dx_d) / (2 w_0),
+// follows one launch later (the carry): the next stage kernel completes the
+// states it reads, u = u~ + B S, and the register, G = G~ + S, with F_nb of the
+// stage before (StageArgs.Fcarry), and k_complete does the same for a state
+// that is handed out.  S is summed over the directions in order and added by
+// one fma wherever it is formed, so every reader of a node gets the same bits.
+// A node of the neighbour's face needs, besides the element's own flux there,
+// those of the neighbour's lateral neighbours where it lies on an edge of the
+// face: on the structured box the element across the neighbour's lateral face
+// is nb + nbr(e, lateral) - e (the shift along the lateral direction does not
+// depend on the coordinate along the face normal).  Density has no carry.
 __device__ __forceinline__ double pick3(const double v[3], int d) { return d == 0 ? v[0] : (d == 1 ? v[1] : v[2]); }
 
-// The neighbour-dependent rest of the neighbour's normal viscous flux at face
-// item it (split BR1), added to fn (in the face frame: normal, t1, t2 and
-// energy components): the viscous flux (linear in the gradient for constant
-// viscosity) of the gradient made of the other halves, with the neighbour's
-// velocity at the node, written out for its few non-zero terms.  own / nb:
-// the element's and the neighbour's face states (rotated frame, FP64).
-//   normal half g_d = c_d q_e:   tau_nn = 4/3 mu c_d u_n,e, tau_tn = mu c_d u_t,e;
-//   lateral half g_dg = c_g u_g: tau_dg,n += mu c_g u_n,g, tau_nn -= 2/3 mu c_g u_dg,g;
-//   F_E = u_nb . tau_n + kappa c_d theta_e.
-__device__ __forceinline__ void split_rest(const StageArgs& A, const FaceItem& it, const State64& own,
-                                           const State64& nb, const SplitLoads<true>& sp, double fn[4]) {
-  // (1/w_0) / 2, w_0 = w_N: a uniform load through the constant address space
-  const double hw = 0.5 * ((const double __attribute__((address_space(4)))*)(uintptr_t)A.basis)[BL.winv()];
-  const double mu = A.mu;
-  const double cd = pick3(A.invJ, it.d) * (it.side ? -hw : hw);
-  double tnn = (4.0 / 3.0) * mu * cd * own.un;
-  double t1 = mu * cd * own.u1, t2 = mu * cd * own.u2;
-  double fe = A.kappa * cd * own.p * own.ir;
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    if (j >= sp.nlat) break;
-    const int dg = sp.lat[j].dir;
-    const double cg = pick3(A.invJ, dg) * (sp.lat[j].side ? hw : -hw) * rcp64(sp.dg[j][0]);
-    const double sh = mu * cg * sp.dg[j][1];                    // tau_dg,n
-    const double dv = (2.0 / 3.0) * mu * cg * sp.dg[j][2];     // from the divergence
-    tnn -= dv;
-    const bool first = dg == (it.d == 2 ? 0 : it.d + 1);        // dg is the t1 direction
-    if (first) t1 += sh;
-    else t2 += sh;
-  }
-  fe += nb.un * tnn + nb.u1 * t1 + nb.u2 * t2;
-  fn[0] += tnn;  // fn in the face frame
-  fn[1] += t1;
-  fn[2] += t2;
-  fn[3] += fe;
+// (1/w_0) / 2, w_0 = w_N: a uniform load through the constant address space.
+using cdouble_ptr = const double __attribute__((address_space(4)))*;
+__device__ __forceinline__ double half_winv(const double* basis) {
+  return 0.5 * ((cdouble_ptr)(uintptr_t)basis)[BL.winv()];
 }
 
-template <bool NS, class R, bool WALL = false, bool SPLIT = false>
+// Carry loads of a face item: the neighbour's flux fn and the element's own fo
+// at the shared face, and those across the neighbour's lateral faces, fl[0]
+// along the lower tangential direction, fl[1] along the higher (rotated
+// components; weight cl, 0 where the node is not on that edge or the lateral
+// face is a wall).
+struct CarryLoads {
+  double fn[4], fo[4], fl[2][4], cl[2];
+};
+
+__device__ __forceinline__ void load_flux_rotated(const double* F, const FaceItem& it, double f[4]) {
+  f[0] = F[it.d * nf];
+  f[1] = F[(it.k1 - 1) * nf];
+  f[2] = F[(it.k2 - 1) * nf];
+  f[3] = F[3 * nf];
+}
+
+// nbrU: the states read need the carry too (else only fn, for the register).
+__device__ __forceinline__ void carry_issue(const StageArgs& A, const FaceItem& it, const Nbr6 nb6, int e,
+                                            bool nbrU, CarryLoads& c) {
+  load_flux_rotated(A.Fcarry + ((size_t)it.nb * 6 + (it.f ^ 1)) * 4 * nf + it.a, it, c.fn);
+  if (!nbrU) return;
+  load_flux_rotated(A.Fcarry + ((size_t)e * 6 + it.f) * 4 * nf + it.a, it, c.fo);
+  const int da = it.d == 0 ? 1 : 0, db = it.d == 2 ? 1 : 2;  // tangential directions, t1 along da
+  const int t1 = it.a % n1, t2 = it.a / n1, ln = it.side ? 0 : N;  // ln: the neighbour's node along d
+  const double hw = half_winv(A.basis);
+  const int nla = nb6.pick(2 * da + (t1 == N ? 1 : 0)), nlb = nb6.pick(2 * db + (t2 == N ? 1 : 0));
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int dl = j ? db : da, tl = j ? t2 : t1, to = j ? t1 : t2;  // to: along the other tangential direction
+    const int sl = tl == N ? 1 : 0;
+    const int nl = j ? nlb : nla;
+    c.cl[j] = 0.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) c.fl[j][k] = 0.0;
+    if ((tl == 0 || tl == N) && nl >= 0) {
+      c.cl[j] = pick3(A.invJ, dl) * (sl ? hw : -hw);
+      // the node on the lateral face (normal dl): coordinates along d (ln) and
+      // the other tangential direction (to), the lower direction first
+      const int dother = j ? da : db;
+      const int al = it.d < dother ? ln + n1 * to : to + n1 * ln;
+      const int el = it.nb + nl - e;
+      load_flux_rotated(A.Fcarry + ((size_t)el * 6 + 2 * dl + (sl ^ 1)) * 4 * nf + al, it, c.fl[j]);
+    }
+  }
+}
+
+// Completes the neighbour's rotated state X at the face node (momentum and
+// energy), the directions in order.
+__device__ __forceinline__ void carry_neighbour(const StageArgs& A, const FaceItem& it, const CarryLoads& c,
+                                                double X[5]) {
+  const double hw = half_winv(A.basis);
+  const double cd = pick3(A.invJ, it.d) * (it.side ? -hw : hw);
+  const double c1 = it.d == 0 ? cd : c.cl[0], c2 = it.d == 0 ? c.cl[0] : (it.d == 1 ? cd : c.cl[1]);
+  const double c3 = it.d == 2 ? cd : c.cl[1];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const double f1 = it.d == 0 ? c.fo[k] : c.fl[0][k], f2 = it.d == 0 ? c.fl[0][k] : (it.d == 1 ? c.fo[k] : c.fl[1][k]);
+    const double f3 = it.d == 2 ? c.fo[k] : c.fl[1][k];
+    X[1 + k] = fma(A.Bcarry, fma(c3, f3, fma(c2, f2, c1 * f1)), X[1 + k]);
+  }
+}
+
+// S of an element's own node from the neighbours' fluxes in sFn (faces of
+// wmask, the walls, have none).
+__device__ __forceinline__ void carry_own(const double (*sFn)[4][nf], const double invJ[3], double hw, const int ijk[3],
+                                          int wmask, double S[4]) {
+#pragma unroll
+  for (int c = 0; c < 4; ++c) S[c] = 0.0;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const int id = ijk[d];
+    const int f = 2 * d + (id == N);
+    if ((id == 0 || id == N) && !((wmask >> f) & 1)) {
+      const int a = d == 0 ? ijk[1] + n1 * ijk[2] : (d == 1 ? ijk[0] + n1 * ijk[2] : ijk[0] + n1 * ijk[1]);
+      const double w = invJ[d] * (id == N ? hw : -hw);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) S[c] = fma(w, sFn[f][c][a], S[c]);
+    }
+  }
+}
+
+// Loads of one face item, issued together before any of them is used.  Two-
+// pass and Euler: both rotated states and (Navier-Stokes) the neighbour's
+// normal viscous flux.  DEFER: the neighbour's rotated state, and the carry;
+// the element's own state comes through LDS, completed (blended kernels read
+// complete states and load both).  At a wall (WALL variant, neighbour -1) fn
+// is the wall-model flux, read from the element's own slot of the wall face.
+template <bool NS, class R, bool WALL = false, bool DEFER = false, bool BOTH = true>
 struct FaceData {
   FaceItem it;
   double L[5], R_[5];
   R fn[4];
-  SplitLoads<SPLIT> sp;
+};
+template <bool NS, class R, bool WALL>
+struct FaceData<NS, R, WALL, true, false> {
+  FaceItem it;
+  double X[5];
+  CarryLoads c;
 };
 
-template <bool NS, class R, bool WALL = false, bool SPLIT = false>
-__device__ __forceinline__ void face_issue(const StageArgs& A, int e, FaceData<NS, R, WALL, SPLIT>& fd,
-                                           const Nbr6* nb6 = nullptr) {
+template <bool NS, class R, bool WALL, bool DEFER, bool BOTH>
+__device__ __forceinline__ void face_issue(const StageArgs& A, int e, FaceData<NS, R, WALL, DEFER, BOTH>& fd,
+                                           const Nbr6& nb6) {
   const FaceItem& it = fd.it;
-  if constexpr (SPLIT) {
-    split_issue(A, it, *nb6, e, fd.sp);
-  }
-  if (WALL && it.nb < 0) {
-    wall_face_loads(A.U, e, it, fd.L, fd.R_);
-    const R* Fn = reinterpret_cast<const R*>(A.Fvf) + ((size_t)e * 6 + it.f) * 4 * nf + it.a;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) fd.fn[c] = Fn[c * nf];
-    return;
-  }
-  face_loads(A.U, e, it, fd.L, fd.R_);
-  if (NS) {
-    const R* Fn = reinterpret_cast<const R*>(A.Fvf) + ((size_t)it.nb * 6 + (it.f ^ 1)) * 4 * nf + it.a;
-    if (SPLIT) {  // in the face frame (normal, t1, t2, energy), as the rest is formed
-      fd.fn[0] = Fn[it.d * nf];
-      fd.fn[1] = Fn[(it.k1 - 1) * nf];
-      fd.fn[2] = Fn[(it.k2 - 1) * nf];
-      fd.fn[3] = Fn[3 * nf];
-    } else {
+  if constexpr (DEFER && !BOTH) {
+    if (WALL && it.nb < 0) {
+      const double* Fw = A.Fvf_out + ((size_t)e * 6 + it.f) * 4 * nf + it.a;
+      load_flux_rotated(Fw, it, fd.c.fn);
+      return;
+    }
+    load_rotated(A.U + (size_t)it.nb * 5 * nn, it.nnb, it, fd.X);
+    if (A.Fcarry) carry_issue(A, it, nb6, e, A.carryU, fd.c);
+  } else {
+    if (WALL && it.nb < 0) {
+      wall_face_loads(A.U, e, it, fd.L, fd.R_);
+      const R* Fn = reinterpret_cast<const R*>(DEFER ? A.Fvf_out : A.Fvf) + ((size_t)e * 6 + it.f) * 4 * nf + it.a;
 #pragma unroll
       for (int c = 0; c < 4; ++c) fd.fn[c] = Fn[c * nf];
+      return;
+    }
+    face_loads(A.U, e, it, fd.L, fd.R_);
+    if (NS) {
+      const R* F = reinterpret_cast<const R*>(DEFER ? A.Fcarry : A.Fvf);
+      if (!DEFER || F) {
+        const R* Fn = F + ((size_t)it.nb * 6 + (it.f ^ 1)) * 4 * nf + it.a;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) fd.fn[c] = Fn[c * nf];
+      }
     }
   }
 }
@@ -1029,26 +1052,12 @@ __device__ __forceinline__ void store_q(const FaceItem& it, const R qs[4], R (*s
   sQ[it.f][3][it.a] = qs[3];
 }
 
-// Interface values of a face item into LDS: advective f*, and for
-// Navier-Stokes q* = (q- + q+)/2 and the neighbour's normal viscous flux.
-template <int VF, bool NS, class R, bool MX, bool WALL = false, bool SPLIT = false>
-__device__ __forceinline__ void face_item(const StageArgs& A, const FaceData<NS, R, WALL, SPLIT>& fd, const Ref& ref,
-                                          R (*sF)[5][nf], R (*sQ)[4][nf], R (*sFn)[4][nf]) {
-  const FaceItem& it = fd.it;
-  const State64 sL = state64<0>(fd.L, A.gamma - 1.0), sR = state64<0>(fd.R_, A.gamma - 1.0);
-  if (NS) {
-    R fn[4] = {fd.fn[0], fd.fn[1], fd.fn[2], fd.fn[3]};
-    if constexpr (SPLIT) {
-      static_assert(sizeof(R) == 8, "split BR1: FP64");
-      __builtin_amdgcn_sched_barrier(0);
-      split_rest(A, it, it.side ? sL : sR, it.side ? sR : sL, fd.sp, fn);
-      __builtin_amdgcn_sched_barrier(0);
-      store_q(it, fn, sFn);  // from the face frame
-    } else {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) sFn[it.f][c][it.a] = fn[c];
-    }
-  }
+// Interface values of a face item into LDS from its minus and plus states:
+// advective f*, and for Navier-Stokes q* = (q- + q+)/2.
+template <int VF, bool NS, class R, bool MX>
+__device__ __forceinline__ void face_item(const StageArgs& A, const FaceItem& it, const double L[5],
+                                          const double Rt[5], const Ref& ref, R (*sF)[5][nf], R (*sQ)[4][nf]) {
+  const State64 sL = state64<0>(L, A.gamma - 1.0), sR = state64<0>(Rt, A.gamma - 1.0);
   const Jumps<R> J = jumps<R, MX>(sL, sR, A.gamma, ref, A.sf);
   R g[5];
   riemann_rot<VF, R>(A.sf, to_rot<R, MX>(sL, ref), to_rot<R, MX>(sR, ref), J, (R)A.gamma, g);
@@ -1181,120 +1190,11 @@ __device__ __forceinline__ void node_viscous_flux(const StageArgs& A, int e, con
 
 __device__ __forceinline__ int axis_stride(int j) { return j == 0 ? 1 : (j == 1 ? n1 : nf); }
 
-// Padded node layout of the split lifting's LDS copy of (u, v, w, theta): one
-// double after every x-row, so that the lines read across a wavefront (x-lines
+// Padded node layout of LDS arrays read by lines: one entry after every x-row, so that the lines read across a wavefront (x-lines
 // of different rows, y-lines of different planes) fall on different LDS banks.
-constexpr int SQP = nn + nn / n1;  // doubles per variable
+constexpr int SQP = nn + nn / n1;  // entries per variable
 __device__ __forceinline__ constexpr int pstride(int j) { return j == 0 ? 1 : (j == 1 ? n1 + 1 : n1 * (n1 + 1)); }
 __device__ __forceinline__ int padded(int m) { return m + m / n1; }  // node m = i0 + n1 i1 + nf i2
-
-// The four lifted variables of node t into the padded layout (P: primitives).
-__device__ __forceinline__ void store_own_q(double* sq, int t, const double P[7]) {
-  const int m = padded(t);
-  sq[m] = P[1];
-  sq[SQP + m] = P[2];
-  sq[2 * SQP + m] = P[3];
-  sq[3 * SQP + m] = P[6];
-}
-
-// Split BR1: the own part of the normal viscous flux at every face node of
-// the element (into Fout, laid out as StageArgs.Fvf), from sq = (u, v, w,
-// theta) at its nodes (LDS, padded layout), by lines rather than one face
-// node at a time:
-//   pass 1: each normal line (3 nf of them) gives the derivatives of
-//     (u, v, w, theta) along it at both end nodes, and each line of a face
-//     plane along one of the plane's axes j (6 faces x 2 axes x n1 lines)
-//     those of u_d and of u_j (d: the face normal; one task per variable, so
-//     that the tasks' work is about even and the code is the same for both)
-//     at its nodes, into the LDS scratch sW (48 nf doubles);
-//   pass 2: each face node forms its flux from these and its velocity.
-// Each line's values are read from LDS once; the differentiation matrix comes
-// with uniform loads from the constant address space.  The interface values
-// are the node's own half, q / 2.  The caller synchronises the workgroup
-// before (sq written, sW free); the function synchronises between the passes.
-using cdouble_ptr = const double __attribute__((address_space(4)))*;
-template <int TPE>
-__device__ __forceinline__ void own_part_by_lines(const StageArgs& A, int e, int t, const double* sq, double* sW,
-                                                  double* Fout) {
-  const cdouble_ptr cb = (cdouble_ptr)(uintptr_t)A.basis;
-  const cdouble_ptr Dw = cb + BL.Dw();
-  const double h0 = -0.5 * cb[BL.winv()], hN = 0.5 * cb[BL.winv() + N];  // own-half weights at the ends
-  double* sGn = sW;            // [3 d][2 side][4 v][nf]
-  double* sT = sW + 24 * nf;   // [6 f][2 jj][2 c][nf]
-  constexpr int NTASK = 3 * nf + 24 * n1;
-  for (int task = t; task < NTASK; task += TPE) {
-    if (task < 3 * nf) {  // normal line
-      const int d = task / nf, a = task - d * nf;
-      const int ja = d == 0 ? 1 : 0, jb = d == 2 ? 1 : 2;
-      const int sd = pstride(d);
-      const int base = (a % n1) * pstride(ja) + (a / n1) * pstride(jb);
-      double g0[4] = {0, 0, 0, 0}, gN[4] = {0, 0, 0, 0};
-#pragma unroll
-      for (int l = 0; l < n1; ++l) {
-        const double c0 = Dw[l], cN = Dw[N * n1 + l];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const double q = sq[v * SQP + base + l * sd];
-          g0[v] = fma(c0, q, g0[v]);
-          gN[v] = fma(cN, q, gN[v]);
-        }
-      }
-      const double J = A.invJ[0] * (d == 0) + A.invJ[1] * (d == 1) + A.invJ[2] * (d == 2);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        g0[v] = J * fma(h0, sq[v * SQP + base], g0[v]);
-        gN[v] = J * fma(hN, sq[v * SQP + base + N * sd], gN[v]);
-        sGn[((2 * d) * 4 + v) * nf + a] = g0[v];
-        sGn[((2 * d + 1) * 4 + v) * nf + a] = gN[v];
-      }
-    } else {  // one variable (u_d or u_j) along a line of a face plane
-      const int u = task - 3 * nf;
-      const int c = u / (12 * n1), w = u - c * 12 * n1;  // c: the variable; the code does not branch on it
-      const int f = w / (2 * n1), r = w - f * 2 * n1, jj = r / n1, pos = r - jj * n1;
-      const int d = f >> 1, id = (f & 1) ? N : 0;
-      const int ja = d == 0 ? 1 : 0, jb = d == 2 ? 1 : 2;
-      const int j = jj ? jb : ja, o = jj ? ja : jb;
-      const int sj = pstride(j);
-      const double* src = sq + (c ? j : d) * SQP + id * pstride(d) + pos * pstride(o);
-      double q[n1];
-#pragma unroll
-      for (int l = 0; l < n1; ++l) q[l] = src[l * sj];
-      const double J = A.invJ[0] * (j == 0) + A.invJ[1] * (j == 1) + A.invJ[2] * (j == 2);
-      double* out = sT + ((f * 2 + jj) * 2 + c) * nf;
-#pragma unroll
-      for (int i = 0; i < n1; ++i) {
-        double tv = 0;
-#pragma unroll
-        for (int l = 0; l < n1; ++l) tv = fma(Dw[i * n1 + l], q[l], tv);
-        if (i == 0) tv = fma(h0, q[0], tv);
-        if (i == N) tv = fma(hN, q[N], tv);
-        out[jj ? pos + n1 * i : i + n1 * pos] = J * tv;
-      }
-    }
-  }
-  __syncthreads();
-  const double mu = A.mu, kap = A.kappa;
-  for (int q = t; q < 6 * nf; q += TPE) {
-    const int f = q / nf, a = q - f * nf, d = f >> 1;
-    const int ja = d == 0 ? 1 : 0, jb = d == 2 ? 1 : 2;
-    const int n = (f & 1 ? N : 0) * pstride(d) + (a % n1) * pstride(ja) + (a / n1) * pstride(jb);
-    const double* gn = sGn + f * 4 * nf + a;  // f = 2 d + side
-    const double dn_ud = gn[d * nf], dn_ua = gn[ja * nf], dn_ub = gn[jb * nf], dn_th = gn[3 * nf];
-    const double* tt = sT + f * 4 * nf + a;
-    const double da_ud = tt[0], da_ua = tt[nf], db_ud = tt[2 * nf], db_ub = tt[3 * nf];
-    const double dv = (2.0 / 3.0) * mu * (dn_ud + da_ua + db_ub);
-    const double Fd = mu * (dn_ud + dn_ud) - dv;
-    const double Fa = mu * (dn_ua + da_ud);
-    const double Fb = mu * (dn_ub + db_ud);
-    const double FE = sq[d * SQP + n] * Fd + sq[ja * SQP + n] * Fa + sq[jb * SQP + n] * Fb + kap * dn_th;
-    double* o = Fout + ((size_t)e * 6 + f) * 4 * nf + a;
-    // streaming stores: read once, by the neighbours' next stage kernel
-    __builtin_nontemporal_store(Fd, &o[d * nf]);
-    __builtin_nontemporal_store(Fa, &o[ja * nf]);
-    __builtin_nontemporal_store(Fb, &o[jb * nf]);
-    __builtin_nontemporal_store(FE, &o[3 * nf]);
-  }
-}
 
 // Line pass of the viscous divergence: sV[4 d + c][padded node] (component c
 // of the viscous flux in direction d) becomes sum_l Dw_il sV_l along the lines
@@ -1336,50 +1236,33 @@ __device__ __forceinline__ void divergence_lines(const StageArgs& A, R (*sV)[SQP
   }
 }
 
-// Split BR1 lifting: the own part of the normal viscous flux at every face
-// node of the element (into StageArgs.Fvf), from the element's own nodes
-// only; one element per workgroup.  The stage kernel's epilogue does the same
-// for its output state.
-__global__ __launch_bounds__(PS::NTB) void k_lift_split(StageArgs A) {
-  static_assert(PS::EPB == 1 && PS::TPE == PS::NTB, "one element per workgroup");
-  __shared__ double sW[4 * SQP + 48 * nf];
-  const int e = element_of_block(blockIdx.x, A.chunk);
-  if (e >= A.nelem) return;  // uniform over the workgroup
-  const int t = threadIdx.x;
-  if (t < nn) {
-    const double* Ue = A.U + (size_t)e * 5 * nn;
-    double u[5], P[7];
-#pragma unroll
-    for (int v = 0; v < 5; ++v) u[v] = Ue[v * nn + t];
-    primitives<VF_PI, double, false>(u, A.gamma - 1.0, Ref{0.0, 0.0, 0.0}, P);
-    store_own_q(sW, t, P);
-  }
-  __syncthreads();
-  own_part_by_lines<PS::TPE>(A, e, t, sW, sW + 4 * SQP, A.Fvf);
-}
-
 // With BLEND (FP64) only the advective operator is blended: the viscous terms
-// enter unweighted, and MODE_DIFF leaves them out.  SPLIT: the split BR1
-// variant (StageArgs.split; FP64 Navier-Stokes without the eddy viscosity,
-// walls or blending).
-template <int VF, int EQ, bool BLEND, class R, bool WALL = false, bool SPLIT = false>
+// enter unweighted, and MODE_DIFF leaves them out.  DEFER: the deferred
+// viscous exchange (FP64 Navier-Stokes); blended kernels read complete states
+// and carry the register only.
+template <int VF, int EQ, bool BLEND, class R, bool WALL = false, bool DEFER = false>
 __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
   constexpr bool NS = (EQ >= 1);
   constexpr bool LES = (EQ == 2);
   constexpr bool MX = sizeof(R) == 4;
+  // the element's own face state comes through LDS (completed by the carry)
+  constexpr bool OWN_LDS = DEFER && !BLEND;
   constexpr bool ROT = !MX && !BLEND;  // partner order of the volume loop
   constexpr bool LINES = N >= 5 && N % 2 == 1;  // viscous divergence by lines
   constexpr int SVP = LINES ? SQP : nnp;        // its LDS row
   static_assert(!(BLEND && MX), "the blended operator is FP64 only");
-  static_assert(!WALL || (NS && !MX), "walls: FP64 Navier-Stokes");
+  static_assert(!WALL || (NS && !MX && DEFER), "walls: FP64 Navier-Stokes");
+  static_assert(!DEFER || (NS && !MX), "deferred viscous exchange: FP64 Navier-Stokes");
   // LDS pool: primitives sP[7][nnp], face fluxes sF[6][5][nf], and for
   // Navier-Stokes the interface values sQ[6][4][nf] and the neighbours' normal
   // viscous fluxes sFn[6][4][nf].  The twelve viscous-flux components of all
   // nodes are later exchanged through sV[12][SVP], which overlays sP, sF and sQ
-  // (all consumed by then) but not sFn.
+  // (all consumed by then) but not sFn.  With OWN_LDS the element's completed
+  // conservative state sU[5][nn] passes through the space of sF and sQ.
   constexpr int oF = 7 * nnp, oQ = oF + 30 * nf, oFn = std::max(oQ + 24 * nf, 12 * SVP);
   constexpr int POOL = NS ? oFn + 24 * nf : oQ;
   static_assert(!NS || 12 * SVP <= oFn, "viscous exchange must not overlay sFn");
+  static_assert(!OWN_LDS || 5 * nn <= 54 * nf, "sU in the space of sF and sQ");
   constexpr int EPB = PS::EPB, TPE = PS::TPE, FI = PS::FI;
   __shared__ R sPoolAll[EPB][POOL];
   __shared__ R sB[NB_STAGE];
@@ -1402,8 +1285,7 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
   // node state and the basis.
   static_assert(EPB == 1, "one element per workgroup: its neighbours are uniform");
   const Nbr6 nb6 = uniform_nbr6(A.nbr, e);
-  static_assert(!SPLIT || (EQ == 1 && !BLEND && !WALL && !MX), "split BR1: FP64 Navier-Stokes on the box");
-  FaceData<NS, R, WALL, SPLIT> fd[FI];
+  FaceData<NS, R, WALL, DEFER, !OWN_LDS> fd[FI];
 #pragma unroll
   for (int k = 0; k < FI; ++k)
     if (t + k * TPE < 6 * nf) fd[k].it = face_item_geometry(nb6, t + k * TPE);
@@ -1427,7 +1309,7 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
   // Round trip 2: the face states (needs the neighbour indices).
 #pragma unroll
   for (int k = 0; k < FI; ++k)
-    if (t + k * TPE < 6 * nf) face_issue<NS, R, WALL, SPLIT>(A, e, fd[k], &nb6);
+    if (t + k * TPE < 6 * nf) face_issue<NS, R, WALL, DEFER, !OWN_LDS>(A, e, fd[k], nb6);
   if (tid < NB_STAGE) {
     sB[tid] = (R)bval;
     if (BLEND) sB64[tid] = bval;
@@ -1442,17 +1324,81 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
   R me[7];
   int ijk[3] = {0, 0, 0};
   if (t < nn) {
-    primitives<VF, R, MX>(u, gm1, ref, me);
-#pragma unroll
-    for (int k = 0; k < 7; ++k)
-      if (k < 6 || NS) sP[k][t] = me[k];
     ijk[0] = t % n1;
     ijk[1] = (t / n1) % n1;
     ijk[2] = t / nf;
   }
+  const double hw = DEFER ? half_winv(A.basis) : 0.0;
+  if constexpr (OWN_LDS) {
+    if (A.Fcarry) {  // uniform: the neighbours' fluxes of the stage before
 #pragma unroll
-  for (int k = 0; k < FI; ++k)
-    if (t + k * TPE < 6 * nf) face_item<VF, NS, R, MX, WALL, SPLIT>(A, fd[k], ref, sF, sQ, sFn);
+      for (int k = 0; k < FI; ++k)
+        if (t + k * TPE < 6 * nf && !(WALL && fd[k].it.nb < 0)) store_q(fd[k].it, fd[k].c.fn, sFn);
+      __syncthreads();
+      if (A.carryU && t < nn) {
+        double S[4];
+        carry_own(sFn, A.invJ, hw, ijk, wmask, S);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) u[1 + c] = fma(A.Bcarry, S[c], u[1 + c]);
+      }
+    }
+    if (t < nn) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) sPool[oF + v * nn + t] = u[v];
+    }
+  }
+  if (t < nn) {
+    if (DEFER && A.Yout) {  // the complete stage state, recorded for the reverse mode
+#pragma unroll
+      for (int v = 0; v < 5; ++v)
+        __builtin_nontemporal_store(u[v], &A.Yout[(size_t)e * 5 * nn + t + v * nn]);
+    }
+    primitives<VF, R, MX>(u, gm1, ref, me);
+#pragma unroll
+    for (int k = 0; k < 7; ++k)
+      if (k < 6 || NS) sP[k][t] = me[k];
+  }
+  if constexpr (OWN_LDS) {
+    double own[FI][5];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < FI; ++k)
+      if (t + k * TPE < 6 * nf) load_rotated(sPool + oF, fd[k].it.nown, fd[k].it, own[k]);
+    __syncthreads();  // sU read: sF and sQ may be written
+#pragma unroll
+    for (int k = 0; k < FI; ++k)
+      if (t + k * TPE < 6 * nf) {
+        const FaceItem& it = fd[k].it;
+        const bool wall = WALL && it.nb < 0;  // the other side is the own state's mirror image
+        double X[5], L[5], Rt[5];
+        if (wall) {
+#pragma unroll
+          for (int v = 0; v < 5; ++v) X[v] = v == 1 ? -own[k][v] : own[k][v];
+          store_q(it, fd[k].c.fn, sFn);  // the wall model's flux
+        } else {
+#pragma unroll
+          for (int v = 0; v < 5; ++v) X[v] = fd[k].X[v];
+          if (A.carryU) carry_neighbour(A, it, fd[k].c, X);
+        }
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+          L[v] = it.side ? own[k][v] : X[v];
+          Rt[v] = it.side ? X[v] : own[k][v];
+        }
+        face_item<VF, NS, R, MX>(A, it, L, Rt, ref, sF, sQ);
+      }
+  } else {
+#pragma unroll
+    for (int k = 0; k < FI; ++k)
+      if (t + k * TPE < 6 * nf) {
+        const FaceItem& it = fd[k].it;
+        if (NS && (!DEFER || A.Fcarry || (WALL && it.nb < 0))) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) sFn[it.f][c][it.a] = fd[k].fn[c];
+        }
+        face_item<VF, NS, R, MX>(A, it, fd[k].L, fd[k].R_, ref, sF, sQ);
+      }
+  }
   __syncthreads();
 
   R acc[5] = {0, 0, 0, 0, 0};
@@ -1642,15 +1588,28 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
           }
         }
         const int a = d == 0 ? ijk[1] + n1 * ijk[2] : (d == 1 ? ijk[0] + n1 * ijk[2] : ijk[0] + n1 * ijk[1]);
-        if (id == 0 || id == N) {  // F*v = mean with the neighbour's normal viscous flux (sFn)
+        if (id == 0 || id == N) {
           const int f = 2 * d + (id == N);
-          const bool wf = WALL && ((wmask >> f) & 1);  // wall: sFn is F*v itself
-          const R w = (wf ? (R)1 : h2) * (id == N ? swinv[N] : -swinv[0]);
-          const R o = wf ? (R)0 : (R)1;
-          s0 = fmaR(w, fmaR(o, Fv[d][0], sFn[f][0][a]), s0);
-          s1 = fmaR(w, fmaR(o, Fv[d][1], sFn[f][1][a]), s1);
-          s2 = fmaR(w, fmaR(o, Fv[d][2], sFn[f][2][a]), s2);
-          s3 = fmaR(w, fmaR(o, Fv[d][3], sFn[f][3][a]), s3);
+          const R w = h2 * (id == N ? swinv[N] : -swinv[0]);
+          if (!DEFER) {  // F*v = mean with the neighbour's normal viscous flux (sFn)
+            s0 = fmaR(w, Fv[d][0] + sFn[f][0][a], s0);
+            s1 = fmaR(w, Fv[d][1] + sFn[f][1][a], s1);
+            s2 = fmaR(w, Fv[d][2] + sFn[f][2][a], s2);
+            s3 = fmaR(w, Fv[d][3] + sFn[f][3][a], s3);
+          } else if (WALL && ((wmask >> f) & 1)) {  // sFn is F*v itself
+            s0 = fmaR((R)2 * w, sFn[f][0][a], s0);
+            s1 = fmaR((R)2 * w, sFn[f][1][a], s1);
+            s2 = fmaR((R)2 * w, sFn[f][2][a], s2);
+            s3 = fmaR((R)2 * w, sFn[f][3][a], s3);
+          } else {  // the own half; the neighbour's follows with the carry
+            R* Fo = reinterpret_cast<R*>(A.Fvf_out) + ((size_t)e * 6 + f) * 4 * nf + a;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) __builtin_nontemporal_store(Fv[d][c], &Fo[c * nf]);
+            s0 = fmaR(w, Fv[d][0], s0);
+            s1 = fmaR(w, Fv[d][1], s1);
+            s2 = fmaR(w, Fv[d][2], s2);
+            s3 = fmaR(w, Fv[d][3], s3);
+          }
         }
         acc[1] = fmaR(invJ[d], s0, acc[1]);
         acc[2] = fmaR(invJ[d], s1, acc[2]);
@@ -1666,6 +1625,12 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
     for (int v = 0; v < 5; ++v) ut[v] = (double)acc[v];
     if (MX) ut[4] += ref.h * ut[0];  // undo the energy-flux shift h0 * (mass flux)
     const size_t o = (size_t)e * 5 * nn + t;
+    if (DEFER && A.Fcarry && A.mode == MODE_RK && A.A != 0.0) {  // the register's carry
+      double S[4];
+      carry_own(reinterpret_cast<const double (*)[4][nf]>(sPool + oFn), A.invJ, hw, ijk, wmask, S);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) gprev[1 + c] += S[c];
+    }
     if (A.mode != MODE_RK) {  // MODE_UT, MODE_DIFF
 #pragma unroll
       for (int v = 0; v < 5; ++v) A.Ut[o + v * nn] = ut[v];
@@ -1680,24 +1645,6 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
         u[v] = u[v] + A.Bdt * gv;  // the stage output, kept for the indicator below
         __builtin_nontemporal_store(u[v], &A.Uout[o + v * nn]);
       }
-    }
-  }
-  // Split BR1, Runge-Kutta stage: the own part of the normal viscous flux of
-  // the stage output at the element's face nodes, for the next stage (what
-  // k_lift_split computes, here from the values just written and still in
-  // registers).
-  if constexpr (SPLIT) {
-    if (A.Fvf_next && A.mode == MODE_RK) {  // uniform over the workgroup
-      static_assert(4 * SQP + 48 * nf <= POOL, "lifted variables and line sums in the LDS pool");
-      double* sq = reinterpret_cast<double*>(sPool);
-      __syncthreads();  // the pool's last readers (the viscous pass) are done
-      if (t < nn) {
-        double P[7];
-        primitives<VF_PI, double, false>(u, gm1, Ref{0.0, 0.0, 0.0}, P);
-        store_own_q(sq, t, P);
-      }
-      __syncthreads();
-      own_part_by_lines<TPE>(A, e, t, sq, sq + 4 * SQP, A.Fvf_next);
     }
   }
   // Euler only: measured on the blended Navier-Stokes stage (N = 4, its
@@ -1848,7 +1795,7 @@ __device__ __forceinline__ void lift_face_node(const StageArgs& A, int e, const 
 // Register budget of the lifting kernel: 8 waves per SIMD (64 VGPRs) with one
 // face item per thread, else 4; the line sums with run-time strides are only
 // partly unrolled so that the partner loads in flight fit in it.
-template <class R, bool LES, bool WALL = false>
+template <class R, bool LES>
 __global__ __launch_bounds__(PL::NTB, PL::FI == 1 && N >= 2 ? 8 : 4) void k_lift(StageArgs A) {
   constexpr bool MX = sizeof(R) == 4;
   constexpr int EPB = PL::EPB, TPE = PL::TPE, FI = PL::FI;
@@ -1886,7 +1833,7 @@ __global__ __launch_bounds__(PL::NTB, PL::FI == 1 && N >= 2 ? 8 : 4) void k_lift
   double FL[FI][5], FR[FI][5];
 #pragma unroll
   for (int k = 0; k < FI; ++k)
-    if (t + k * TPE < 6 * nf) face_loads_w<WALL>(A.U, e, its[k], FL[k], FR[k]);
+    if (t + k * TPE < 6 * nf) face_loads(A.U, e, its[k], FL[k], FR[k]);
   if (tid < NB_STAGE) sB[tid] = (R)bval;
   const R invJ[3] = {(R)A.invJ[0], (R)A.invJ[1], (R)A.invJ[2]};
   if (t < nn) {
@@ -1904,11 +1851,31 @@ __global__ __launch_bounds__(PL::NTB, PL::FI == 1 && N >= 2 ? 8 : 4) void k_lift
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < FI; ++k)
-    if (t + k * TPE < 6 * nf && !(WALL && its[k].nb < 0)) lift_face_node<R, LES>(A, e, its[k], sq, sQ, sB, invJ);
+    if (t + k * TPE < 6 * nf) lift_face_node<R, LES>(A, e, its[k], sq, sQ, sB, invJ);
+}
+
+// Carry S of one node of element e, straight from global memory (see CarryLoads).
+__device__ __forceinline__ void carry_node(const StageArgs& A, int e, int n, double S[4]) {
+  const int ijk[3] = {n % n1, (n / n1) % n1, n / nf};
+  const double hw = half_winv(A.basis);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) S[c] = 0.0;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const int id = ijk[d];
+    if (id != 0 && id != N) continue;
+    const int f = 2 * d + (id == N), nb = A.nbr[6 * e + f];
+    if (nb < 0) continue;
+    const int a = d == 0 ? ijk[1] + n1 * ijk[2] : (d == 1 ? ijk[0] + n1 * ijk[2] : ijk[0] + n1 * ijk[1]);
+    const double* F = A.Fcarry + ((size_t)nb * 6 + (f ^ 1)) * 4 * nf + a;
+    const double w = A.invJ[d] * (id == N ? hw : -hw);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) S[c] = fma(w, F[c * nf], S[c]);
+  }
 }
 
 // Wall-model flux at every wall face node (FP64): thread -> (side p, element
-// of the wall plane, face node a); the flux goes into Fvf[e][f][c][a] of the
+// of the wall plane, face node a); the flux goes into Fvf_out[e][f][c][a] of the
 // wall face f = 2 wall_dir + p, in the global components (x, y, z momentum,
 // energy), read by the stage kernel of the same element.
 __global__ __launch_bounds__(256) void k_wall_flux(StageArgs A) {
@@ -1929,9 +1896,15 @@ __global__ __launch_bounds__(256) void k_wall_flux(StageArgs A) {
   const int f = 2 * wd + p;
   const FaceItem it = face_item_geometry(A.nbr, e, f * nf + a);
   const double* Ue = A.U + (size_t)e * 5 * nn;
-  double g[4];
-  wall_model_flux(A, Ue[it.nown], Ue[it.nnb], Ue[it.k1 * nn + it.nnb], Ue[it.k2 * nn + it.nnb], p ? -1.0 : 1.0, g);
-  double* out = A.Fvf + ((size_t)e * 6 + f) * 4 * nf + a;
+  double g[4], m1 = Ue[it.k1 * nn + it.nnb], m2 = Ue[it.k2 * nn + it.nnb];
+  if (A.carryU) {  // complete the exchange node's momenta (density has no carry)
+    double S[4];
+    carry_node(A, e, it.nnb, S);
+    m1 = fma(A.Bcarry, pick3(S, it.k1 - 1), m1);
+    m2 = fma(A.Bcarry, pick3(S, it.k2 - 1), m2);
+  }
+  wall_model_flux(A, Ue[it.nown], Ue[it.nnb], m1, m2, p ? -1.0 : 1.0, g);
+  double* out = A.Fvf_out + ((size_t)e * 6 + f) * 4 * nf + a;
   out[it.d * nf] = g[0];
   out[(it.k1 - 1) * nf] = g[1];
   out[(it.k2 - 1) * nf] = g[2];
@@ -3190,13 +3163,92 @@ __global__ void k_axpby(double* y, double a, const double* x, double b, size_t n
 }
 
 // ---------------------------------------------------------------------------
+// Completion of a state with the carry (deferred viscous exchange).
+// ---------------------------------------------------------------------------
+// The neighbours' fluxes of all faces of element e into sFn; returns the wall
+// faces (bit f), which have none.
+__device__ __forceinline__ int load_carry(const StageArgs& A, int e, int t, double (*sFn)[4][nf]) {
+  const Nbr6 nb6 = uniform_nbr6(A.nbr, e);
+  int wmask = 0;
+#pragma unroll
+  for (int f = 0; f < 6; ++f) wmask |= nb6.n[f] < 0 ? 1 << f : 0;
+  for (int q = t; q < 6 * nf; q += NT) {
+    const int f = q / nf, a = q - f * nf, nb = nb6.pick(f);
+    if (nb < 0) continue;
+    const double* F = A.Fcarry + ((size_t)nb * 6 + (f ^ 1)) * 4 * nf + a;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) sFn[f][c][a] = F[c * nf];
+  }
+  return wmask;
+}
+
+// u += B S at the element's node; stores momentum and energy of the boundary
+// nodes to out (in place), or the whole state (copy).
+__device__ __forceinline__ void complete_node(const StageArgs& A, const double (*sFn)[4][nf], int wmask,
+                                              const int ijk[3], double u[5], double* out, bool copy) {
+  const bool boundary = ijk[0] == 0 || ijk[0] == N || ijk[1] == 0 || ijk[1] == N || ijk[2] == 0 || ijk[2] == N;
+  if (boundary) {
+    double S[4];
+    carry_own(sFn, A.invJ, half_winv(A.basis), ijk, wmask, S);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) u[1 + c] = fma(A.Bcarry, S[c], u[1 + c]);
+  }
+  if (copy) {
+#pragma unroll
+    for (int v = 0; v < 5; ++v) out[v * nn] = u[v];
+  } else if (boundary) {
+#pragma unroll
+    for (int v = 1; v < 5; ++v) out[v * nn] = u[v];
+  }
+}
+
+// X = U + B S (S: the carry of the stage that wrote U), with X = U or another
+// array, and with A.G its register G += S.  Bound by HBM: in place it reads and
+// writes the momentum and energy rows and reads the neighbours' fluxes, 64 +
+// 192/(N+1) B per node; with the copy of a state that ends in the other buffer
+// 80 + 192/(N+1) B.
+__global__ __launch_bounds__(NT) void k_complete(StageArgs A, double* X) {
+  __shared__ double sFn[6][4][nf];
+  const int e = element_of_block(blockIdx.x, A.chunk);
+  if (e >= A.nelem) return;
+  const int t = threadIdx.x;
+  const bool copy = X != A.U;
+  const size_t o = (size_t)e * 5 * nn + t;
+  double u[5];
+  int ijk[3] = {0, 0, 0};
+  if (t < nn) {
+#pragma unroll
+    for (int v = 0; v < 5; ++v)
+      if (v > 0 || copy) u[v] = A.U[o + v * nn];
+    ijk[0] = t % n1;
+    ijk[1] = (t / n1) % n1;
+    ijk[2] = t / nf;
+  }
+  const int wmask = load_carry(A, e, t, sFn);
+  __syncthreads();
+  if (t >= nn) return;
+  complete_node(A, sFn, wmask, ijk, u, X + o, copy);
+  if (A.G) {
+    double S[4];
+    carry_own(sFn, A.invJ, half_winv(A.basis), ijk, wmask, S);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) A.G[o + (1 + c) * nn] += S[c];
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Modal indicator -> clipped blending coefficient a1 per element (FP64).
 // q = rho p; qhat = (Vinv x Vinv x Vinv) q on orthonormal Legendre modes;
 // E_N = energy of modes with max index N over all; E_{N-1} likewise over the
 // modes up to N-1; E = max (or E_N only); a0 = 1/(1 + exp(-s/T (E - T)));
 // a1 = min(a0, a_max), 0 below a_min.
 // ---------------------------------------------------------------------------
+// FIX (blended Navier-Stokes): first completes the state in place with the
+// carry of the stage before (40 B + 192/(N+1) B read and 32 B written per node
+// instead of a completion pass and an indicator pass).
+template <bool FIX>
 __global__ __launch_bounds__(NT) void k_alpha1(StageArgs A) {
+  __shared__ double sFn[FIX ? 6 : 1][4][nf];
   __shared__ double sV[nf];
   __shared__ double sq[nn];
   __shared__ double st[nn];
@@ -3208,15 +3260,20 @@ __global__ __launch_bounds__(NT) void k_alpha1(StageArgs A) {
   const double* Ue = A.U + (size_t)e * 5 * nn;
   int ijk[3] = {0, 0, 0};
   double qt = 0.0;
+  double u[5];
   if (t < nn) {
-    double u[5];
 #pragma unroll
     for (int v = 0; v < 5; ++v) u[v] = Ue[v * nn + t];
-    qt = indicator_q(u, A.gamma - 1.0);
     ijk[0] = t % n1;
     ijk[1] = (t / n1) % n1;
     ijk[2] = t / nf;
   }
+  if (FIX) {
+    const int wmask = load_carry(A, e, t, sFn);
+    __syncthreads();
+    if (t < nn) complete_node(A, sFn, wmask, ijk, u, const_cast<double*>(Ue) + t, false);
+  }
+  if (t < nn) qt = indicator_q(u, A.gamma - 1.0);
   const double a1 = element_alpha1(A, sV, sq, st, sred, t, ijk, qt);
   if (t == 0) const_cast<double*>(A.alpha1)[e] = a1;
 }
@@ -3531,10 +3588,72 @@ __device__ __forceinline__ CFaceItem curved_face_item(const StageArgs& A, int e,
   return cface(A.conn, A.nbr, e, q);
 }
 
+// The neighbour projected its viscous flux on its own face metric: along the
+// own +xi that is -s_own s_nb times its value.
+__device__ __forceinline__ double flux_sign(const CFaceItem& it) {
+  return ((it.side != 0) == ((it.fb & 1) != 0)) ? -1.0 : 1.0;
+}
+
+// Carry of the deferred viscous exchange on curved elements, times J: sFn holds
+// the neighbours' projected fluxes along the own +xi.
+__device__ __forceinline__ void carry_own_curved(const double (*sFn)[4][nf], double winv, const int ijk[3],
+                                                 double S[4]) {
+#pragma unroll
+  for (int c = 0; c < 4; ++c) S[c] = 0.0;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const int id = ijk[d];
+    if (id != 0 && id != N) continue;
+    const int f = 2 * d + (id == N);
+    const int a = d == 0 ? ijk[1] + n1 * ijk[2] : (d == 1 ? ijk[0] + n1 * ijk[2] : ijk[0] + n1 * ijk[1]);
+    const double w = id == N ? 0.5 * winv : -0.5 * winv;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) S[c] = fma(w, sFn[f][c][a], S[c]);
+  }
+}
+
+// k_complete on curved elements (any connectivity), in place or as a copy.
+__global__ __launch_bounds__(NT) void k_complete_curved(StageArgs A, double* X) {
+  __shared__ double sFn[6][4][nf];
+  const int e = element_of_block(blockIdx.x, A.chunk);
+  if (e >= A.nelem) return;
+  const int t = threadIdx.x;
+  const bool copy = X != A.U;
+  const size_t o = (size_t)e * 5 * nn + t;
+  double u[5], iJ = 0.0;
+  if (t < nn) {
+#pragma unroll
+    for (int v = 0; v < 5; ++v)
+      if (v > 0 || copy) u[v] = A.U[o + v * nn];
+    iJ = A.M[((size_t)e * MS + 9) * nn + t];
+  }
+  for (int q = t; q < 6 * nf; q += NT) {
+    const CFaceItem it = cface(A.conn, A.nbr, e, q);
+    const double* F = A.Fcarry + ((size_t)it.nb * 6 + it.fb) * 4 * nf + it.ab;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) sFn[it.f][c][it.a] = flux_sign(it) * F[c * nf];
+  }
+  __syncthreads();
+  if (t >= nn) return;
+  const int ijk[3] = {t % n1, (t / n1) % n1, t / nf};
+  const bool boundary = ijk[0] == 0 || ijk[0] == N || ijk[1] == 0 || ijk[1] == N || ijk[2] == 0 || ijk[2] == N;
+  if (!boundary && !copy) return;
+  double S[4];
+  carry_own_curved(sFn, 2.0 * half_winv(A.basis), ijk, S);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    u[1 + c] = fma(A.Bcarry, iJ * S[c], u[1 + c]);
+    X[o + (1 + c) * nn] = u[1 + c];
+    if (A.G && boundary) A.G[o + (1 + c) * nn] = fma(iJ, S[c], A.G[o + (1 + c) * nn]);
+  }
+  if (copy) X[o] = u[0];
+}
+
 // Loads of a curved face item: both conservative states in Cartesian
 // components (L the minus, R the plus side), the metric row of each side's
 // face direction at its node, signed by its face side (s Ja, s = +1 on +
-// faces), and (Navier-Stokes) the neighbour's projected viscous flux.
+// faces), and (Navier-Stokes, with a carry) the
+// neighbour's projected viscous flux of the stage before.
 struct CurvedFace {
   CFaceItem it;
   double L[5], R[5], jm[3], jp[3], fn[4];
@@ -3557,8 +3676,8 @@ __device__ __forceinline__ void curved_face_issue(const StageArgs& A, int e, Cur
     cf.jm[m] = sL * A.M[((size_t)eL * MS + 3 * (fL >> 1) + m) * nn + nL];
     cf.jp[m] = sR * A.M[((size_t)eR * MS + 3 * (fR >> 1) + m) * nn + nR];
   }
-  if (NS) {
-    const double* Fn = A.Fvf + ((size_t)it.nb * 6 + it.fb) * 4 * nf + it.ab;
+  if (NS && A.Fcarry) {
+    const double* Fn = A.Fcarry + ((size_t)it.nb * 6 + it.fb) * 4 * nf + it.ab;
 #pragma unroll
     for (int c = 0; c < 4; ++c) cf.fn[c] = Fn[c * nf];
   }
@@ -3750,13 +3869,10 @@ __global__ __launch_bounds__(NT, DG_N == 5 ? 3 : 1) void k_stage_curved(StageArg
       if (NS) {
         double q[4];
         curved_face_q(c, gm1, q);
-        // the neighbour projected its flux on its own face metric: along
-        // the own +xi that is -s_own s_nb times its value
-        const double sn = ((it.side != 0) == ((it.fb & 1) != 0)) ? -1.0 : 1.0;
 #pragma unroll
         for (int cc = 0; cc < 4; ++cc) {
           sQ[it.f][cc][it.a] = q[cc];
-          sFn[it.f][cc][it.a] = sn * c.fn[cc];
+          if (A.Fcarry) sFn[it.f][cc][it.a] = flux_sign(it) * c.fn[cc];
         }
 #pragma unroll
         for (int m = 0; m < 3; ++m) jfk[k][m] = so * Nv[m];
@@ -3857,14 +3973,23 @@ __global__ __launch_bounds__(NT, DG_N == 5 ? 3 : 1) void k_stage_curved(StageArg
           s3 = fma(c, sV[4 * d + 3][m], s3);
         }
         const int a = d == 0 ? ijk[1] + n1 * ijk[2] : (d == 1 ? ijk[0] + n1 * ijk[2] : ijk[0] + n1 * ijk[1]);
-        if (id == 0 || id == N) {  // Gt* = Ja_f . (Fv(own) + Fv(nb)) / 2, the neighbour's part in sFn
+        if (id == 0 || id == N) {
+          // Gt* = Ja_f . (Fv(own) + Fv(nb)) / 2: the own half; the neighbour's
+          // follows with the carry, from what it writes to Fvf_out
           const int f = 2 * d + (id == N);
           const double w = 0.5 * (id == N ? swinv[N] : -swinv[0]);
           const double jx = sJf[f][0][a], jy = sJf[f][1][a], jz = sJf[f][2][a];
-          s0 = fma(w, jx * Fv[0][0] + jy * Fv[1][0] + jz * Fv[2][0] + sFn[f][0][a], s0);
-          s1 = fma(w, jx * Fv[0][1] + jy * Fv[1][1] + jz * Fv[2][1] + sFn[f][1][a], s1);
-          s2 = fma(w, jx * Fv[0][2] + jy * Fv[1][2] + jz * Fv[2][2] + sFn[f][2][a], s2);
-          s3 = fma(w, jx * Fv[0][3] + jy * Fv[1][3] + jz * Fv[2][3] + sFn[f][3][a], s3);
+          double* Fo = A.Fvf_out + ((size_t)e * 6 + f) * 4 * nf + a;
+          double p[4];
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            p[c] = jx * Fv[0][c] + jy * Fv[1][c] + jz * Fv[2][c];
+            __builtin_nontemporal_store(p[c], &Fo[c * nf]);
+          }
+          s0 = fma(w, p[0], s0);
+          s1 = fma(w, p[1], s1);
+          s2 = fma(w, p[2], s2);
+          s3 = fma(w, p[3], s3);
         }
         acc[1] += s0;
         acc[2] += s1;
@@ -3877,6 +4002,12 @@ __global__ __launch_bounds__(NT, DG_N == 5 ? 3 : 1) void k_stage_curved(StageArg
   if (t < nn) {
     const double iJ = mt[9];
     const size_t o = (size_t)e * 5 * nn + t;
+    if (NS && A.Fcarry && A.mode == MODE_RK && A.A != 0.0) {  // the register's carry
+      double S[4];
+      carry_own_curved(sFn, swinv[0], ijk, S);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) gprev[1 + c] = fma(iJ, S[c], gprev[1 + c]);
+    }
     if (A.mode != MODE_RK) {
 #pragma unroll
       for (int v = 0; v < 5; ++v) A.Ut[o + v * nn] = acc[v] * iJ;
@@ -3891,130 +4022,6 @@ __global__ __launch_bounds__(NT, DG_N == 5 ? 3 : 1) void k_stage_curved(StageArg
       }
     }
   }
-}
-
-// BR1 lifting pass on curved elements: at each own face node the full
-// lifted gradient (reference derivatives of q along the three directions with
-// their lifting terms, chain rule with the node metric), the Cartesian viscous
-// fluxes and their projection on the face metric, Ja_f . Fv -> Fvf[e][f][c][a].
-// One element per workgroup (measured at N = 5: two elements per workgroup,
-// which speeds up the Cartesian lifting kernel, make this one 9 % slower).
-using PLC = Pack<1>;
-template <bool LES>
-__global__ __launch_bounds__(PLC::NTB) void k_lift_curved(StageArgs A) {
-  constexpr int EPB = PLC::EPB, TPE = PLC::TPE, FIC = PLC::FI;
-  __shared__ double sB[NB_STAGE];
-  __shared__ double sqAll[EPB][LES ? 5 : 4][nn];
-  __shared__ double sQAll[EPB][6][4][nf];
-  const int e0 = EPB * element_of_block(blockIdx.x, A.chunk);
-  if (e0 >= A.nelem) return;  // uniform over the workgroup
-  const Slot sl = slot_of_thread<PLC>(e0, A.nelem);
-  const int e = sl.e, t = sl.t, tid = threadIdx.x;
-  double (*sq)[nn] = sqAll[sl.s];
-  double (*sQ)[4][nf] = sQAll[sl.s];
-  const double gm1 = A.gamma - 1.0;
-  CurvedFace cf[FIC];
-#pragma unroll
-  for (int k = 0; k < FIC; ++k)
-    if (t + k * TPE < 6 * nf) cf[k].it = curved_face_item(A, e, t + k * TPE);
-  const double* Ue = A.U + (size_t)e * 5 * nn;
-  double u[5];
-  if (t < nn) {
-#pragma unroll
-    for (int v = 0; v < 5; ++v) u[v] = Ue[v * nn + t];
-  }
-  const double bval = tid < NB_STAGE ? A.basis[tid] : 0.0;
-#pragma unroll
-  for (int k = 0; k < FIC; ++k)
-    if (t + k * TPE < 6 * nf) curved_face_issue<false>(A, e, cf[k]);
-  if (tid < NB_STAGE) sB[tid] = bval;
-  if (t < nn) {
-    const double ir = rcp64(u[0]);
-    const double vx = u[1] * ir, vy = u[2] * ir, vz = u[3] * ir;
-    const double p = gm1 * (u[4] - 0.5 * (u[1] * vx + u[2] * vy + u[3] * vz));
-    sq[0][t] = vx;
-    sq[1][t] = vy;
-    sq[2][t] = vz;
-    sq[3][t] = p * ir;
-    if (LES) sq[LES ? 4 : 0][t] = u[0];
-  }
-#pragma unroll
-  for (int k = 0; k < FIC; ++k)
-    if (t + k * TPE < 6 * nf) {
-      double q[4];
-      curved_face_q(cf[k], gm1, q);
-#pragma unroll
-      for (int c = 0; c < 4; ++c) sQ[cf[k].it.f][c][cf[k].it.a] = q[c];
-    }
-  __syncthreads();
-  const double* sDw = sB + BL.Dw();
-  const double* swinv = sB + BL.winv();
-#pragma unroll
-  for (int k = 0; k < FIC; ++k)
-    if (t + k * TPE < 6 * nf) {
-      const CFaceItem& it = cf[k].it;
-      const int n = it.nown;
-      const int ijk[3] = {n % n1, (n / n1) % n1, n / nf};
-      const double* Mn = A.M + (size_t)e * MS * nn + n;
-      double s[3][4];
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        const int st = d == 0 ? 1 : (d == 1 ? n1 : nf);
-        const int id = ijk[d];
-        const int base = n - id * st;
-        const double* crow = sDw + id * n1;
-        double a0 = 0, a1 = 0, a2 = 0, a3 = 0;
-#pragma unroll 2
-        for (int l = 0; l < n1; ++l) {
-          const int m = base + l * st;
-          const double c = crow[l];
-          a0 = fma(c, sq[0][m], a0);
-          a1 = fma(c, sq[1][m], a1);
-          a2 = fma(c, sq[2][m], a2);
-          a3 = fma(c, sq[3][m], a3);
-        }
-        if (id == 0 || id == N) {
-          const int f = 2 * d + (id == N);
-          const int a = d == 0 ? ijk[1] + n1 * ijk[2] : (d == 1 ? ijk[0] + n1 * ijk[2] : ijk[0] + n1 * ijk[1]);
-          const double w = id == N ? swinv[N] : -swinv[0];
-          a0 = fma(w, sQ[f][0][a], a0);
-          a1 = fma(w, sQ[f][1][a], a1);
-          a2 = fma(w, sQ[f][2][a], a2);
-          a3 = fma(w, sQ[f][3][a], a3);
-        }
-        s[d][0] = a0;
-        s[d][1] = a1;
-        s[d][2] = a2;
-        s[d][3] = a3;
-      }
-      double mt[MS];
-#pragma unroll
-      for (int kk = 0; kk < MS; ++kk) mt[kk] = Mn[kk * nn];
-      double g[3][4];
-#pragma unroll
-      for (int m = 0; m < 3; ++m)
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-          g[m][c] = mt[9] * (mt[m] * s[0][c] + mt[3 + m] * s[1][c] + mt[6 + m] * s[2][c]);
-      double F[3][4];
-      double mu = A.mu, kap = A.kappa;
-      if (LES) {  // Smagorinsky eddy viscosity with the element's filter width
-        const double cs = A.cs_elem ? A.cs_elem[e] : A.cs;
-        const double mut = eddy_viscosity<double>(g, sq[LES ? 4 : 0][n], cs * cs * A.delta2_elem[e]);
-        mu += mut;
-        kap = fma(A.ktf, mut, kap);
-      }
-      viscous_flux<0, double>(g, sq[0][n], sq[1][n], sq[2][n], mu, kap, F[0]);
-      viscous_flux<1, double>(g, sq[0][n], sq[1][n], sq[2][n], mu, kap, F[1]);
-      viscous_flux<2, double>(g, sq[0][n], sq[1][n], sq[2][n], mu, kap, F[2]);
-      double Nv[3];
-      const double so = curved_face_normal(cf[k], Nv);
-      const double Jf[3] = {so * Nv[0], so * Nv[1], so * Nv[2]};  // face metric along the own +xi
-      double* out = A.Fvf + ((size_t)e * 6 + it.f) * 4 * nf + it.a;
-#pragma unroll
-      for (int c = 0; c < 4; ++c)  // streaming: read once, by the neighbour
-        __builtin_nontemporal_store(Jf[0] * F[0][c] + Jf[1] * F[1][c] + Jf[2] * F[2][c], &out[c * nf]);
-    }
 }
 
 // ===========================================================================
@@ -4581,93 +4588,77 @@ inline StageArgs grouped(const StageArgs& A) {
   return B;
 }
 
-template <int VF, class R>
+template <int VF, bool BLEND, bool WALL, bool DEFER>
+hipError_t launch_stage_ns(const StageArgs& A, int eq, hipStream_t s) {
+  const dim3 grid(blocks_for(A)), block(PS::NTB);
+  if (eq == 2) {
+    if constexpr (VF != VF_CH && DEFER) hipLaunchKernelGGL((k_stage<VF, 2, BLEND, double, WALL, DEFER>), grid, block, 0, s, A);
+    else return hipErrorInvalidValue;
+  } else {
+    hipLaunchKernelGGL((k_stage<VF, 1, BLEND, double, WALL, DEFER>), grid, block, 0, s, A);
+  }
+  return hipGetLastError();
+}
+
+// FP64.  Navier-Stokes runs with the deferred viscous exchange; A.Fvf set asks
+// for the two-pass lifting (no eddy viscosity, walls or blending).
+template <int VF>
 hipError_t launch_stage_vf(const StageArgs& A0, int eq, hipStream_t s) {
   const StageArgs A = grouped<PS>(A0);
   const dim3 grid(blocks_for(A)), block(PS::NTB);
-  if (A.wall_dir >= 0) {  // walls: FP64 Navier-Stokes (checked on the host)
-    if constexpr (sizeof(R) == 8) {
-      if (eq == 2) {
-        if constexpr (VF != VF_CH) {
-          if (A.blend) hipLaunchKernelGGL((k_stage<VF, 2, true, double, true>), grid, block, 0, s, A);
-          else hipLaunchKernelGGL((k_stage<VF, 2, false, double, true>), grid, block, 0, s, A);
-        } else {
-          return hipErrorInvalidValue;
-        }
-      } else if (eq == 1) {
-        if (A.blend) hipLaunchKernelGGL((k_stage<VF, 1, true, double, true>), grid, block, 0, s, A);
-        else hipLaunchKernelGGL((k_stage<VF, 1, false, double, true>), grid, block, 0, s, A);
-      } else {
-        return hipErrorInvalidValue;
-      }
-      return hipGetLastError();
-    } else {
-      return hipErrorInvalidValue;
-    }
+  if (eq == 0) {
+    if (A.wall_dir >= 0) return hipErrorInvalidValue;
+    if (A.blend) hipLaunchKernelGGL((k_stage<VF, 0, true, double>), grid, block, 0, s, A);
+    else hipLaunchKernelGGL((k_stage<VF, 0, false, double>), grid, block, 0, s, A);
+    return hipGetLastError();
   }
-  if (A.blend && eq >= 1) {  // FP64 (checked on the host)
-    if constexpr (sizeof(R) == 8) {
-      if (eq == 2) {
-        if constexpr (VF != VF_CH) hipLaunchKernelGGL((k_stage<VF, 2, true, double>), grid, block, 0, s, A);
-        else return hipErrorInvalidValue;
-      } else {
-        hipLaunchKernelGGL((k_stage<VF, 1, true, double>), grid, block, 0, s, A);
-      }
-    } else {
-      return hipErrorInvalidValue;
-    }
-  } else if (eq == 2) {
-    if constexpr (VF != VF_CH) hipLaunchKernelGGL((k_stage<VF, 2, false, R>), grid, block, 0, s, A);
-    else return hipErrorInvalidValue;
-  } else if (eq == 1) {
-    if constexpr (sizeof(R) == 8) {
-      if (A.split) {
-        hipLaunchKernelGGL((k_stage<VF, 1, false, double, false, true>), grid, block, 0, s, A);
-        return hipGetLastError();
-      }
-    }
-    hipLaunchKernelGGL((k_stage<VF, 1, false, R>), grid, block, 0, s, A);
-  } else if (A.blend) {
-    if constexpr (sizeof(R) == 8) hipLaunchKernelGGL((k_stage<VF, 0, true, double>), grid, block, 0, s, A);
-    else return hipErrorInvalidValue;
-  } else {
-    hipLaunchKernelGGL((k_stage<VF, 0, false, R>), grid, block, 0, s, A);
-  }
+  if (A.Fvf) return A.blend || A.wall_dir >= 0 ? hipErrorInvalidValue : launch_stage_ns<VF, false, false, false>(A, eq, s);
+  if (A.wall_dir >= 0)
+    return A.blend ? launch_stage_ns<VF, true, true, true>(A, eq, s) : launch_stage_ns<VF, false, true, true>(A, eq, s);
+  return A.blend ? launch_stage_ns<VF, true, false, true>(A, eq, s) : launch_stage_ns<VF, false, false, true>(A, eq, s);
+}
+
+template <int VF>
+hipError_t launch_stage_mixed_vf(const StageArgs& A0, int eq, hipStream_t s) {
+  const StageArgs A = grouped<PS>(A0);
+  const dim3 grid(blocks_for(A)), block(PS::NTB);
+  if (A.wall_dir >= 0 || A.blend) return hipErrorInvalidValue;
+  if (eq == 2) hipLaunchKernelGGL((k_stage<VF, 2, false, float>), grid, block, 0, s, A);
+  else if (eq == 1) hipLaunchKernelGGL((k_stage<VF, 1, false, float>), grid, block, 0, s, A);
+  else hipLaunchKernelGGL((k_stage<VF, 0, false, float>), grid, block, 0, s, A);
   return hipGetLastError();
 }
 
 hipError_t launch_stage(const StageArgs& A, int eq, hipStream_t s) {
   switch (A.vf) {
-    case VF_KG: return launch_stage_vf<VF_KG, double>(A, eq, s);
-    case VF_PI: return launch_stage_vf<VF_PI, double>(A, eq, s);
-    case VF_CH: return launch_stage_vf<VF_CH, double>(A, eq, s);
-    default: return launch_stage_vf<VF_STD, double>(A, eq, s);
+    case VF_KG: return launch_stage_vf<VF_KG>(A, eq, s);
+    case VF_PI: return launch_stage_vf<VF_PI>(A, eq, s);
+    case VF_CH: return launch_stage_vf<VF_CH>(A, eq, s);
+    default: return launch_stage_vf<VF_STD>(A, eq, s);
   }
 }
 
 // Mixed operator: flux forms whose reference shift is exact (PI, STD).
 hipError_t launch_stage_mixed(const StageArgs& A, int eq, hipStream_t s) {
   switch (A.vf) {
-    case VF_PI: return launch_stage_vf<VF_PI, float>(A, eq, s);
-    case VF_STD: return launch_stage_vf<VF_STD, float>(A, eq, s);
+    case VF_PI: return launch_stage_mixed_vf<VF_PI>(A, eq, s);
+    case VF_STD: return launch_stage_mixed_vf<VF_STD>(A, eq, s);
     default: return hipErrorInvalidValue;
   }
 }
 
+// Two-pass lifting (FP64 Navier-Stokes without the eddy viscosity or walls).
 hipError_t launch_lift(const StageArgs& A0, int eq, hipStream_t s) {
   const StageArgs A = grouped<PL>(A0);
-  if (A.wall_dir >= 0) {
-    if (eq == 2) hipLaunchKernelGGL((k_lift<double, true, true>), dim3(blocks_for(A)), dim3(PL::NTB), 0, s, A);
-    else hipLaunchKernelGGL((k_lift<double, false, true>), dim3(blocks_for(A)), dim3(PL::NTB), 0, s, A);
-    return hipGetLastError();
-  }
-  if (eq == 2) hipLaunchKernelGGL((k_lift<double, true>), dim3(blocks_for(A)), dim3(PL::NTB), 0, s, A);
-  else if (A.split) {
-    const StageArgs B = grouped<PS>(A0);
-    hipLaunchKernelGGL(k_lift_split, dim3(blocks_for(B)), dim3(PS::NTB), 0, s, B);
-  } else {
-    hipLaunchKernelGGL((k_lift<double, false>), dim3(blocks_for(A)), dim3(PL::NTB), 0, s, A);
-  }
+  if (A.wall_dir >= 0 || eq != 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_lift<double, false>), dim3(blocks_for(A)), dim3(PL::NTB), 0, s, A);
+  return hipGetLastError();
+}
+
+// X = A.U + B S, and A.G += S where set (see k_complete).
+hipError_t launch_complete(const StageArgs& A, double* X, hipStream_t s) {
+  if (A.M) hipLaunchKernelGGL(k_complete_curved, dim3(blocks_for(A)), dim3(NT), 0, s, A, X);
+  else hipLaunchKernelGGL(k_complete, dim3(blocks_for(A)), dim3(NT), 0, s, A, X);
   return hipGetLastError();
 }
 
@@ -4688,7 +4679,8 @@ hipError_t launch_lift_mixed(const StageArgs& A0, int eq, hipStream_t s) {
 }
 
 hipError_t launch_alpha1(const StageArgs& A, hipStream_t s) {
-  hipLaunchKernelGGL(k_alpha1, dim3(blocks_for(A)), dim3(NT), 0, s, A);
+  if (A.carryU) hipLaunchKernelGGL(k_alpha1<true>, dim3(blocks_for(A)), dim3(NT), 0, s, A);
+  else hipLaunchKernelGGL(k_alpha1<false>, dim3(blocks_for(A)), dim3(NT), 0, s, A);
   return hipGetLastError();
 }
 
@@ -4781,13 +4773,6 @@ hipError_t launch_stage_curved(const StageArgs& A, int eq, hipStream_t s) {
   }
 }
 
-hipError_t launch_lift_curved(const StageArgs& A0, int eq, hipStream_t s) {
-  const StageArgs A = grouped<PLC>(A0);
-  if (eq == 2) hipLaunchKernelGGL((k_lift_curved<true>), dim3(blocks_for(A)), dim3(PLC::NTB), 0, s, A);
-  else hipLaunchKernelGGL((k_lift_curved<false>), dim3(blocks_for(A)), dim3(PLC::NTB), 0, s, A);
-  return hipGetLastError();
-}
-
 template <int VF>
 hipError_t launch_vjp_curved_vf(const VjpArgs& A, int eq, hipStream_t s) {
   const dim3 grid(8 * A.chunk), block(NT);
@@ -4824,9 +4809,9 @@ hipError_t launch_nonfinite(const ReduceArgs& R, hipStream_t s) {
 }
 
 const KernelTable kTable = {
-    NT, kFusedAlpha1 ? 1 : 0, launch_stage, launch_stage_mixed, launch_lift, launch_lift_mixed, launch_alpha1, launch_spread,
+    NT, kFusedAlpha1 ? 1 : 0, launch_stage, launch_stage_mixed, launch_lift, launch_lift_mixed, launch_complete, launch_alpha1, launch_spread,
     launch_max_rate, launch_integrals, launch_nonfinite, launch_vjp, launch_vjp_lift, launch_vjp_alpha_bar,
-    launch_vjp_alpha, launch_vjp_fv, launch_axpby, launch_metrics, launch_stage_curved, launch_lift_curved,
+    launch_vjp_alpha, launch_vjp_fv, launch_axpby, launch_metrics, launch_stage_curved,
     launch_vjp_curved, launch_vjp_lift_curved, launch_wall_flux,
 };
 
