@@ -897,8 +897,8 @@ __device__ __forceinline__ Slot slot_of_thread(int e0, int nelem) {
 // follows one launch later (the carry): the next stage kernel completes the
 // states it reads, u = u~ + B S, and the register, G = G~ + S, with F_nb of the
 // stage before (StageArgs.Fcarry), and k_complete does the same for a state
-// that is handed out.  S is summed over the directions in order and added by
-// one fma wherever it is formed, so every reader of a node gets the same bits.
+// that is handed out.  S is formed from rounded products as (x + y) + z over the
+// directions and added by one fma, so every reader of a node gets the same bits.
 // A node of the neighbour's face needs, besides the element's own flux there,
 // those of the neighbour's lateral neighbours where it lies on an edge of the
 // face: on the structured box the element across the neighbour's lateral face
@@ -959,18 +959,18 @@ __device__ __forceinline__ void carry_issue(const StageArgs& A, const FaceItem& 
 }
 
 // Completes the neighbour's rotated state X at the face node (momentum and
-// energy), the directions in order.
+// energy): (x + y) + z is (d + a) + b in the face direction d and the lateral
+// ones a < b, and (b + a) + d for d = z.
 __device__ __forceinline__ void carry_neighbour(const StageArgs& A, const FaceItem& it, const CarryLoads& c,
                                                 double X[5]) {
+#pragma clang fp contract(off)
   const double hw = half_winv(A.basis);
   const double cd = pick3(A.invJ, it.d) * (it.side ? -hw : hw);
-  const double c1 = it.d == 0 ? cd : c.cl[0], c2 = it.d == 0 ? c.cl[0] : (it.d == 1 ? cd : c.cl[1]);
-  const double c3 = it.d == 2 ? cd : c.cl[1];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    const double f1 = it.d == 0 ? c.fo[k] : c.fl[0][k], f2 = it.d == 0 ? c.fl[0][k] : (it.d == 1 ? c.fo[k] : c.fl[1][k]);
-    const double f3 = it.d == 2 ? c.fo[k] : c.fl[1][k];
-    X[1 + k] = fma(A.Bcarry, fma(c3, f3, fma(c2, f2, c1 * f1)), X[1 + k]);
+    const double pd = cd * c.fo[k], pa = c.cl[0] * c.fl[0][k], pb = c.cl[1] * c.fl[1][k];
+    const double S = ((it.d == 2 ? pb : pd) + pa) + (it.d == 2 ? pd : pb);
+    X[1 + k] = fma(A.Bcarry, S, X[1 + k]);
   }
 }
 
@@ -978,6 +978,7 @@ __device__ __forceinline__ void carry_neighbour(const StageArgs& A, const FaceIt
 // wmask, the walls, have none).
 __device__ __forceinline__ void carry_own(const double (*sFn)[4][nf], const double invJ[3], double hw, const int ijk[3],
                                           int wmask, double S[4]) {
+#pragma clang fp contract(off)
 #pragma unroll
   for (int c = 0; c < 4; ++c) S[c] = 0.0;
 #pragma unroll
@@ -988,7 +989,7 @@ __device__ __forceinline__ void carry_own(const double (*sFn)[4][nf], const doub
       const int a = d == 0 ? ijk[1] + n1 * ijk[2] : (d == 1 ? ijk[0] + n1 * ijk[2] : ijk[0] + n1 * ijk[1]);
       const double w = invJ[d] * (id == N ? hw : -hw);
 #pragma unroll
-      for (int c = 0; c < 4; ++c) S[c] = fma(w, sFn[f][c][a], S[c]);
+      for (int c = 0; c < 4; ++c) S[c] = S[c] + w * sFn[f][c][a];
     }
   }
 }
@@ -1329,15 +1330,19 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
     ijk[2] = t / nf;
   }
   const double hw = DEFER ? half_winv(A.basis) : 0.0;
+  // the carry of the own node, kept for the register where registers allow
+  // (with walls it is formed again: 132 registers would leave 3 waves per SIMD)
+  constexpr bool KEEP_S = OWN_LDS && !WALL;
+  double S[4] = {0.0, 0.0, 0.0, 0.0};
   if constexpr (OWN_LDS) {
     if (A.Fcarry) {  // uniform: the neighbours' fluxes of the stage before
 #pragma unroll
       for (int k = 0; k < FI; ++k)
         if (t + k * TPE < 6 * nf && !(WALL && fd[k].it.nb < 0)) store_q(fd[k].it, fd[k].c.fn, sFn);
       __syncthreads();
+      if (KEEP_S || A.carryU)
+        if (t < nn) carry_own(sFn, A.invJ, hw, ijk, wmask, S);
       if (A.carryU && t < nn) {
-        double S[4];
-        carry_own(sFn, A.invJ, hw, ijk, wmask, S);
 #pragma unroll
         for (int c = 0; c < 4; ++c) u[1 + c] = fma(A.Bcarry, S[c], u[1 + c]);
       }
@@ -1409,16 +1414,24 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
     volume_dir<VF, 0, R, FG, ROT>(sP, sDhat, swinv[0], t, ijk[0], me, invJ[0], (R)gm1, acc, sDw, gs[0]);
     volume_dir<VF, 1, R, FG, ROT>(sP, sDhat, swinv[0], t, ijk[1], me, invJ[1], (R)gm1, acc, sDw, gs[1]);
     volume_dir<VF, 2, R, FG, ROT>(sP, sDhat, swinv[0], t, ijk[2], me, invJ[2], (R)gm1, acc, sDw, gs[2]);
-    // advective surface terms
+    // one branch per direction: advective surface terms and, with the fused
+    // gradient, the diagonal of Dw (zero inside) and the lifting terms
+    const R qo[4] = {me[1], me[2], me[3], me[6]};
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       const int id = ijk[d];
-      const int a = d == 0 ? ijk[1] + n1 * ijk[2] : (d == 1 ? ijk[0] + n1 * ijk[2] : ijk[0] + n1 * ijk[1]);
-      if (id == 0 || id == N) {  // one branch for both faces (N >= 1)
+      if (id == 0 || id == N) {
+        const int a = d == 0 ? ijk[1] + n1 * ijk[2] : (d == 1 ? ijk[0] + n1 * ijk[2] : ijk[0] + n1 * ijk[1]);
         const int f = 2 * d + (id == N);
-        const R c = invJ[d] * (id == N ? -swinv[N] : swinv[0]);
+        const R w = id == N ? swinv[N] : -swinv[0];
+        const R c = -(invJ[d] * w);
 #pragma unroll
         for (int v = 0; v < 5; ++v) acc[v] = fmaR(c, sF[f][v][a], acc[v]);
+        if (FG) {
+          const R cd = sDw[id * n1 + id];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) gs[d][k] = fmaR(w, sQ[f][k][a], fmaR(cd, qo[k], gs[d][k]));
+        }
       }
     }
     if (NS && !BLEND) {  // blended: after the subcell pass (registers)
@@ -1426,23 +1439,10 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
       if (!FG) {
         lifted_gradient<R, nnp>(sP, sQ, sDw, swinv, t, ijk, invJ, g);
       } else {
-      // BR1 gradient: line sums from the volume loop + diagonal + interface values
-      const R qo[4] = {me[1], me[2], me[3], me[6]};
 #pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        const int id = ijk[d];
-        const int a = d == 0 ? ijk[1] + n1 * ijk[2] : (d == 1 ? ijk[0] + n1 * ijk[2] : ijk[0] + n1 * ijk[1]);
-        R s[4] = {gs[d][0], gs[d][1], gs[d][2], gs[d][3]};
-        if (id == 0 || id == N) {  // diagonal of Dw (zero inside) and the lifting term
-          const int f = 2 * d + (id == N);
-          const R cd = sDw[id * n1 + id];
-          const R w = id == N ? swinv[N] : -swinv[0];
+        for (int d = 0; d < 3; ++d)
 #pragma unroll
-          for (int c = 0; c < 4; ++c) s[c] = fmaR(w, sQ[f][c][a], fmaR(cd, qo[c], s[c]));
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c) g[d][c] = invJ[d] * s[c];
-      }
+          for (int c = 0; c < 4; ++c) g[d][c] = invJ[d] * gs[d][c];
       }
       node_viscous_flux<LES, R>(A, e, g, me, Fv);
     }
@@ -1626,8 +1626,7 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
     if (MX) ut[4] += ref.h * ut[0];  // undo the energy-flux shift h0 * (mass flux)
     const size_t o = (size_t)e * 5 * nn + t;
     if (DEFER && A.Fcarry && A.mode == MODE_RK && A.A != 0.0) {  // the register's carry
-      double S[4];
-      carry_own(reinterpret_cast<const double (*)[4][nf]>(sPool + oFn), A.invJ, hw, ijk, wmask, S);
+      if (!KEEP_S) carry_own(reinterpret_cast<const double (*)[4][nf]>(sPool + oFn), A.invJ, hw, ijk, wmask, S);
 #pragma unroll
       for (int c = 0; c < 4; ++c) gprev[1 + c] += S[c];
     }
@@ -1856,6 +1855,7 @@ __global__ __launch_bounds__(PL::NTB, PL::FI == 1 && N >= 2 ? 8 : 4) void k_lift
 
 // Carry S of one node of element e, straight from global memory (see CarryLoads).
 __device__ __forceinline__ void carry_node(const StageArgs& A, int e, int n, double S[4]) {
+#pragma clang fp contract(off)
   const int ijk[3] = {n % n1, (n / n1) % n1, n / nf};
   const double hw = half_winv(A.basis);
 #pragma unroll
@@ -1870,7 +1870,7 @@ __device__ __forceinline__ void carry_node(const StageArgs& A, int e, int n, dou
     const double* F = A.Fcarry + ((size_t)nb * 6 + (f ^ 1)) * 4 * nf + a;
     const double w = A.invJ[d] * (id == N ? hw : -hw);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) S[c] = fma(w, F[c * nf], S[c]);
+    for (int c = 0; c < 4; ++c) S[c] = S[c] + w * F[c * nf];
   }
 }
 
