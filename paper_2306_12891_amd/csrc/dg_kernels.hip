@@ -857,7 +857,11 @@ __device__ __forceinline__ void wall_face_loads(const double* U, int e, const Fa
 template <int E>
 struct Pack {
   static constexpr int EPB = E;
-  static constexpr int TPE = E == 1 ? NT : (nn > 6 * nf ? nn : 6 * nf);
+  // one element: whole waves, enough of them for one face item per thread (at N
+  // = 3 and 4 the element has more face nodes than nodes: with NT threads a
+  // second, mostly empty round of face items doubles the face data in registers)
+  static constexpr int ITEMS = nn > 6 * nf ? nn : 6 * nf;
+  static constexpr int TPE = E == 1 ? (ITEMS + 63) / 64 * 64 : ITEMS;
   static constexpr int NTB = ((E * TPE + 63) / 64) * 64;
   // face items handled by one thread of a slot (item q = t + k TPE, k < FI)
   static constexpr int FI = (6 * nf + TPE - 1) / TPE;
@@ -1086,7 +1090,7 @@ __device__ __forceinline__ void face_item(const StageArgs& A, const FaceItem& it
 #elif DG_EPB_STAGE > 1
 #define DG_STAGE_BOUNDS __launch_bounds__(PS::NTB, VF == VF_CH ? 1 : 4)
 #else
-#define DG_STAGE_BOUNDS __launch_bounds__(PS::NTB)
+#define DG_STAGE_BOUNDS __launch_bounds__(PS::NTB, BLEND && EQ >= 1 && VF != VF_CH && N <= 4 ? 4 : 1)
 #endif
 // Indicator quantity q = rho p of a conservative node state.
 __device__ __forceinline__ double indicator_q(const double u[5], double gm1) {
@@ -1100,8 +1104,8 @@ __device__ __forceinline__ double indicator_q(const double u[5], double gm1) {
 // st: nn doubles each, sVi: V^-1 already written), the three energy sums by
 // lane shuffles within each wave and the per-wave partials (sred: 3 NT/64
 // doubles) in a fixed order, then the sigmoid, the clip at alpha_max and the
-// cut-off below alpha_min.  Every thread of the workgroup (NT threads, one
-// element) calls it; the result is valid in thread 0.
+// cut-off below alpha_min.  Every thread of the workgroup (at least NT threads,
+// one element) calls it; the result is valid in thread 0.
 constexpr int NWAVE = NT / 64;
 __device__ __forceinline__ double element_alpha1(const StageArgs& A, const double* sVi, double* sq, double* st,
                                                  double* sred, int t, const int ijk[3], double qt) {
@@ -1140,7 +1144,7 @@ __device__ __forceinline__ double element_alpha1(const StageArgs& A, const doubl
     r1 += __shfl_xor(r1, o);
     r2 += __shfl_xor(r2, o);
   }
-  if ((t & 63) == 0) {
+  if ((t & 63) == 0 && t < NT) {
     sred[t >> 6] = r0;
     sred[NWAVE + (t >> 6)] = r1;
     sred[2 * NWAVE + (t >> 6)] = r2;
@@ -1651,7 +1655,7 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
   // separate indicator launch it saves.
   if constexpr (BLEND && !NS && kFusedAlpha1) {
     if (A.alpha1_next && A.mode == MODE_RK) {  // uniform over the workgroup
-      static_assert(POOL >= 2 * nn + 3 * NWAVE && PS::NTB == NT && BL.Vinv() == NB_STAGE,
+      static_assert(POOL >= 2 * nn + 3 * NWAVE && BL.Vinv() == NB_STAGE,
                     "indicator scratch in the LDS pool, V^-1 after the stage basis");
       double* sq = reinterpret_cast<double*>(sPool);
       double* st = sq + nn;
