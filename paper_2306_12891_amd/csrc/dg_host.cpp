@@ -185,6 +185,7 @@ struct dg_ctx {
   double* basis = nullptr;
   double* G = nullptr;
   double* U2 = nullptr;
+  double* U3 = nullptr;  // third state of an odd chain of stages (allocated on first use, may stay NULL)
   double* alpha1 = nullptr;
   double* alpha1b = nullptr;  // the other of the pair the fused indicator ping-pongs
   double* alpha = nullptr;
@@ -253,6 +254,7 @@ void release(dg_ctx* c) {
   hipFree(c->basis);
   hipFree(c->G);
   hipFree(c->U2);
+  hipFree(c->U3);
   hipFree(c->alpha1);
   hipFree(c->alpha1b);
   hipFree(c->alpha);
@@ -390,16 +392,34 @@ struct Carry {
 // before while it writes its own.  Without it (no memory, or the stream is
 // being captured and the first call did not come before) every stage completes
 // its state and register by a pass of its own: the same results.
-void ensure_carry_buffer(dg_ctx* c) {
-  if (!deferred_on(c) || c->Fvf2) return;
+bool capturing(dg_ctx* c) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(c->stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
-    return;
-  }
+  if (hipStreamIsCapturing(c->stream, &st) == hipSuccess && st == hipStreamCaptureStatusNone) return false;
+  (void)hipGetLastError();
+  return true;
+}
+
+void ensure_carry_buffer(dg_ctx* c) {
+  if (!deferred_on(c) || c->Fvf2 || capturing(c)) return;
   if (hipMalloc((void**)&c->Fvf2, (size_t)c->nelem * 6 * 4 * c->nf * sizeof(double)) != hipSuccess) {
     (void)hipGetLastError();
     c->Fvf2 = nullptr;
+  }
+}
+
+// The third state of an odd number of stages: U -> U2 -> U3 -> U and then U and
+// U2 in turn end in U, where two states end in U2 and need a copy (80 B per
+// node, 8 % of an Euler step at N = 7).  The deferred exchange needs none: its
+// completion at the end of the call goes from U2 to U.  Taken only where it is at
+// most an eighth of the free memory; without it the copy remains.
+void ensure_third_state(dg_ctx* c) {
+  if (c->U3 || deferred_on(c) || capturing(c)) return;
+  const size_t bytes = c->nstate * sizeof(double);
+  size_t avail = 0, total = 0;
+  if (hipMemGetInfo(&avail, &total) != hipSuccess || bytes > avail / 8 ||
+      hipMalloc((void**)&c->U3, bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    c->U3 = nullptr;
   }
 }
 
@@ -997,6 +1017,9 @@ int dg_rk_steps(dg_ctx* c, double* U, double dt, int nsteps) {
   if (!finite_pos(dt)) return fail(c, DG_EINVAL, "rk_step: dt must be finite and > 0");
   if (nsteps < 0) return fail(c, DG_EINVAL, "rk_step: nsteps < 0");
   ensure_carry_buffer(c);
+  const bool odd = nsteps % 2 == 1 && !deferred_on(c);
+  if (odd) ensure_third_state(c);
+  const bool three = odd && c->U3;
   double* cur = U;
   Carry carry;
   // blended Euler operator: the indicator of the start state once, then each
@@ -1011,7 +1034,7 @@ int dg_rk_steps(dg_ctx* c, double* U, double dt, int nsteps) {
   }
   for (int s = 0; s < nsteps; ++s)
     for (int k = 0; k < 5; ++k) {
-      double* nxt = (cur == U) ? c->U2 : U;
+      double* nxt = (cur == U) ? c->U2 : (three && s == 0 && k == 1) ? c->U3 : U;
       const int writeG = (k < 4) ? 1 : 0;  // the last stage's register is never read again
       const int rc = run_stage(c, cur, nxt, nullptr, MODE_RK, kA[k], kB[k] * dt, writeG, nullptr,
                                fuse ? c->alpha1b : nullptr, &carry);
