@@ -2316,39 +2316,35 @@ __device__ void wall_model_flux_vjp(const VjpArgs& A, double rhow, double rx, do
 }
 
 // Neighbour lambda (components 1..4) on face item q into sLn (zero at walls).
-template <int D>
-__device__ __forceinline__ void neighbour_lambda(const VjpArgs& A, int e, int q, double (*sLn)[4][nf]) {
-  const int f = q / nf;
-  const int a = q - f * nf;
-  const int side = f & 1;
-  if (A.nbr[6 * e + f] < 0) {
+__device__ __forceinline__ void neighbour_lambda(const VjpArgs& A, const Nbr6& nb6, int q, double (*sLn)[4][nf]) {
+  const FaceItem it = face_item_geometry(nb6, q);
+  if (it.nb < 0) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) sLn[f][c][a] = 0.0;
+    for (int c = 0; c < 4; ++c) sLn[it.f][c][it.a] = 0.0;
     return;
   }
-  const double* Ln = A.Lbar + (size_t)A.nbr[6 * e + f] * 5 * nn;
-  const int nnb = face_node(D, side ? 0 : N, a);
+  const double* Ln = A.Lbar + (size_t)it.nb * 5 * nn + it.nnb;
 #pragma unroll
-  for (int c = 0; c < 4; ++c) sLn[f][c][a] = Ln[(1 + c) * nn + nnb];
+  for (int c = 0; c < 4; ++c) sLn[it.f][c][it.a] = Ln[(1 + c) * nn];
 }
 
 // Pass 1 of the viscous reverse: cotangent of each element's normal lifted
-// gradient at its own face nodes -> Gbf[e][f][c][a].
-template <int D>
+// gradient at its own face nodes -> Gbf[e][f][c][a].  One code path for all
+// directions: with a branch per direction a wave at N = 5 (36 nodes per face)
+// ran two of them.
 __device__ __forceinline__ void vjp_lift_face_node(const VjpArgs& A, int e, int q, const double (*sLam)[nn],
                                                    const double (*sLn)[4][nf], const double (*sU)[nn],
                                                    const double* sDw, const double* swinv, int wmask) {
-  const int f = q / nf;
-  const int a = q - f * nf;
-  const int m = face_node(D, (f & 1) ? N : 0, a);
+  const int f = q / nf, a = q - f * nf, d = f >> 1;
+  const int m = face_node(d, (f & 1) ? N : 0, a);
   const int ijk[3] = {m % n1, (m / n1) % n1, m / nf};
   double Fvb[3][4], gb[3][4];
   viscous_flux_cotangent(sLam, sLn, sDw, swinv, m, ijk, A.invJ, Fvb, wmask);
   const double u[3] = {sU[0][m], sU[1][m], sU[2][m]};
   gradient_cotangent(Fvb, u, A.mu, A.kappa, gb);
-  double* out = A.Gbf + ((size_t)e * 6 + f) * 4 * nf;
+  double* out = A.Gbf + ((size_t)e * 6 + f) * 4 * nf + a;
 #pragma unroll
-  for (int c = 0; c < 4; ++c) out[c * nf + a] = gb[D][c];
+  for (int c = 0; c < 4; ++c) out[c * nf] = d == 0 ? gb[0][c] : (d == 1 ? gb[1][c] : gb[2][c]);
 }
 
 __global__ __launch_bounds__(NT) void k_vjp_lift(VjpArgs A) {
@@ -2369,18 +2365,12 @@ __global__ __launch_bounds__(NT) void k_vjp_lift(VjpArgs A) {
 #pragma unroll
     for (int v = 0; v < 5; ++v) sLam[v][t] = Le[v * nn + t];
   }
-  for (int q = t; q < 6 * nf; q += NT) {
-    if (q < 2 * nf) neighbour_lambda<0>(A, e, q, sLn);
-    else if (q < 4 * nf) neighbour_lambda<1>(A, e, q, sLn);
-    else neighbour_lambda<2>(A, e, q, sLn);
-  }
+  const Nbr6 nb6 = uniform_nbr6(A.nbr, e);
+  for (int q = t; q < 6 * nf; q += NT) neighbour_lambda(A, nb6, q, sLn);
   __syncthreads();
   const int wmask = vjp_wall_mask(A, e);
-  for (int q = t; q < 6 * nf; q += NT) {
-    if (q < 2 * nf) vjp_lift_face_node<0>(A, e, q, sLam, sLn, sU, sB + BL.Dw(), sB + BL.winv(), wmask);
-    else if (q < 4 * nf) vjp_lift_face_node<1>(A, e, q, sLam, sLn, sU, sB + BL.Dw(), sB + BL.winv(), wmask);
-    else vjp_lift_face_node<2>(A, e, q, sLam, sLn, sU, sB + BL.Dw(), sB + BL.winv(), wmask);
-  }
+  for (int q = t; q < 6 * nf; q += NT)
+    vjp_lift_face_node(A, e, q, sLam, sLn, sU, sB + BL.Dw(), sB + BL.winv(), wmask);
 }
 
 // Interface part of face item q: the cotangent of the element's own face
@@ -2393,33 +2383,71 @@ __global__ __launch_bounds__(NT) void k_vjp_lift(VjpArgs A) {
 // the own state through both arguments; plus the reverse of the wall model's
 // viscous flux, whose exchange-node part goes to sWx[side][variable][a]
 // (density and momenta).
-template <int VF, bool WALL = false>
-__device__ __forceinline__ void vjp_face_item(const VjpArgs& A, int e, int q, const double* swinv,
-                                              double (*sSF)[5][nf], double (*sWx)[4][nf] = nullptr) {
-  const FaceItem it = face_item_geometry(A.nbr, e, q);
-  if (WALL && it.nb < 0) {
-    const int row[5] = {0, 1 + it.d, it.k1, it.k2, 4};
-    const double* Ue = A.U + (size_t)e * 5 * nn;
-    const double* Le = A.Lbar + (size_t)e * 5 * nn;
-    const double invJd = it.d == 0 ? A.invJ[0] : (it.d == 1 ? A.invJ[1] : A.invJ[2]);
+// Navier-Stokes: the same loads also give q* (forward gradient, into sQ) and the
+// neighbour's lambda (sLn), and the neighbour's normal-gradient cotangent of
+// pass 1 is read into sGn.  The element's own lambda comes from sLam.
+template <int VF, bool NS, bool WALL>
+__device__ __forceinline__ void vjp_face_item(const VjpArgs& A, int e, const Nbr6& nb6, int q, const double* swinv,
+                                              const double (*sLam)[nn], double (*sSF)[5][nf], double (*sQ)[4][nf],
+                                              double (*sLn)[4][nf], double (*sGn)[4][nf],
+                                              double (*sWx)[4][nf] = nullptr) {
+  const FaceItem it = face_item_geometry(nb6, q);
+  const double invJd = it.d == 0 ? A.invJ[0] : (it.d == 1 ? A.invJ[1] : A.invJ[2]);
+  const int row[5] = {0, 1 + it.d, it.k1, it.k2, 4};  // rotated position -> variable
+  const bool wall = WALL && it.nb < 0;
+  const double* Ue = A.U + (size_t)e * 5 * nn;
+  double L[5], R[5], fb[5], Lb[5], Rb[5], lo[5];
+  load_rotated(Ue, it.nown, it, L);  // own, for now
+#pragma unroll
+  for (int r = 0; r < 5; ++r) lo[r] = sLam[row[r]][it.nown];
+  if (wall) {
     const double cw = it.side ? -invJd * swinv[N] : invJd * swinv[0];
-    double L[5], R[5], fb[5], Lb[5], Rb[5];
 #pragma unroll
     for (int r = 0; r < 5; ++r) {
-      const double X = Ue[row[r] * nn + it.nown];
-      L[r] = (r == 1 && !it.side) ? -X : X;
-      R[r] = (r == 1 && it.side) ? -X : X;
-      fb[r] = cw * Le[row[r] * nn + it.nown];
+      R[r] = (r == 1 && it.side) ? -L[r] : L[r];
+      fb[r] = cw * lo[r];
     }
-    riemann_vjp<VF>(A.sf, L, R, A.gamma, fb, Lb, Rb);
+    if (!it.side) L[1] = -L[1];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) sLn[it.f][c][it.a] = sGn[it.f][c][it.a] = 0.0;
+  } else {
+    double ln[5], gn[4];
+    load_rotated(A.U + (size_t)it.nb * 5 * nn, it.nnb, it, R);  // the neighbour's, for now
+    load_rotated(A.Lbar + (size_t)it.nb * 5 * nn, it.nnb, it, ln);
+    if (NS) {
+      const double* Gn = A.Gbf + ((size_t)it.nb * 6 + (it.f ^ 1)) * 4 * nf + it.a;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) gn[c] = Gn[c * nf];
+    }
+    const double cm = -invJd * swinv[N], cp = invJd * swinv[0];
+#pragma unroll
+    for (int r = 0; r < 5; ++r) {
+      fb[r] = it.side ? fma(cm, lo[r], cp * ln[r]) : fma(cm, ln[r], cp * lo[r]);
+      const double o = L[r];
+      L[r] = it.side ? o : R[r];
+      R[r] = it.side ? R[r] : o;
+    }
+    if (NS) {
+      store_q(it, ln + 1, sLn);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) sGn[it.f][c][it.a] = gn[c];
+    }
+  }
+  if (NS) {
+    const double gm1 = A.gamma - 1.0;
+    double qs[4];
+    interface_q<0, double, false>(state64<0>(L, gm1), state64<0>(R, gm1), Ref{0.0, 0.0, 0.0}, qs);
+    store_q(it, qs, sQ);
+  }
+  riemann_vjp<VF>(A.sf, L, R, A.gamma, fb, Lb, Rb);
+  if (wall) {
     double ob[5];
 #pragma unroll
     for (int r = 0; r < 5; ++r) ob[r] = (it.side ? Lb[r] : Rb[r]) + (r == 1 ? -1.0 : 1.0) * (it.side ? Rb[r] : Lb[r]);
     const double cv = invJd * (it.side ? swinv[N] : -swinv[0]);
     double rhowb = 0.0, rxb = 0.0, m1b = 0.0, m2b = 0.0;
     wall_model_flux_vjp(A, L[0], Ue[it.nnb], Ue[it.k1 * nn + it.nnb], Ue[it.k2 * nn + it.nnb],
-                        it.side ? -1.0 : 1.0, cv * Le[it.k1 * nn + it.nown], cv * Le[it.k2 * nn + it.nown], rhowb,
-                        rxb, m1b, m2b);
+                        it.side ? -1.0 : 1.0, cv * lo[2], cv * lo[3], rhowb, rxb, m1b, m2b);
     ob[0] += rhowb;
 #pragma unroll
     for (int r = 0; r < 5; ++r) sSF[it.f][row[r]][it.a] = ob[r];
@@ -2429,74 +2457,29 @@ __device__ __forceinline__ void vjp_face_item(const VjpArgs& A, int e, int q, co
     sWx[it.side][it.k2][it.a] = m2b;
     return;
   }
-  const int eL = it.side ? e : it.nb, eR = it.side ? it.nb : e;
-  const int nL = it.side ? it.nown : it.nnb, nR = it.side ? it.nnb : it.nown;
-  const int row[5] = {0, 1 + it.d, it.k1, it.k2, 4};  // rotated position -> variable
-  const double* UL = A.U + (size_t)eL * 5 * nn;
-  const double* UR = A.U + (size_t)eR * 5 * nn;
-  const double* LL = A.Lbar + (size_t)eL * 5 * nn;
-  const double* LR = A.Lbar + (size_t)eR * 5 * nn;
-  const double invJd = it.d == 0 ? A.invJ[0] : (it.d == 1 ? A.invJ[1] : A.invJ[2]);
-  const double cm = -invJd * swinv[N], cp = invJd * swinv[0];
-  double L[5], R[5], fb[5], Lb[5], Rb[5];
-#pragma unroll
-  for (int r = 0; r < 5; ++r) {
-    const int v = row[r];
-    L[r] = UL[v * nn + nL];
-    R[r] = UR[v * nn + nR];
-    fb[r] = fma(cm, LL[v * nn + nL], cp * LR[v * nn + nR]);
-  }
-  riemann_vjp<VF>(A.sf, L, R, A.gamma, fb, Lb, Rb);
 #pragma unroll
   for (int r = 0; r < 5; ++r) sSF[it.f][row[r]][it.a] = it.side ? Lb[r] : Rb[r];
 }
 
-// Navier-Stokes data of face item q: q* (forward gradient), the neighbour's
-// lambda and its normal-gradient cotangent.
-template <int D, bool GN = true>
-__device__ __forceinline__ void vjp_face_ns(const VjpArgs& A, int e, int q, double (*sQ)[4][nf],
-                                            double (*sLn)[4][nf], double (*sGn)[4][nf]) {
-  const int f = q / nf;
-  const int a = q - f * nf;
-  const int side = f & 1;
-  const int nb = A.nbr[6 * e + f];
-  const int eL = side ? e : nb, eR = side ? nb : e;
-  const int nL = face_node(D, N, a), nR = face_node(D, 0, a), nnb = side ? nR : nL;
-  double L[5], R[5];
-  if (nb < 0) {  // wall: the own face state and its mirror image
-    const int no = side ? nL : nR;
-#pragma unroll
-    for (int v = 0; v < 5; ++v) L[v] = R[v] = A.U[((size_t)e * 5 + v) * nn + no];
-    if (side) R[1 + D] = -R[1 + D];
-    else L[1 + D] = -L[1 + D];
-    const double gm1 = A.gamma - 1.0;
-    double qs[4];
-    interface_q<D, double, false>(state64<D>(L, gm1), state64<D>(R, gm1), Ref{0.0, 0.0, 0.0}, qs);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      sQ[f][c][a] = qs[c];
-      sLn[f][c][a] = 0.0;
-      if (GN) sGn[f][c][a] = 0.0;
-    }
-    return;
-  }
-#pragma unroll
-  for (int v = 0; v < 5; ++v) {
-    L[v] = A.U[((size_t)eL * 5 + v) * nn + nL];
-    R[v] = A.U[((size_t)eR * 5 + v) * nn + nR];
-  }
+// Pass 1 with the eddy viscosity: q* and the neighbour's lambda of face item q.
+__device__ __forceinline__ void vjp_face_ns(const VjpArgs& A, int e, const Nbr6& nb6, int q, double (*sQ)[4][nf],
+                                            double (*sLn)[4][nf]) {
+  const FaceItem it = face_item_geometry(nb6, q);
   const double gm1 = A.gamma - 1.0;
-  const Ref ref{0.0, 0.0, 0.0};
-  double qs[4];
-  interface_q<D, double, false>(state64<D>(L, gm1), state64<D>(R, gm1), ref, qs);
-  const double* Ln = A.Lbar + (size_t)nb * 5 * nn;
-  const double* Gn = A.Gbf + ((size_t)nb * 6 + (f ^ 1)) * 4 * nf;
+  double L[5], R[5], qs[4];
+  load_rotated(A.U + (size_t)e * 5 * nn, it.nown, it, L);
+  if (it.nb < 0) {  // wall: the own face state and its mirror image
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    sQ[f][c][a] = qs[c];
-    sLn[f][c][a] = Ln[(1 + c) * nn + nnb];
-    if (GN) sGn[f][c][a] = Gn[c * nf + a];
+    for (int v = 0; v < 5; ++v) R[v] = v == 1 ? -L[v] : L[v];
+  } else {
+    load_rotated(A.U + (size_t)it.nb * 5 * nn, it.nnb, it, R);
   }
+  // q* is the mean of both sides whichever is the minus one
+  interface_q<0, double, false>(state64<0>(L, gm1), state64<0>(R, gm1), Ref{0.0, 0.0, 0.0}, qs);
+  store_q(it, qs, sQ);
+  const double* Ln = A.Lbar + (size_t)it.nb * 5 * nn + it.nnb;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) sLn[it.f][c][it.a] = it.nb < 0 ? 0.0 : Ln[(1 + c) * nn];
 }
 
 // Pass 1 with the Smagorinsky model: the gradient cotangent at a face node
@@ -2527,11 +2510,8 @@ __global__ __launch_bounds__(NT) void k_vjp_lift_les(VjpArgs A) {
 #pragma unroll
     for (int k = 0; k < 7; ++k) sP[k][t] = me[k];
   }
-  for (int q = t; q < 6 * nf; q += NT) {
-    if (q < 2 * nf) vjp_face_ns<0, false>(A, e, q, sQ, sLn, nullptr);
-    else if (q < 4 * nf) vjp_face_ns<1, false>(A, e, q, sQ, sLn, nullptr);
-    else vjp_face_ns<2, false>(A, e, q, sQ, sLn, nullptr);
-  }
+  const Nbr6 nb6 = uniform_nbr6(A.nbr, e);
+  for (int q = t; q < 6 * nf; q += NT) vjp_face_ns(A, e, nb6, q, sQ, sLn);
   __syncthreads();
   const double* sDw = sB + BL.Dw();
   const double* swinv = sB + BL.winv();
@@ -2554,44 +2534,80 @@ __global__ __launch_bounds__(NT) void k_vjp_lift_les(VjpArgs A) {
 
 // Hand-derived reverse mode of the two-point volume flux with respect to its
 // first argument, in primitive variables (rho, u, p, x), for the flux
-// cotangent w (unrotated components).  x = h (PI, STD) or e (KG).
+// cotangent w (unrotated components).  x = h (PI, STD) or e (KG).  With the
+// sums s = a + b of the two nodes' values F_rho = r_s u_Ds / 4, F_m = F_rho u_s / 2
+// + p_s e_D / 2, F_E = F_rho x_s / 2 (+ p_s u_Ds / 4 for KG), so with T = 2 w_0 +
+// w_m . u_s + w_4 x_s the cotangents are
+//   rho: u_Ds T / 8, u: w_m r_s u_Ds / 8 + e_D r_s T / 8, p: w_D / 2,
+//   x: w_4 r_s u_Ds / 8  (KG: p += w_4 u_Ds / 4, u_D += w_4 p_s / 4).
+// The sums over the partners are formed without the factors 1/8, 1/2 and 1/4
+// (pb[0..3], pb[5]; pp; pe, ue), which vjp_volume_scale applies once.
+struct VolumeVjp {
+  double pb[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};  // rho, u, v, w, p (factor 1/2), x
+  double pe = 0.0, ue[3] = {0.0, 0.0, 0.0};       // KG: factor 1/4
+};
+
 template <int VF, int D>
 __device__ __forceinline__ void twopoint_vjp(const double me[7], double rl, const double ul[3], double pl,
-                                             double xl, const double w[5], double pb[6]) {
+                                             double xl, const double w[5], VolumeVjp& S) {
   if (VF == VF_STD) {
-    // d1 F# = (1/2) dF(a)/da; F = (rho u_D, rho u_D u + p e_D, rho h u_D)
-    const double r = me[0], uD = me[1 + D];
-    const double s = w[0] + w[1] * me[1] + w[2] * me[2] + w[3] * me[3] + w[4] * me[5];
-    pb[0] += 0.5 * uD * s;
-#pragma unroll
-    for (int j = 0; j < 3; ++j) pb[1 + j] += 0.5 * w[1 + j] * r * uD;
-    pb[1 + D] += 0.5 * r * s;
-    pb[4] += 0.5 * w[1 + D];
-    pb[5] += 0.5 * w[4] * r * uD;
+    // d1 F# = (1/2) dF(a)/da; F = (rho u_D, rho u_D u + p e_D, rho h u_D): only
+    // the sums of w are needed; they are kept in pb[0..3], pb[5] (w_0..w_4 order
+    // 0, 1, 2, 3, 5) by direction
+    S.pb[0] += w[0];
+    S.pb[1] += w[1];
+    S.pb[2] += w[2];
+    S.pb[3] += w[3];
+    S.pb[5] += w[4];
     return;
   }
-  const double rm = 0.5 * (me[0] + rl);
-  const double um[3] = {0.5 * (me[1] + ul[0]), 0.5 * (me[2] + ul[1]), 0.5 * (me[3] + ul[2])};
-  const double xm = 0.5 * (me[5] + xl);
-  const double fr = rm * um[D];
-  double wr = w[0] + w[1] * um[0] + w[2] * um[1] + w[3] * um[2] + w[4] * xm;  // total cotangent of f_rho
-  pb[0] += 0.5 * wr * um[D];
+  const double rs = me[0] + rl;
+  const double us[3] = {me[1] + ul[0], me[2] + ul[1], me[3] + ul[2]};
+  const double xs = me[5] + xl;
+  const double T = fma(w[4], xs, fma(w[3], us[2], fma(w[2], us[1], fma(w[1], us[0], w[0] + w[0]))));
+  const double a = rs * us[D];
+  S.pb[0] = fma(us[D], T, S.pb[0]);
 #pragma unroll
-  for (int j = 0; j < 3; ++j) pb[1 + j] += 0.5 * w[1 + j] * fr;
-  pb[1 + D] += 0.5 * wr * rm;
-  pb[4] += 0.5 * w[1 + D];
-  pb[5] += 0.5 * w[4] * fr;
+  for (int j = 0; j < 3; ++j) S.pb[1 + j] = fma(w[1 + j], a, S.pb[1 + j]);
+  S.pb[1 + D] = fma(rs, T, S.pb[1 + D]);
+  S.pb[4] += w[1 + D];
+  S.pb[5] = fma(w[4], a, S.pb[5]);
   if (VF == VF_KG) {  // + p_m u_m,D in the energy flux
-    const double pm = 0.5 * (me[4] + pl);
-    pb[4] += 0.5 * w[4] * um[D];
-    pb[1 + D] += 0.5 * w[4] * pm;
+    S.pe = fma(w[4], us[D], S.pe);
+    S.ue[D] = fma(w[4], me[4] + pl, S.ue[D]);
+  }
+}
+
+// Adds one direction of the STD flux to pb: its sums of w times dF/da / 2.
+template <int D>
+__device__ __forceinline__ void std_vjp(const double me[7], const VolumeVjp& S, double pb[6]) {
+  const double r = me[0], uD = me[1 + D];
+  const double s = S.pb[0] + S.pb[1] * me[1] + S.pb[2] * me[2] + S.pb[3] * me[3] + S.pb[5] * me[5];
+  pb[0] += 0.5 * uD * s;
+#pragma unroll
+  for (int j = 0; j < 3; ++j) pb[1 + j] += 0.5 * S.pb[1 + j] * r * uD;
+  pb[1 + D] += 0.5 * r * s;
+  pb[4] += 0.5 * S.pb[1 + D];
+  pb[5] += 0.5 * S.pb[5] * r * uD;
+}
+
+template <int VF>
+__device__ __forceinline__ void vjp_volume_scale(const VolumeVjp& S, double pb[6]) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) pb[j] = 0.125 * S.pb[j];
+  pb[4] = 0.5 * S.pb[4];
+  pb[5] = 0.125 * S.pb[5];
+  if (VF == VF_KG) {
+    pb[4] = fma(0.25, S.pe, pb[4]);
+#pragma unroll
+    for (int j = 0; j < 3; ++j) pb[1 + j] = fma(0.25, S.ue[j], pb[1 + j]);
   }
 }
 
 template <int VF, int D>
 __device__ __forceinline__ void volume_vjp_dir(const double (*sP)[nn], const double (*sLam)[nn], const double* sDhat,
                                                int n, int id, const double me[7], const double lam[5], double invJ,
-                                               double pb[6]) {
+                                               VolumeVjp& S) {
   constexpr int st = D == 0 ? 1 : (D == 1 ? n1 : nf);
   const int base = n - id * st;
 #pragma unroll 1
@@ -2602,8 +2618,30 @@ __device__ __forceinline__ void volume_vjp_dir(const double (*sP)[nn], const dou
 #pragma unroll
     for (int v = 0; v < 5; ++v) w[v] = fma(c1, lam[v], c2 * sLam[v][m]);
     const double ul[3] = {sP[1][m], sP[2][m], sP[3][m]};
-    twopoint_vjp<VF, D>(me, sP[0][m], ul, sP[4][m], sP[5][m], w, pb);
+    twopoint_vjp<VF, D>(me, sP[0][m], ul, sP[4][m], sP[5][m], w, S);
   }
+}
+
+// Cotangent of the node's primitives from the volume integral (adds to pb = 0).
+template <int VF>
+__device__ __forceinline__ void volume_vjp(const VjpArgs& A, const double (*sP)[nn], const double (*sLam)[nn],
+                                           const double* sDhat, int n, const int ijk[3], const double me[7],
+                                           const double lam[5], double pb[6]) {
+  if (VF == VF_STD) {
+    VolumeVjp S0, S1, S2;
+    volume_vjp_dir<VF, 0>(sP, sLam, sDhat, n, ijk[0], me, lam, A.invJ[0], S0);
+    std_vjp<0>(me, S0, pb);
+    volume_vjp_dir<VF, 1>(sP, sLam, sDhat, n, ijk[1], me, lam, A.invJ[1], S1);
+    std_vjp<1>(me, S1, pb);
+    volume_vjp_dir<VF, 2>(sP, sLam, sDhat, n, ijk[2], me, lam, A.invJ[2], S2);
+    std_vjp<2>(me, S2, pb);
+    return;
+  }
+  VolumeVjp S;
+  volume_vjp_dir<VF, 0>(sP, sLam, sDhat, n, ijk[0], me, lam, A.invJ[0], S);
+  volume_vjp_dir<VF, 1>(sP, sLam, sDhat, n, ijk[1], me, lam, A.invJ[1], S);
+  volume_vjp_dir<VF, 2>(sP, sLam, sDhat, n, ijk[2], me, lam, A.invJ[2], S);
+  vjp_volume_scale<VF>(S, pb);
 }
 
 // Main reverse kernel.  Writes U_bar (or U_acc + U_bar when A.Uacc is set).
@@ -2652,17 +2690,12 @@ __global__ __launch_bounds__(NT, WALL || N > 6 ? 1 : 3) void k_vjp(VjpArgs A) {
     ijk[1] = (t / n1) % n1;
     ijk[2] = t / nf;
   }
-  __syncthreads();  // the face items read the basis (swinv)
+  __syncthreads();  // the face items read the basis (swinv) and lambda
   const int wmask = WALL ? vjp_wall_mask(A, e) : 0;
+  const Nbr6 nb6 = uniform_nbr6(A.nbr, e);
 #pragma unroll 1
-  for (int q = t; q < 6 * nf; q += NT) vjp_face_item<VF, WALL>(A, e, q, swinv, sSF, sWx);
-  if (NS) {
-    for (int q = t; q < 6 * nf; q += NT) {
-      if (q < 2 * nf) vjp_face_ns<0>(A, e, q, sQ, sLn, sGn);
-      else if (q < 4 * nf) vjp_face_ns<1>(A, e, q, sQ, sLn, sGn);
-      else vjp_face_ns<2>(A, e, q, sQ, sLn, sGn);
-    }
-  }
+  for (int q = t; q < 6 * nf; q += NT)
+    vjp_face_item<VF, NS, WALL>(A, e, nb6, q, swinv, sLam, sSF, sQ, sLn, sGn, sWx);
   __syncthreads();
 
   // primitive cotangents: rho, u, v, w, p, x (= h or e); theta added below
@@ -2670,9 +2703,7 @@ __global__ __launch_bounds__(NT, WALL || N > 6 ? 1 : 3) void k_vjp(VjpArgs A) {
   double thb = 0.0;
   double gb[3][4];
   if (t < nn) {
-    volume_vjp_dir<VF, 0>(sP, sLam, sDhat, t, ijk[0], me, lam, A.invJ[0], pb);
-    volume_vjp_dir<VF, 1>(sP, sLam, sDhat, t, ijk[1], me, lam, A.invJ[1], pb);
-    volume_vjp_dir<VF, 2>(sP, sLam, sDhat, t, ijk[2], me, lam, A.invJ[2], pb);
+    volume_vjp<VF>(A, sP, sLam, sDhat, t, ijk, me, lam, pb);
     if (A.alpha) {  // blended: the DG advective volume term enters with weight 1 - alpha
       const double wv = 1.0 - A.alpha[e];
 #pragma unroll
