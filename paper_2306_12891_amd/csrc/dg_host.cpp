@@ -201,11 +201,11 @@ struct dg_ctx {
   double wm_uinf = 1.0, wm_mainf = 0.0;
   double* partial = nullptr;
   double* h_partial = nullptr;
-  // reverse mode (allocated on first use): stage states Y_0..Y_4, the
-  // register and state cotangents, and the face buffer of gradient cotangents
+  // reverse mode (allocated on first use): stage states Y_0..Y_4, the pair of
+  // register cotangents, and the face buffer of gradient cotangents
   double* Y[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
   double* Gbar = nullptr;
-  double* Ybar = nullptr;
+  double* Gbar2 = nullptr;  // the other of the pair that the reverse stages alternate
   double* Gbf = nullptr;
   // reverse mode through the blending: U_t^FV - U_t^DG and the cotangent of alpha
   double* Dfd = nullptr;
@@ -269,7 +269,7 @@ void release(dg_ctx* c) {
   if (c->h_partial) hipHostFree(c->h_partial);
   for (double* y : c->Y) hipFree(y);
   hipFree(c->Gbar);
-  hipFree(c->Ybar);
+  hipFree(c->Gbar2);
   hipFree(c->Gbf);
   hipFree(c->Dfd);
   hipFree(c->abar);
@@ -561,7 +561,7 @@ int ensure_reverse_buffers(dg_ctx* c, bool rk, bool stages = true) {
     for (int k = 0; k < 5 && e == hipSuccess && stages; ++k)
       if (!c->Y[k]) e = hipMalloc((void**)&c->Y[k], bytes);
     if (e == hipSuccess && !c->Gbar) e = hipMalloc((void**)&c->Gbar, bytes);
-    if (e == hipSuccess && !c->Ybar) e = hipMalloc((void**)&c->Ybar, bytes);
+    if (e == hipSuccess && !c->Gbar2) e = hipMalloc((void**)&c->Gbar2, bytes);
   }
   if (e != hipSuccess) {
     (void)hipGetLastError();
@@ -574,8 +574,15 @@ int ensure_reverse_buffers(dg_ctx* c, bool rk, bool stages = true) {
 // reverse-mode buffers: the face buffer of gradient cotangents Gbf
 // (Navier-Stokes), and with blending U_t^FV - U_t^DG (Dfd) and the cotangent
 // of alpha (abar).  Every entry of them is written before it is read.
+// next (or its array NULL): the last kernel also writes next.G = next.a lambda +
+// next.b U_bar.
+struct NextCotangent {
+  double* G = nullptr;
+  double a = 0.0, b = 0.0;
+};
+
 int run_vjp_buffers(dg_ctx* c, const double* U, const double* lambda, double* U_bar, const double* Uacc,
-                    double* Gbf, double* Dfd, double* abar) {
+                    double* Gbf, double* Dfd, double* abar, const NextCotangent& next = NextCotangent()) {
   int rc = 0;
   VjpArgs v;
   std::memset(&v, 0, sizeof(v));
@@ -583,6 +590,9 @@ int run_vjp_buffers(dg_ctx* c, const double* U, const double* lambda, double* U_
   v.Lbar = lambda;
   v.Ubar = U_bar;
   v.Uacc = Uacc;
+  v.Gnext = next.G;
+  v.ga = next.a;
+  v.gb = next.b;
   v.nbr = c->nbr;
   v.basis = c->basis;
   v.Gbf = Gbf;
@@ -653,10 +663,11 @@ int run_vjp_buffers(dg_ctx* c, const double* U, const double* lambda, double* U_
 
 // U_bar = [Uacc +] (dL/dU)^T lambda with the context's reverse-mode buffers
 // (allocated on first use).
-int run_vjp(dg_ctx* c, const double* U, const double* lambda, double* U_bar, const double* Uacc) {
+int run_vjp(dg_ctx* c, const double* U, const double* lambda, double* U_bar, const double* Uacc,
+            const NextCotangent& next = NextCotangent()) {
   const int rc = ensure_reverse_buffers(c, false);
   if (rc) return rc;
-  return run_vjp_buffers(c, U, lambda, U_bar, Uacc, c->Gbf, c->Dfd, c->abar);
+  return run_vjp_buffers(c, U, lambda, U_bar, Uacc, c->Gbf, c->Dfd, c->abar, next);
 }
 
 // Structured periodic neighbour table of the context's mesh.
@@ -1089,21 +1100,32 @@ namespace {
 bool overlaps(const double* a, size_t na, const double* b, size_t nb) { return a < b + nb && b < a + na; }
 
 // Reverse 2N-storage recurrence over the stage states Ys[0..4] of one step:
-//   Gbar <- A_{k+1} Gbar + B_k dt Ybar,  Ybar <- Ybar + VJP(Y_k, Gbar), k = 4..0.
+//   Gbar <- A_{k+1} Gbar + B_k dt Ybar,  Ybar <- Ybar + VJP(Y_k, Gbar), k = 4..0,
+// with Ybar in U_bar_n; each reverse product also writes the next Gbar, into
+// the other of two arrays.
 int rk_reverse(dg_ctx* c, const double* const Ys[5], double dt, const double* U_bar_np1, double* U_bar_n,
                const char* where) {
-  const size_t bytes = c->nstate * sizeof(double);
-  hipError_t e = hipMemcpyAsync(c->Ybar, U_bar_np1, bytes, hipMemcpyDeviceToDevice, c->stream);
+  hipError_t e = hipSuccess;
+  if (U_bar_n != U_bar_np1 && overlaps(U_bar_n, c->nstate, U_bar_np1, c->nstate)) {
+    const size_t bytes = c->nstate * sizeof(double);
+    e = hipMemcpyAsync(c->Gbar2, U_bar_np1, bytes, hipMemcpyDeviceToDevice, c->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(U_bar_n, c->Gbar2, bytes, hipMemcpyDeviceToDevice, c->stream);
+    U_bar_np1 = U_bar_n;
+  }
+  double *G = c->Gbar, *other = c->Gbar2;
+  if (e == hipSuccess) e = c->kt->axpby(G, 0.0, U_bar_np1, kB[4] * dt, c->nstate, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, where);
   for (int k = 4; k >= 0; --k) {
-    const double a = (k == 4) ? 0.0 : kA[k + 1];
-    e = c->kt->axpby(c->Gbar, a, c->Ybar, kB[k] * dt, c->nstate, c->stream);
-    if (e != hipSuccess) return hip_fail(c, e, where);
-    const int rc = run_vjp(c, Ys[k], c->Gbar, c->Ybar, c->Ybar);
+    NextCotangent next;
+    if (k > 0) {
+      next.G = other;
+      next.a = kA[k];
+      next.b = kB[k - 1] * dt;
+    }
+    const int rc = run_vjp(c, Ys[k], G, U_bar_n, k == 4 ? U_bar_np1 : U_bar_n, next);
     if (rc) return rc;
+    std::swap(G, other);
   }
-  e = hipMemcpyAsync(U_bar_n, c->Ybar, bytes, hipMemcpyDeviceToDevice, c->stream);
-  if (e != hipSuccess) return hip_fail(c, e, where);
   return DG_OK;
 }
 

@@ -100,6 +100,9 @@ struct VjpArgs {
   const double* Lbar;   // cotangent of U_t (lambda)
   double* Ubar;         // output: (dL/dU)^T lambda, or Uacc + that
   const double* Uacc;   // optional: accumulate into this array (may alias Ubar)
+  // optional (vjp kernels): Gnext = ga Lbar + gb Ubar, the next stage's cotangent
+  double* Gnext;
+  double ga, gb;
   const int32_t* nbr;
   const double* basis;
   double* Gbf;          // NS: [nelem][6][4][nf] cotangent of the normal lifted gradient at own face nodes

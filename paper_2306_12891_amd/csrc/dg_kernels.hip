@@ -2836,7 +2836,13 @@ __global__ __launch_bounds__(NT, WALL || N > 6 ? 1 : 3) void k_vjp(VjpArgs A) {
     }
     const size_t o = (size_t)e * 5 * nn + t;
 #pragma unroll
-    for (int v = 0; v < 5; ++v) A.Ubar[o + v * nn] = A.Uacc ? A.Uacc[o + v * nn] + out[v] : out[v];
+    for (int v = 0; v < 5; ++v) {
+      const double ub = A.Uacc ? A.Uacc[o + v * nn] + out[v] : out[v];
+      A.Ubar[o + v * nn] = ub;
+      // the next reverse stage's cotangent of U_t, into another array (the
+      // neighbours still read this one); a separate pass would read both again
+      if (A.Gnext) A.Gnext[o + v * nn] = A.ga * A.Lbar[o + v * nn] + A.gb * ub;
+    }
   }
 }
 
@@ -4605,7 +4611,13 @@ __global__ __launch_bounds__(NT) void k_vjp_curved(VjpArgs A) {
     }
     const size_t o = (size_t)e * 5 * nn + t;
 #pragma unroll
-    for (int v = 0; v < 5; ++v) A.Ubar[o + v * nn] = A.Uacc ? A.Uacc[o + v * nn] + out[v] : out[v];
+    for (int v = 0; v < 5; ++v) {
+      const double ub = A.Uacc ? A.Uacc[o + v * nn] + out[v] : out[v];
+      A.Ubar[o + v * nn] = ub;
+      // the next reverse stage's cotangent of U_t, into another array (the
+      // neighbours still read this one); a separate pass would read both again
+      if (A.Gnext) A.Gnext[o + v * nn] = A.ga * A.Lbar[o + v * nn] + A.gb * ub;
+    }
   }
 }
 
