@@ -2533,15 +2533,18 @@ __global__ __launch_bounds__(NT) void k_vjp_lift_les(VjpArgs A) {
 }
 
 // Hand-derived reverse mode of the two-point volume flux with respect to its
-// first argument, in primitive variables (rho, u, p, x), for the flux
-// cotangent w (unrotated components).  x = h (PI, STD) or e (KG).  With the
-// sums s = a + b of the two nodes' values F_rho = r_s u_Ds / 4, F_m = F_rho u_s / 2
-// + p_s e_D / 2, F_E = F_rho x_s / 2 (+ p_s u_Ds / 4 for KG), so with T = 2 w_0 +
-// w_m . u_s + w_4 x_s the cotangents are
-//   rho: u_Ds T / 8, u: w_m r_s u_Ds / 8 + e_D r_s T / 8, p: w_D / 2,
-//   x: w_4 r_s u_Ds / 8  (KG: p += w_4 u_Ds / 4, u_D += w_4 p_s / 4).
-// The sums over the partners are formed without the factors 1/8, 1/2 and 1/4
-// (pb[0..3], pb[5]; pp; pe, ue), which vjp_volume_scale applies once.
+// first argument, in primitive variables (rho, u, p, x).  x = h (PI, STD) or e
+// (KG).  The flux between nodes i and l of a line has the cotangent
+//   w = -(2/dx) (Dhat_il lambda_i + Dhat_li lambda_l) = -(2/dx) W_i Dhat_il (mu_i - mu_l),
+// mu = lambda / W with the node's weight W = w_i w_j w_k, since w_i Dhat_il is
+// skew: one difference per component and one coefficient.  With z = mu_i - mu_l,
+// c = (2/dx) Dhat_il and the sums s = a + b of the two nodes' values F_rho =
+// r_s u_Ds / 4, F_m = F_rho u_s / 2 + p_s e_D / 2, F_E = F_rho x_s / 2 (+ p_s u_Ds / 4
+// for KG), so with T = 2 z_0 + z_m . u_s + z_4 x_s the cotangents are -W_i c times
+//   rho: u_Ds T / 8, u: z_m r_s u_Ds / 8 + e_D r_s T / 8, p: z_D / 2,
+//   x: z_4 r_s u_Ds / 8  (KG: p += z_4 u_Ds / 4, u_D += z_4 p_s / 4).
+// The sums over the partners are formed without -W_i and the factors 1/8, 1/2
+// and 1/4 (pb[0..3], pb[5]; pb[4]; pe, ue), which vjp_volume_scale applies once.
 struct VolumeVjp {
   double pb[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};  // rho, u, v, w, p (factor 1/2), x
   double pe = 0.0, ue[3] = {0.0, 0.0, 0.0};       // KG: factor 1/4
@@ -2549,99 +2552,183 @@ struct VolumeVjp {
 
 template <int VF, int D>
 __device__ __forceinline__ void twopoint_vjp(const double me[7], double rl, const double ul[3], double pl,
-                                             double xl, const double w[5], VolumeVjp& S) {
+                                             double xl, const double z[5], double c, VolumeVjp& S) {
   if (VF == VF_STD) {
     // d1 F# = (1/2) dF(a)/da; F = (rho u_D, rho u_D u + p e_D, rho h u_D): only
-    // the sums of w are needed; they are kept in pb[0..3], pb[5] (w_0..w_4 order
-    // 0, 1, 2, 3, 5) by direction
-    S.pb[0] += w[0];
-    S.pb[1] += w[1];
-    S.pb[2] += w[2];
-    S.pb[3] += w[3];
-    S.pb[5] += w[4];
+    // the sums of c z are needed; they are kept in pb[0..3], pb[5] (z_0..z_4
+    // order 0, 1, 2, 3, 5) by direction
+    S.pb[0] = fma(c, z[0], S.pb[0]);
+    S.pb[1] = fma(c, z[1], S.pb[1]);
+    S.pb[2] = fma(c, z[2], S.pb[2]);
+    S.pb[3] = fma(c, z[3], S.pb[3]);
+    S.pb[5] = fma(c, z[4], S.pb[5]);
     return;
   }
   const double rs = me[0] + rl;
   const double us[3] = {me[1] + ul[0], me[2] + ul[1], me[3] + ul[2]};
   const double xs = me[5] + xl;
-  const double T = fma(w[4], xs, fma(w[3], us[2], fma(w[2], us[1], fma(w[1], us[0], w[0] + w[0]))));
-  const double a = rs * us[D];
-  S.pb[0] = fma(us[D], T, S.pb[0]);
+  const double T = fma(z[4], xs, fma(z[3], us[2], fma(z[2], us[1], fma(z[1], us[0], z[0] + z[0]))));
+  const double cu = c * us[D], cr = c * rs, a = cr * us[D];
+  S.pb[0] = fma(cu, T, S.pb[0]);
 #pragma unroll
-  for (int j = 0; j < 3; ++j) S.pb[1 + j] = fma(w[1 + j], a, S.pb[1 + j]);
-  S.pb[1 + D] = fma(rs, T, S.pb[1 + D]);
-  S.pb[4] += w[1 + D];
-  S.pb[5] = fma(w[4], a, S.pb[5]);
+  for (int j = 0; j < 3; ++j) S.pb[1 + j] = fma(z[1 + j], a, S.pb[1 + j]);
+  S.pb[1 + D] = fma(cr, T, S.pb[1 + D]);
+  S.pb[4] = fma(c, z[1 + D], S.pb[4]);
+  S.pb[5] = fma(z[4], a, S.pb[5]);
   if (VF == VF_KG) {  // + p_m u_m,D in the energy flux
-    S.pe = fma(w[4], us[D], S.pe);
-    S.ue[D] = fma(w[4], me[4] + pl, S.ue[D]);
+    S.pe = fma(z[4], cu, S.pe);
+    S.ue[D] = fma(c * z[4], me[4] + pl, S.ue[D]);
   }
 }
 
-// Adds one direction of the STD flux to pb: its sums of w times dF/da / 2.
+// Adds one direction of the STD flux to pb: its sums times -W dF/da / 2 (k = -W).
 template <int D>
-__device__ __forceinline__ void std_vjp(const double me[7], const VolumeVjp& S, double pb[6]) {
-  const double r = me[0], uD = me[1 + D];
+__device__ __forceinline__ void std_vjp(const double me[7], const VolumeVjp& S, double k, double pb[6]) {
+  const double r = me[0], uD = me[1 + D], h = 0.5 * k;
   const double s = S.pb[0] + S.pb[1] * me[1] + S.pb[2] * me[2] + S.pb[3] * me[3] + S.pb[5] * me[5];
-  pb[0] += 0.5 * uD * s;
+  pb[0] += h * uD * s;
 #pragma unroll
-  for (int j = 0; j < 3; ++j) pb[1 + j] += 0.5 * S.pb[1 + j] * r * uD;
-  pb[1 + D] += 0.5 * r * s;
-  pb[4] += 0.5 * S.pb[1 + D];
-  pb[5] += 0.5 * S.pb[5] * r * uD;
+  for (int j = 0; j < 3; ++j) pb[1 + j] += h * S.pb[1 + j] * r * uD;
+  pb[1 + D] += h * r * s;
+  pb[4] += h * S.pb[1 + D];
+  pb[5] += h * S.pb[5] * r * uD;
 }
 
 template <int VF>
-__device__ __forceinline__ void vjp_volume_scale(const VolumeVjp& S, double pb[6]) {
+__device__ __forceinline__ void vjp_volume_scale(const VolumeVjp& S, double k, double pb[6]) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) pb[j] = 0.125 * S.pb[j];
-  pb[4] = 0.5 * S.pb[4];
-  pb[5] = 0.125 * S.pb[5];
+  for (int j = 0; j < 4; ++j) pb[j] = 0.125 * k * S.pb[j];
+  pb[4] = 0.5 * k * S.pb[4];
+  pb[5] = 0.125 * k * S.pb[5];
   if (VF == VF_KG) {
-    pb[4] = fma(0.25, S.pe, pb[4]);
+    pb[4] = fma(0.25 * k, S.pe, pb[4]);
 #pragma unroll
-    for (int j = 0; j < 3; ++j) pb[1 + j] = fma(0.25, S.ue[j], pb[1 + j]);
+    for (int j = 0; j < 3; ++j) pb[1 + j] = fma(0.25 * k, S.ue[j], pb[1 + j]);
   }
 }
 
-template <int VF, int D>
-__device__ __forceinline__ void volume_vjp_dir(const double (*sP)[nn], const double (*sLam)[nn], const double* sDhat,
-                                               int n, int id, const double me[7], const double lam[5], double invJ,
-                                               VolumeVjp& S) {
+// One direction of the reverse volume sums.  sN: the nodes' primitives (rows 0
+// to 6) and mu = lambda / W (rows 7 to 11).  Navier-Stokes: the same partner values and
+// coefficients also give sum_l Dhat_il mu_l (momentum, energy; lv) for the
+// viscous-flux cotangent and sum_l Dhat_il q_l (gq) for the forward gradient.
+template <int VF, int D, bool NS>
+__device__ __forceinline__ void reverse_dir(const double (*sN)[nn], const double* sDhat, int n, int id,
+                                            const double me[7], const double mu[5], double invJ, VolumeVjp& S,
+                                            double lv[4], double gq[4]) {
   constexpr int st = D == 0 ? 1 : (D == 1 ? n1 : nf);
-  const int base = n - id * st;
-#pragma unroll 1
-  for (int l = 0; l < n1; ++l) {
-    const int m = base + l * st;
-    const double c1 = -invJ * sDhat[id * n1 + l], c2 = -invJ * sDhat[l * n1 + id];
-    double w[5];
 #pragma unroll
-    for (int v = 0; v < 5; ++v) w[v] = fma(c1, lam[v], c2 * sLam[v][m]);
-    const double ul[3] = {sP[1][m], sP[2][m], sP[3][m]};
-    twopoint_vjp<VF, D>(me, sP[0][m], ul, sP[4][m], sP[5][m], w, S);
+  for (int k = 0; k < 4; ++k) lv[k] = gq[k] = 0.0;
+  auto pair = [&](double ch, int m) {
+    const double ul[3] = {sN[1][m], sN[2][m], sN[3][m]};
+    double z[5];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      const double ml = sN[7 + v][m];
+      if (NS && v > 0) lv[v - 1] = fma(ch, ml, lv[v - 1]);
+      z[v] = mu[v] - ml;
+    }
+    if (NS) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) gq[k] = fma(ch, ul[k], gq[k]);
+      gq[3] = fma(ch, sN[6][m], gq[3]);
+    }
+    twopoint_vjp<VF, D>(me, sN[0][m], ul, sN[4][m], sN[5][m], z, invJ * ch, S);
+  };
+  auto tie = [&](int& k, int& ic) {
+    asm volatile("" : "+v"(k), "+v"(ic), "+v"(S.pb[0]), "+v"(S.pb[1]), "+v"(S.pb[2]), "+v"(S.pb[3]), "+v"(S.pb[5]));
+    if (VF != VF_STD) asm volatile("" : "+v"(k), "+v"(S.pb[4]));
+    if (VF == VF_KG) asm volatile("" : "+v"(k), "+v"(S.pe), "+v"(S.ue[D]));
+    if (NS)
+      asm volatile("" : "+v"(k), "+v"(lv[0]), "+v"(lv[1]), "+v"(lv[2]), "+v"(lv[3]), "+v"(gq[0]), "+v"(gq[1]),
+                   "+v"(gq[2]), "+v"(gq[3]));
+  };
+  partner_loop<true, true, st>(id, n, sDhat, pair, tie);
+}
+
+// Cotangent of the node's primitives from the volume integral (pb), the
+// viscous-flux cotangent Fvb and the lifted gradient g (Navier-Stokes).  With
+// D_li = -(w_i / w_l) D_il off the diagonal and +-1/(2 w) on it (line ends),
+//   sum_l Dw_li lambda_l = -(W_i / 2) sum_{l /= i} Dhat_il mu_l  -+  lambda_i / (2 w)  at the ends;
+// the end term cancels against the own half of the interface term, so that only
+// the neighbour's half is left (at walls, which have no interface term, the end
+// term itself).  Likewise the gradient's end term is +-(q* - q_i / 2) / w.
+template <int VF, bool NS, bool WALL>
+__device__ __forceinline__ void reverse_volume(const VjpArgs& A, const double (*sN)[nn], const double (*sQ)[4][nf],
+                                               const double (*sLn)[4][nf], const double* sDhat, const double* swinv,
+                                               int n, const int ijk[3], const double me[7], const double mu[5],
+                                               double W, int wmask, double pb[6], double Fvb[3][4], double g[3][4]) {
+  VolumeVjp S;
+  reverse_dir<VF, 0, NS>(sN, sDhat, n, ijk[0], me, mu, A.invJ[0], S, Fvb[0], g[0]);
+  if (VF == VF_STD) { std_vjp<0>(me, S, -W, pb); S = VolumeVjp(); }
+  reverse_dir<VF, 1, NS>(sN, sDhat, n, ijk[1], me, mu, A.invJ[1], S, Fvb[1], g[1]);
+  if (VF == VF_STD) { std_vjp<1>(me, S, -W, pb); S = VolumeVjp(); }
+  reverse_dir<VF, 2, NS>(sN, sDhat, n, ijk[2], me, mu, A.invJ[2], S, Fvb[2], g[2]);
+  if (VF == VF_STD) std_vjp<2>(me, S, -W, pb);
+  else vjp_volume_scale<VF>(S, -W, pb);
+  if (!NS) return;
+  const double hW = -0.5 * W;
+  const double qn[4] = {me[1], me[2], me[3], me[6]};
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const int id = ijk[d];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      Fvb[d][c] *= hW;
+      g[d][c] *= 0.5;
+    }
+    if (id == 0 || id == N) {
+      const int f = 2 * d + (id == N);
+      const int a = d == 0 ? ijk[1] + n1 * ijk[2] : (d == 1 ? ijk[0] + n1 * ijk[2] : ijk[0] + n1 * ijk[1]);
+      const double w = id == N ? swinv[N] : -swinv[0];
+      const double wn = id == N ? -0.5 * swinv[0] : 0.5 * swinv[N];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        g[d][c] = fma(w, fma(-0.5, qn[c], sQ[f][c][a]), g[d][c]);
+        if (WALL && ((wmask >> f) & 1)) Fvb[d][c] = fma(-0.5 * w * W, mu[1 + c], Fvb[d][c]);
+        else Fvb[d][c] = fma(wn, sLn[f][c][a], Fvb[d][c]);
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      Fvb[d][c] *= A.invJ[d];
+      g[d][c] *= A.invJ[d];
+    }
   }
 }
 
-// Cotangent of the node's primitives from the volume integral (adds to pb = 0).
-template <int VF>
-__device__ __forceinline__ void volume_vjp(const VjpArgs& A, const double (*sP)[nn], const double (*sLam)[nn],
-                                           const double* sDhat, int n, const int ijk[3], const double me[7],
-                                           const double lam[5], double pb[6]) {
-  if (VF == VF_STD) {
-    VolumeVjp S0, S1, S2;
-    volume_vjp_dir<VF, 0>(sP, sLam, sDhat, n, ijk[0], me, lam, A.invJ[0], S0);
-    std_vjp<0>(me, S0, pb);
-    volume_vjp_dir<VF, 1>(sP, sLam, sDhat, n, ijk[1], me, lam, A.invJ[1], S1);
-    std_vjp<1>(me, S1, pb);
-    volume_vjp_dir<VF, 2>(sP, sLam, sDhat, n, ijk[2], me, lam, A.invJ[2], S2);
-    std_vjp<2>(me, S2, pb);
-    return;
+// q_bar along direction D (without 2/dx): Dw^T of the gradient cotangent and
+// the interface terms, from nu = gb / W in LDS, as above.  Interface value
+// q* = (q + q_nb)/2; at a wall (q + M q)/2, M the mirror (normal velocity
+// reversed).
+template <int D, bool WALL>
+__device__ __forceinline__ void gradient_transpose_dir(const double (*sX)[nn], const double (*sGn)[4][nf],
+                                                       const double* sDhat, const double* swinv, int n,
+                                                       const int ijk[3], double W, int wmask, double s[4]) {
+  constexpr int st = D == 0 ? 1 : (D == 1 ? n1 : nf);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) s[c] = 0.0;
+  auto pair = [&](double ch, int m) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) s[c] = fma(ch, sX[4 * D + c][m], s[c]);
+  };
+  auto tie = [&](int& k, int& ic) { asm volatile("" : "+v"(k), "+v"(ic), "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3])); };
+  partner_loop<true, true, st>(ijk[D], n, sDhat, pair, tie);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) s[c] *= -0.5 * W;
+  if (ijk[D] == 0 || ijk[D] == N) {
+    const bool hi = ijk[D] == N;
+    const int f = 2 * D + hi;
+    const int a = D == 0 ? ijk[1] + n1 * ijk[2] : (D == 1 ? ijk[0] + n1 * ijk[2] : ijk[0] + n1 * ijk[1]);
+    if (WALL && ((wmask >> f) & 1)) {
+      const double w = 0.5 * W * (hi ? swinv[N] : -swinv[0]);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) s[c] = fma(c == D ? -w : w, sX[4 * D + c][n], s[c]);
+    } else {
+      const double wn = hi ? -0.5 * swinv[0] : 0.5 * swinv[N];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) s[c] = fma(wn, sGn[f][c][a], s[c]);
+    }
   }
-  VolumeVjp S;
-  volume_vjp_dir<VF, 0>(sP, sLam, sDhat, n, ijk[0], me, lam, A.invJ[0], S);
-  volume_vjp_dir<VF, 1>(sP, sLam, sDhat, n, ijk[1], me, lam, A.invJ[1], S);
-  volume_vjp_dir<VF, 2>(sP, sLam, sDhat, n, ijk[2], me, lam, A.invJ[2], S);
-  vjp_volume_scale<VF>(S, pb);
 }
 
 // Main reverse kernel.  Writes U_bar (or U_acc + U_bar when A.Uacc is set).
@@ -2657,8 +2744,7 @@ __global__ __launch_bounds__(NT, WALL || N > 6 ? 1 : 3) void k_vjp(VjpArgs A) {
   static_assert(!WALL || EQ >= 1, "walls: Navier-Stokes");
   __shared__ double sWx[WALL ? 2 : 1][4][nf];
   __shared__ double sB[NB_STAGE];
-  __shared__ double sP[7][nn];
-  __shared__ double sLam[5][nn];
+  __shared__ double sN[12][nn];  // primitives and lambda, then lambda / W; last the gradient cotangents
   __shared__ double sSF[6][5][nf];
   __shared__ double sQ[NS ? 6 : 1][4][nf];
   __shared__ double sLn[NS ? 6 : 1][4][nf];
@@ -2667,12 +2753,11 @@ __global__ __launch_bounds__(NT, WALL || N > 6 ? 1 : 3) void k_vjp(VjpArgs A) {
   if (e >= A.nelem) return;
   const int t = threadIdx.x;
   const double gm1 = A.gamma - 1.0;
-  for (int q = t; q < NB_STAGE; q += NT) sB[q] = A.basis[q];
+  for (int q = t; q < NB_STAGE; q += NT) sB[q] = A.basis[q < nf ? dhat_index(q) : q];
   const double* sDhat = sB + BL.Dhat();
-  const double* sDw = sB + BL.Dw();
   const double* swinv = sB + BL.winv();
   const Ref ref{0.0, 0.0, 0.0};
-  double u[5], me[7], lam[5];
+  double u[5], me[7], mu[5];
   int ijk[3] = {0, 0, 0};
   if (t < nn) {
     const double* Ue = A.U + (size_t)e * 5 * nn;
@@ -2680,12 +2765,12 @@ __global__ __launch_bounds__(NT, WALL || N > 6 ? 1 : 3) void k_vjp(VjpArgs A) {
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
       u[v] = Ue[v * nn + t];
-      lam[v] = Le[v * nn + t];
-      sLam[v][t] = lam[v];
+      mu[v] = Le[v * nn + t];
+      sN[7 + v][t] = mu[v];
     }
     primitives<VF, double, false>(u, gm1, ref, me);
 #pragma unroll
-    for (int k = 0; k < 7; ++k) sP[k][t] = me[k];
+    for (int k = 0; k < 7; ++k) sN[k][t] = me[k];
     ijk[0] = t % n1;
     ijk[1] = (t / n1) % n1;
     ijk[2] = t / nf;
@@ -2695,7 +2780,16 @@ __global__ __launch_bounds__(NT, WALL || N > 6 ? 1 : 3) void k_vjp(VjpArgs A) {
   const Nbr6 nb6 = uniform_nbr6(A.nbr, e);
 #pragma unroll 1
   for (int q = t; q < 6 * nf; q += NT)
-    vjp_face_item<VF, NS, WALL>(A, e, nb6, q, swinv, sLam, sSF, sQ, sLn, sGn, sWx);
+    vjp_face_item<VF, NS, WALL>(A, e, nb6, q, swinv, sN + 7, sSF, sQ, sLn, sGn, sWx);
+  const double iW = swinv[ijk[0]] * swinv[ijk[1]] * swinv[ijk[2]], W = rcp64(iW);
+  __syncthreads();
+  if (t < nn) {
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      mu[v] *= iW;
+      sN[7 + v][t] = mu[v];
+    }
+  }
   __syncthreads();
 
   // primitive cotangents: rho, u, v, w, p, x (= h or e); theta added below
@@ -2703,16 +2797,14 @@ __global__ __launch_bounds__(NT, WALL || N > 6 ? 1 : 3) void k_vjp(VjpArgs A) {
   double thb = 0.0;
   double gb[3][4];
   if (t < nn) {
-    volume_vjp<VF>(A, sP, sLam, sDhat, t, ijk, me, lam, pb);
+    double Fvb[3][4], g[3][4];
+    reverse_volume<VF, NS, WALL>(A, sN, sQ, sLn, sDhat, swinv, t, ijk, me, mu, W, wmask, pb, Fvb, g);
     if (A.alpha) {  // blended: the DG advective volume term enters with weight 1 - alpha
       const double wv = 1.0 - A.alpha[e];
 #pragma unroll
       for (int i = 0; i < 6; ++i) pb[i] *= wv;
     }
     if (NS) {
-      double Fvb[3][4], g[3][4];
-      viscous_flux_cotangent(sLam, sLn, sDw, swinv, t, ijk, A.invJ, Fvb, wmask);
-      lifted_gradient<double>(sP, sQ, sDw, swinv, t, ijk, A.invJ, g);
       const double csd2 = LES ? vjp_csd2(A, e) : 0.0;
       const double mue = LES ? A.mu + eddy_viscosity<double>(g, me[0], csd2) : A.mu;
       // u enters the energy flux u . tau_d
@@ -2734,53 +2826,31 @@ __global__ __launch_bounds__(NT, WALL || N > 6 ? 1 : 3) void k_vjp(VjpArgs A) {
   }
   if (NS) {
     // q_bar = sum_d' (2/dx_d') [ Dw^T gb_d' along the d' line + interface terms ]
-    double (*sX)[nn] = sLam;  // lambda is no longer needed
+    __syncthreads();  // primitives and lambda read
+    if (t < nn) {
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      __syncthreads();
-      if (t < nn) {
+      for (int d = 0; d < 3; ++d)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) sX[c][t] = gb[d][c];
-      }
-      __syncthreads();
-      if (t < nn) {
-        const int st = d == 0 ? 1 : (d == 1 ? n1 : nf);
-        const int id = ijk[d];
-        const int base = t - id * st;
-        const int a = d == 0 ? ijk[1] + n1 * ijk[2] : (d == 1 ? ijk[0] + n1 * ijk[2] : ijk[0] + n1 * ijk[1]);
-        double s[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int l = 0; l < n1; ++l) {
-          const double c = sDw[l * n1 + id];
-          const int k = base + l * st;
-#pragma unroll
-          for (int cc = 0; cc < 4; ++cc) s[cc] = fma(c, sX[cc][k], s[cc]);
-        }
-        // interface value q* = (q + q_nb)/2; at a wall (q + M q)/2, M the
-        // mirror (normal velocity reversed)
-        if (id == N) {
-          if (WALL && ((wmask >> (2 * d + 1)) & 1)) {
-#pragma unroll
-            for (int cc = 0; cc < 4; ++cc) s[cc] += cc == d ? 0.0 : swinv[N] * gb[d][cc];
-          } else {
-#pragma unroll
-            for (int cc = 0; cc < 4; ++cc) s[cc] += 0.5 * (swinv[N] * gb[d][cc] - swinv[0] * sGn[2 * d + 1][cc][a]);
-          }
-        }
-        if (id == 0) {
-          if (WALL && ((wmask >> (2 * d)) & 1)) {
-#pragma unroll
-            for (int cc = 0; cc < 4; ++cc) s[cc] -= cc == d ? 0.0 : swinv[0] * gb[d][cc];
-          } else {
-#pragma unroll
-            for (int cc = 0; cc < 4; ++cc) s[cc] += 0.5 * (swinv[N] * sGn[2 * d][cc][a] - swinv[0] * gb[d][cc]);
-          }
-        }
-        pb[1] += A.invJ[d] * s[0];
-        pb[2] += A.invJ[d] * s[1];
-        pb[3] += A.invJ[d] * s[2];
-        thb += A.invJ[d] * s[3];
-      }
+        for (int c = 0; c < 4; ++c) sN[4 * d + c][t] = gb[d][c] * iW;
+    }
+    __syncthreads();
+    if (t < nn) {
+      double s[4];
+      gradient_transpose_dir<0, WALL>(sN, sGn, sDhat, swinv, t, ijk, W, wmask, s);
+      pb[1] = fma(A.invJ[0], s[0], pb[1]);
+      pb[2] = fma(A.invJ[0], s[1], pb[2]);
+      pb[3] = fma(A.invJ[0], s[2], pb[3]);
+      thb = A.invJ[0] * s[3];
+      gradient_transpose_dir<1, WALL>(sN, sGn, sDhat, swinv, t, ijk, W, wmask, s);
+      pb[1] = fma(A.invJ[1], s[0], pb[1]);
+      pb[2] = fma(A.invJ[1], s[1], pb[2]);
+      pb[3] = fma(A.invJ[1], s[2], pb[3]);
+      thb = fma(A.invJ[1], s[3], thb);
+      gradient_transpose_dir<2, WALL>(sN, sGn, sDhat, swinv, t, ijk, W, wmask, s);
+      pb[1] = fma(A.invJ[2], s[0], pb[1]);
+      pb[2] = fma(A.invJ[2], s[1], pb[2]);
+      pb[3] = fma(A.invJ[2], s[2], pb[3]);
+      thb = fma(A.invJ[2], s[3], thb);
     }
   }
   if (t < nn) {
