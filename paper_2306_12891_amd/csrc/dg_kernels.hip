@@ -53,6 +53,9 @@ constexpr int n1 = N + 1;
 constexpr int nn = n1 * n1 * n1;
 constexpr int nf = n1 * n1;
 constexpr int NT = ((nn + 63) / 64) * 64;
+// k_vjp: a thread for each node and each face item (at N = 3 and 4 the faces
+// have more)
+constexpr int NTV = ((std::max(nn, 6 * nf) + 63) / 64) * 64;
 // Row stride of the stage kernel's node arrays in LDS: a multiple of 64
 // doubles (N >= 3), so that one base address reaches every row through the
 // 512-byte offset units of paired LDS reads.
@@ -2377,7 +2380,10 @@ __global__ __launch_bounds__(NT) void k_vjp_lift(VjpArgs A) {
 // state, (d f*/d U_own)^T fbar with fbar = -(2/dx_d)(lambda_- / w_N -
 // lambda_+ / w_0), by the reverse sweep of the interface flux (riemann_vjp).
 // One code path for all directions: states and cotangent are rotated by
-// address (normal component first).
+// address (normal component first).  And one for both sides: where the own
+// state is the plus one, both states are mirrored (normal momentum reversed),
+// f*(U-, U+) = -M f*(M U+, M U-), so the own state is always the first argument
+// and the compiler drops the sweep's other half, the cotangent of the second.
 // At a wall face (WALL, neighbour -1): the interface flux with the mirror
 // state (normal momentum reversed) as the other side, so its cotangent reaches
 // the own state through both arguments; plus the reverse of the wall model's
@@ -2386,79 +2392,84 @@ __global__ __launch_bounds__(NT) void k_vjp_lift(VjpArgs A) {
 // Navier-Stokes: the same loads also give q* (forward gradient, into sQ) and the
 // neighbour's lambda (sLn), and the neighbour's normal-gradient cotangent of
 // pass 1 is read into sGn.  The element's own lambda comes from sLam.
+// The loads (vjp_face_load) are issued before the kernel's first barrier, with
+// those of the node, so that their latencies overlap.
+struct VjpFace {
+  FaceItem it;
+  double own[5], nb[5], ln[5], gn[4];  // states (rotated), the neighbour's lambda and gradient cotangent
+};
+
+template <bool NS, bool WALL>
+__device__ __forceinline__ void vjp_face_load(const VjpArgs& A, int e, const Nbr6& nb6, int q, VjpFace& F) {
+  F.it = face_item_geometry(nb6, q);
+  load_rotated(A.U + (size_t)e * 5 * nn, F.it.nown, F.it, F.own);
+  if (WALL && F.it.nb < 0) return;
+  load_rotated(A.U + (size_t)F.it.nb * 5 * nn, F.it.nnb, F.it, F.nb);
+  load_rotated(A.Lbar + (size_t)F.it.nb * 5 * nn, F.it.nnb, F.it, F.ln);
+  if (NS) {
+    const double* Gn = A.Gbf + ((size_t)F.it.nb * 6 + (F.it.f ^ 1)) * 4 * nf + F.it.a;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) F.gn[c] = Gn[c * nf];
+  }
+}
+
 template <int VF, bool NS, bool WALL>
-__device__ __forceinline__ void vjp_face_item(const VjpArgs& A, int e, const Nbr6& nb6, int q, const double* swinv,
+__device__ __forceinline__ void vjp_face_item(const VjpArgs& A, int e, const VjpFace& F, const double* swinv,
                                               const double (*sLam)[nn], double (*sSF)[5][nf], double (*sQ)[4][nf],
                                               double (*sLn)[4][nf], double (*sGn)[4][nf],
                                               double (*sWx)[4][nf] = nullptr) {
-  const FaceItem it = face_item_geometry(nb6, q);
+  const FaceItem& it = F.it;
   const double invJd = it.d == 0 ? A.invJ[0] : (it.d == 1 ? A.invJ[1] : A.invJ[2]);
   const int row[5] = {0, 1 + it.d, it.k1, it.k2, 4};  // rotated position -> variable
   const bool wall = WALL && it.nb < 0;
-  const double* Ue = A.U + (size_t)e * 5 * nn;
+  const double sg = it.side ? 1.0 : -1.0;  // mirrored where the own state is the plus one
+  const double co = -invJd * (it.side ? swinv[N] : swinv[0]), cn = invJd * (it.side ? swinv[0] : swinv[N]);
   double L[5], R[5], fb[5], Lb[5], Rb[5], lo[5];
-  load_rotated(Ue, it.nown, it, L);  // own, for now
 #pragma unroll
-  for (int r = 0; r < 5; ++r) lo[r] = sLam[row[r]][it.nown];
-  if (wall) {
-    const double cw = it.side ? -invJd * swinv[N] : invJd * swinv[0];
-#pragma unroll
-    for (int r = 0; r < 5; ++r) {
-      R[r] = (r == 1 && it.side) ? -L[r] : L[r];
-      fb[r] = cw * lo[r];
+  for (int r = 0; r < 5; ++r) {
+    lo[r] = sLam[row[r]][it.nown];
+    L[r] = r == 1 ? sg * F.own[r] : F.own[r];
+    if (wall) {
+      R[r] = r == 1 ? -L[r] : L[r];
+      fb[r] = co * lo[r];
+    } else {
+      R[r] = r == 1 ? sg * F.nb[r] : F.nb[r];
+      fb[r] = fma(co, lo[r], cn * F.ln[r]);
     }
-    if (!it.side) L[1] = -L[1];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) sLn[it.f][c][it.a] = sGn[it.f][c][it.a] = 0.0;
-  } else {
-    double ln[5], gn[4];
-    load_rotated(A.U + (size_t)it.nb * 5 * nn, it.nnb, it, R);  // the neighbour's, for now
-    load_rotated(A.Lbar + (size_t)it.nb * 5 * nn, it.nnb, it, ln);
-    if (NS) {
-      const double* Gn = A.Gbf + ((size_t)it.nb * 6 + (it.f ^ 1)) * 4 * nf + it.a;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) gn[c] = Gn[c * nf];
-    }
-    const double cm = -invJd * swinv[N], cp = invJd * swinv[0];
-#pragma unroll
-    for (int r = 0; r < 5; ++r) {
-      fb[r] = it.side ? fma(cm, lo[r], cp * ln[r]) : fma(cm, ln[r], cp * lo[r]);
-      const double o = L[r];
-      L[r] = it.side ? o : R[r];
-      R[r] = it.side ? R[r] : o;
-    }
-    if (NS) {
-      store_q(it, ln + 1, sLn);
-#pragma unroll
-      for (int c = 0; c < 4; ++c) sGn[it.f][c][it.a] = gn[c];
-    }
+    if (r == 1) fb[r] *= sg;
   }
   if (NS) {
+    double ln[4], gn[4], qs[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      ln[c] = wall ? 0.0 : F.ln[1 + c];
+      gn[c] = wall ? 0.0 : F.gn[c];
+    }
+    store_q(it, ln, sLn);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) sGn[it.f][c][it.a] = gn[c];
     const double gm1 = A.gamma - 1.0;
-    double qs[4];
     interface_q<0, double, false>(state64<0>(L, gm1), state64<0>(R, gm1), Ref{0.0, 0.0, 0.0}, qs);
+    qs[0] *= sg;
     store_q(it, qs, sQ);
   }
   riemann_vjp<VF>(A.sf, L, R, A.gamma, fb, Lb, Rb);
   if (wall) {
-    double ob[5];
 #pragma unroll
-    for (int r = 0; r < 5; ++r) ob[r] = (it.side ? Lb[r] : Rb[r]) + (r == 1 ? -1.0 : 1.0) * (it.side ? Rb[r] : Lb[r]);
+    for (int r = 0; r < 5; ++r) Lb[r] += r == 1 ? -Rb[r] : Rb[r];
     const double cv = invJd * (it.side ? swinv[N] : -swinv[0]);
+    const double* Ue = A.U + (size_t)e * 5 * nn;
     double rhowb = 0.0, rxb = 0.0, m1b = 0.0, m2b = 0.0;
     wall_model_flux_vjp(A, L[0], Ue[it.nnb], Ue[it.k1 * nn + it.nnb], Ue[it.k2 * nn + it.nnb],
                         it.side ? -1.0 : 1.0, cv * lo[2], cv * lo[3], rhowb, rxb, m1b, m2b);
-    ob[0] += rhowb;
-#pragma unroll
-    for (int r = 0; r < 5; ++r) sSF[it.f][row[r]][it.a] = ob[r];
+    Lb[0] += rhowb;
     sWx[it.side][0][it.a] = rxb;
     sWx[it.side][1 + it.d][it.a] = 0.0;
     sWx[it.side][it.k1][it.a] = m1b;
     sWx[it.side][it.k2][it.a] = m2b;
-    return;
   }
 #pragma unroll
-  for (int r = 0; r < 5; ++r) sSF[it.f][row[r]][it.a] = it.side ? Lb[r] : Rb[r];
+  for (int r = 0; r < 5; ++r) sSF[it.f][row[r]][it.a] = r == 1 ? sg * Lb[r] : Lb[r];
 }
 
 // Pass 1 with the eddy viscosity: q* and the neighbour's lambda of face item q.
@@ -2738,7 +2749,7 @@ __device__ __forceinline__ void gradient_transpose_dir(const double (*sX)[nn], c
 // kernel faster than two without spills; the wall variants keep their
 // registers, and so does N = 7, where the LDS admits one workgroup per CU.
 template <int VF, int EQ, bool WALL = false>
-__global__ __launch_bounds__(NT, WALL || N > 6 ? 1 : 3) void k_vjp(VjpArgs A) {
+__global__ __launch_bounds__(NTV, WALL || N > 6 ? 1 : 3) void k_vjp(VjpArgs A) {
   constexpr bool NS = (EQ >= 1);
   constexpr bool LES = (EQ == 2);
   static_assert(!WALL || EQ >= 1, "walls: Navier-Stokes");
@@ -2753,40 +2764,46 @@ __global__ __launch_bounds__(NT, WALL || N > 6 ? 1 : 3) void k_vjp(VjpArgs A) {
   if (e >= A.nelem) return;
   const int t = threadIdx.x;
   const double gm1 = A.gamma - 1.0;
-  for (int q = t; q < NB_STAGE; q += NT) sB[q] = A.basis[q < nf ? dhat_index(q) : q];
+  for (int q = t; q < NB_STAGE; q += NTV) sB[q] = A.basis[q < nf ? dhat_index(q) : q];
   const double* sDhat = sB + BL.Dhat();
   const double* swinv = sB + BL.winv();
   const Ref ref{0.0, 0.0, 0.0};
-  double u[5], me[7], mu[5];
-  int ijk[3] = {0, 0, 0};
-  if (t < nn) {
-    const double* Ue = A.U + (size_t)e * 5 * nn;
-    const double* Le = A.Lbar + (size_t)e * 5 * nn;
-#pragma unroll
-    for (int v = 0; v < 5; ++v) {
-      u[v] = Ue[v * nn + t];
-      mu[v] = Le[v * nn + t];
-      sN[7 + v][t] = mu[v];
-    }
-    primitives<VF, double, false>(u, gm1, ref, me);
-#pragma unroll
-    for (int k = 0; k < 7; ++k) sN[k][t] = me[k];
-    ijk[0] = t % n1;
-    ijk[1] = (t / n1) % n1;
-    ijk[2] = t / nf;
-  }
-  __syncthreads();  // the face items read the basis (swinv) and lambda
   const int wmask = WALL ? vjp_wall_mask(A, e) : 0;
   const Nbr6 nb6 = uniform_nbr6(A.nbr, e);
-#pragma unroll 1
-  for (int q = t; q < 6 * nf; q += NT)
-    vjp_face_item<VF, NS, WALL>(A, e, nb6, q, swinv, sN + 7, sSF, sQ, sLn, sGn, sWx);
-  const double iW = swinv[ijk[0]] * swinv[ijk[1]] * swinv[ijk[2]], W = rcp64(iW);
+  const size_t o = (size_t)e * 5 * nn + t;
+  double me[7], mu[5];
+  VjpFace face;
+  {
+    double u[5];
+    if (t < nn) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        u[v] = A.U[o + v * nn];
+        mu[v] = A.Lbar[o + v * nn];
+      }
+    }
+    if (t < 6 * nf) vjp_face_load<NS, WALL>(A, e, nb6, t, face);
+    if (t < nn) {
+      primitives<VF, double, false>(u, gm1, ref, me);
+#pragma unroll
+      for (int k = 0; k < 7; ++k) sN[k][t] = me[k];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) sN[7 + v][t] = mu[v];
+    }
+  }
+  __syncthreads();  // the face items read the basis (swinv) and lambda
+  if (t < 6 * nf) vjp_face_item<VF, NS, WALL>(A, e, face, swinv, sN + 7, sSF, sQ, sLn, sGn, sWx);
+  const int ijk[3] = {t % n1, (t / n1) % n1, t / nf};
+  double iW = 0.0, W = 0.0;
   __syncthreads();
-  if (t < nn) {
+  if (t < nn) {  // the node's values again, not kept through the face items
+    iW = swinv[ijk[0]] * swinv[ijk[1]] * swinv[ijk[2]];
+    W = rcp64(iW);
+#pragma unroll
+    for (int k = 0; k < 7; ++k) me[k] = sN[k][t];
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
-      mu[v] *= iW;
+      mu[v] = sN[7 + v][t] * iW;
       sN[7 + v][t] = mu[v];
     }
   }
@@ -2824,6 +2841,15 @@ __global__ __launch_bounds__(NT, WALL || N > 6 ? 1 : 3) void k_vjp(VjpArgs A) {
       else gradient_cotangent(Fvb, uu, A.mu, A.kappa, gb);
     }
   }
+  // loaded here for the end of the kernel
+  double acc[5], lam[5];
+  if (t < nn) {
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      if (A.Uacc) acc[v] = A.Uacc[o + v * nn];
+      if (A.Gnext) lam[v] = A.Lbar[o + v * nn];
+    }
+  }
   if (NS) {
     // q_bar = sum_d' (2/dx_d') [ Dw^T gb_d' along the d' line + interface terms ]
     __syncthreads();  // primitives and lambda read
@@ -2856,7 +2882,7 @@ __global__ __launch_bounds__(NT, WALL || N > 6 ? 1 : 3) void k_vjp(VjpArgs A) {
   if (t < nn) {
     // primitive cotangents -> conservative: u = m/rho, p = (g-1)(E - |m|^2/(2 rho)),
     // x = h = (E + p)/rho (PI, STD) or e = E/rho (KG), theta = p/rho
-    const double ir = rcp64(u[0]);
+    const double ir = rcp64(me[0]);
     double rb = pb[0], ub[3] = {pb[1], pb[2], pb[3]}, pbar = pb[4], Eb = 0.0;
     if (VF == VF_KG) {
       Eb += pb[5] * ir;
@@ -2904,14 +2930,13 @@ __global__ __launch_bounds__(NT, WALL || N > 6 ? 1 : 3) void k_vjp(VjpArgs A) {
           for (int v = 0; v < 4; ++v) out[v] += sWx[0][v][a];
       }
     }
-    const size_t o = (size_t)e * 5 * nn + t;
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
-      const double ub = A.Uacc ? A.Uacc[o + v * nn] + out[v] : out[v];
+      const double ub = A.Uacc ? acc[v] + out[v] : out[v];
       A.Ubar[o + v * nn] = ub;
       // the next reverse stage's cotangent of U_t, into another array (the
       // neighbours still read this one); a separate pass would read both again
-      if (A.Gnext) A.Gnext[o + v * nn] = A.ga * A.Lbar[o + v * nn] + A.gb * ub;
+      if (A.Gnext) A.Gnext[o + v * nn] = A.ga * lam[v] + A.gb * ub;
     }
   }
 }
@@ -4818,7 +4843,7 @@ hipError_t launch_integrals(const ReduceArgs& R, hipStream_t s) {
 
 template <int VF>
 hipError_t launch_vjp_vf(const VjpArgs& A, int eq, hipStream_t s) {
-  const dim3 grid(8 * A.chunk), block(NT);
+  const dim3 grid(8 * A.chunk), block(NTV);
   if (A.wall_dir >= 0) {  // walls: Navier-Stokes (checked on the host)
     if (eq == 2) hipLaunchKernelGGL((k_vjp<VF, 2, true>), grid, block, 0, s, A);
     else if (eq == 1) hipLaunchKernelGGL((k_vjp<VF, 1, true>), grid, block, 0, s, A);
