@@ -1086,15 +1086,13 @@ __device__ __forceinline__ void face_item(const StageArgs& A, const FaceItem& it
 // EQ: 0 Euler, 1 Navier-Stokes, 2 Navier-Stokes with the Smagorinsky eddy
 // viscosity.  R: arithmetic type (double, or float for the mixed operator, MX).
 // ---------------------------------------------------------------------------
-// Several elements per workgroup: two workgroups per CU need 4 waves per SIMD
-// (at most 128 registers); not imposed on the CH flux, which would spill.
-#if DG_STAGE_MIN_WAVES > 0
-#define DG_STAGE_BOUNDS __launch_bounds__(PS::NTB, DG_STAGE_MIN_WAVES)
-#elif DG_EPB_STAGE > 1
-#define DG_STAGE_BOUNDS __launch_bounds__(PS::NTB, VF == VF_CH ? 1 : 4)
-#else
-#define DG_STAGE_BOUNDS __launch_bounds__(PS::NTB, BLEND && EQ >= 1 && VF != VF_CH && N <= 4 ? 4 : 1)
-#endif
+// Navier-Stokes: four waves per SIMD (at most 128 registers) where the LDS admits
+// as many: every unblended kernel, the blended ones at N <= 4.  Most take fewer
+// anyway; the ones that would take 129 to 132 (STD at N = 5, KG and STD at N = 7)
+// keep the fourth wave (at N = 7 the second workgroup of a CU) at the cost of
+// none or two spilled registers.  Measured: STD N = 5 Smagorinsky step 1882 ->
+// 1763 us.  Not imposed on the CH flux, which would spill much more.
+#define DG_STAGE_BOUNDS __launch_bounds__(PS::NTB, EQ >= 1 && VF != VF_CH && (!BLEND || N <= 4) ? 4 : 1)
 // Indicator quantity q = rho p of a conservative node state.
 __device__ __forceinline__ double indicator_q(const double u[5], double gm1) {
   const double ir = 1.0 / u[0];
