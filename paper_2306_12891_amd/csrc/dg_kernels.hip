@@ -1091,8 +1091,9 @@ __device__ __forceinline__ void face_item(const StageArgs& A, const FaceItem& it
 // anyway; the ones that would take 129 to 132 (STD at N = 5, KG and STD at N = 7)
 // keep the fourth wave (at N = 7 the second workgroup of a CU) at the cost of
 // none or two spilled registers.  Measured: STD N = 5 Smagorinsky step 1882 ->
-// 1763 us.  Not imposed on the CH flux, which would spill much more.
-#define DG_STAGE_BOUNDS __launch_bounds__(PS::NTB, EQ >= 1 && VF != VF_CH && (!BLEND || N <= 4) ? 4 : 1)
+// 1763 us; N = 7 24^3 step, KG 3392 -> 2219 us, STD 3361 -> 2172 us.  Not imposed
+// on the CH flux and at N = 1, which would spill much more.
+#define DG_STAGE_BOUNDS __launch_bounds__(PS::NTB, EQ >= 1 && VF != VF_CH && N >= 2 && (!BLEND || N <= 4) ? 4 : 1)
 // Indicator quantity q = rho p of a conservative node state.
 __device__ __forceinline__ double indicator_q(const double u[5], double gm1) {
   const double ir = 1.0 / u[0];
@@ -3925,10 +3926,11 @@ __device__ __forceinline__ void volume_dir_curved(const double (*sP)[nnp], const
 // twelve contravariant viscous fluxes sV[12][nnp]), interface fluxes
 // sF[6][5][nf], and for Navier-Stokes q* sQ[6][4][nf], which the face metrics
 // sJf[6][3][nf] overlay once the gradient is formed, and the neighbours'
-// projected viscous fluxes sFn[6][4][nf].  At N = 5 this is 53 KB: three
-// workgroups per CU, with at most 168 registers (3 waves per SIMD).
+// projected viscous fluxes sFn[6][4][nf].  At N = 5 this is 53 KB, three
+// workgroups per CU, at N = 6 78 KB, two, both with at most 168 registers (3 waves
+// per SIMD).
 template <int VF, int EQ>
-__global__ __launch_bounds__(NT, DG_N == 5 ? 3 : 1) void k_stage_curved(StageArgs A) {
+__global__ __launch_bounds__(NT, N == 5 || N == 6 ? 3 : 1) void k_stage_curved(StageArgs A) {
   constexpr bool NS = EQ >= 1;
   constexpr int oM = 7 * nnp, oF = oM + 9 * nn, oQ = oF + 30 * nf, oFn = oQ + 24 * nf;
   constexpr int POOL = NS ? oFn + 24 * nf : oQ;
