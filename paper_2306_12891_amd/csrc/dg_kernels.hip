@@ -402,31 +402,43 @@ __device__ __forceinline__ void surface_flux_dir(int d, int sf, const double L[5
 // ---------------------------------------------------------------------------
 // Volume integral along direction D for node n (index id along D).
 // ---------------------------------------------------------------------------
-// ROT: the N partners l != id of a node in a rotated order, fully unrolled, so
-// that step m adds a compile-time offset to the node: l = id ^ m where N + 1
-// is a power of two, else l = (id + m) mod (N + 1), i.e. node n + m st or,
-// past the line's end, n + (m - N - 1) st.  The coefficients Dhat_{id l} lie in
-// LDS in the same order (sDhat[m][id], see dhat_index).  Before each partner
+// ROT: the N partners l != id of a node, fully unrolled, in an order in which
+// the lanes of a wave spread over the LDS banks and step m adds compile-time
+// offsets: l = id ^ m where N + 1 is a power of two, else l = line_order(m) where
+// id's own position comes first, line_order(m - 1) where it comes later.  The
+// coefficients Dhat_{id l} lie in LDS in the same order (sDhat[m][id], see
+// dhat_index).  Before each partner
 // tie(k, ic) makes the next indices depend on all running sums (an empty asm),
 // so that a partner's values are loaded only once the sums of the one before
 // are formed: else the unrolled loop takes more than 200 registers.
-// Otherwise (the mixed operator and the blended kernels): every l in order, the
-// zero diagonal term included, sDhat as in the basis; rolled with the gradient
-// (unrolled, its loads in flight need more than 200 registers).
-// Measured at 32^3: the Euler N = 7 step 3213 -> 3155 us, the N = 5
-// Navier-Stokes stage 370 -> 363 us with ROT (one partner in N + 1 less, no
-// loop); the blended N = 5 step 290 -> 298 us, so those keep the plain order.
+// Otherwise (the mixed operator): every l in order, the zero diagonal term
+// included, sDhat as in the basis; rolled with the gradient (unrolled, its loads
+// in flight need more than 200 registers).
+// The loop is bound by LDS.  16 lanes read 16 doubles in a cycle if they fall
+// on 16 different bank pairs; the two neighbouring values that the lanes of one
+// line read in a step (most of them the same one) do at N = 5 and 6, where a
+// rotation l = (id + m) mod (N + 1) of every line loses more cycles to conflicts
+// than the omitted diagonal saves.  Cycles per wave and value at N = 5, sum over
+// directions: every l 75, rotated 80, this order 59.  At N = 4 (rows of 5) plain
+// ascending order conflicts along x (76; every l 70), the order 3 1 2 0 4 does
+// less (64).
+// Measured at 32^3: every l -> without the diagonal, Euler N = 7 step 3213 -> 3155
+// us; rotated -> this order, N = 5 Smagorinsky step 2320 -> 2284 us, N = 6 186 ->
+// 178 us (small mesh); blended Navier-Stokes N = 6 620 -> 606 us.
 constexpr bool kPow2 = (n1 & (n1 - 1)) == 0;
+// Line positions in the order in which partners are visited (its own inverse).
+__host__ __device__ constexpr int line_order(int m) { return N == 4 && (m == 0 || m == 3) ? 3 - m : m; }
 template <bool ROT, bool ROLLED, int ST, class R, class F, class T>
 __device__ __forceinline__ void partner_loop(int id, int n, const R* sDhat, F&& body, T&& tie) {
   if (ROT) {
-    const int nw = n - n1 * ST;
+    const int base = n - id * ST, pos = line_order(id);
     int ic = id;
 #pragma unroll
     for (int m = 1; m <= N; ++m) {
+      const int la = line_order(m - 1), lb = line_order(m);
       int k;
       if (kPow2) k = n ^ (m * ST);
-      else k = (id >= n1 - m ? nw : n) + m * ST;
+      else k = (pos < m ? base + (lb - la) * ST : base) + la * ST;
       if (m == 1) asm volatile("" : "+v"(k), "+v"(ic));
       else tie(k, ic);
       body(sDhat[m * n1 + ic], k);
@@ -450,8 +462,7 @@ __device__ __forceinline__ void partner_loop(int id, int n, const R* sDhat, F&& 
 __device__ __forceinline__ int dhat_index(int t) {
   const int m = t / n1, id = t - m * n1;
   if (kPow2) return id * n1 + (id ^ m);
-  const int l = id + m;
-  return id * n1 + (l >= n1 ? l - n1 : l);
+  return id * n1 + (m == 0 ? id : line_order(line_order(id) < m ? m : m - 1));
 }
 
 // With GRAD, also returns gs[c] = sum_{l != id} Dw_{id l} q_c(l) along the line
@@ -1254,7 +1265,7 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
   constexpr bool MX = sizeof(R) == 4;
   // the element's own face state comes through LDS (completed by the carry)
   constexpr bool OWN_LDS = DEFER && !BLEND;
-  constexpr bool ROT = !MX && !BLEND;  // partner order of the volume loop
+  constexpr bool ROT = !MX;  // partner order of the volume loop (the mixed bits stay)
   constexpr bool LINES = N >= 5 && N % 2 == 1;  // viscous divergence by lines
   constexpr int SVP = LINES ? SQP : nnp;        // its LDS row
   static_assert(!(BLEND && MX), "the blended operator is FP64 only");
