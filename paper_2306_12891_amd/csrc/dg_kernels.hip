@@ -756,12 +756,13 @@ __device__ __forceinline__ FaceItem face_item_geometry(const Nbr6& b, int q) {
 }
 
 // Conservative state of node n with the momentum rotated to (normal, t1, t2).
+template <int ROW = nn>
 __device__ __forceinline__ void load_rotated(const double* Ux, int n, const FaceItem& it, double X[5]) {
   X[0] = Ux[n];
-  X[1] = Ux[(1 + it.d) * nn + n];
-  X[2] = Ux[it.k1 * nn + n];
-  X[3] = Ux[it.k2 * nn + n];
-  X[4] = Ux[4 * nn + n];
+  X[1] = Ux[(1 + it.d) * ROW + n];
+  X[2] = Ux[it.k1 * ROW + n];
+  X[3] = Ux[it.k2 * ROW + n];
+  X[4] = Ux[4 * ROW + n];
 }
 
 // Conservative minus (L) and plus (R) states of the face item, rotated (the
@@ -1208,11 +1209,25 @@ __device__ __forceinline__ void node_viscous_flux(const StageArgs& A, int e, con
 
 __device__ __forceinline__ int axis_stride(int j) { return j == 0 ? 1 : (j == 1 ? n1 : nf); }
 
-// Padded node layout of LDS arrays read by lines: one entry after every x-row, so that the lines read across a wavefront (x-lines
-// of different rows, y-lines of different planes) fall on different LDS banks.
-constexpr int SQP = nn + nn / n1;  // entries per variable
-__device__ __forceinline__ constexpr int pstride(int j) { return j == 0 ? 1 : (j == 1 ? n1 + 1 : n1 * (n1 + 1)); }
-__device__ __forceinline__ int padded(int m) { return m + m / n1; }  // node m = i0 + n1 i1 + nf i2
+// Node layout of LDS arrays read by nodes and by lines: entry padded(m) for node
+// m = i0 + n1 i1 + nf i2, SQP entries per variable.  One entry after every x-row,
+// so that x-lines of different rows and y-lines of different planes fall on
+// different banks.  FP64 at N = 7 (PAD16): one after every 16 nodes instead.  16
+// lanes read 16 doubles in a cycle if they differ modulo 16; rows of 8 + 1 do
+// not when read by nodes, 16 + 1 do, and so do their x-lines, z-lines and, in the
+// order of divergence_lines, y-lines: 192 instead of 320 cycles per wave for the
+// divergence.  Measured: N = 7 64^3 step 40.54 -> 39.83 ms, KG 24^3 2275 -> 2083 us (the floats of the
+// mixed operator lose: 4646 -> 4802 us at 32^3).
+template <class R>
+struct LineLayout {
+  static constexpr bool PAD16 = N == 7 && sizeof(R) == 8;
+  static constexpr int SQP = PAD16 ? nn + nn / 16 : nn + nn / n1;
+  __device__ static __forceinline__ int padded(int m) { return PAD16 ? m + (m >> 4) : m + m / n1; }
+  // stride of axis j, without PAD16's entry after two rows along y
+  __device__ static __forceinline__ int stride(int j) {
+    return j == 0 ? 1 : (j == 1 ? (PAD16 ? n1 : n1 + 1) : (PAD16 ? nf + nf / 16 : nf + n1));
+  }
+};
 
 // Line pass of the viscous divergence: sV[4 d + c][padded node] (component c
 // of the viscous flux in direction d) becomes sum_l Dw_il sV_l along the lines
@@ -1221,22 +1236,27 @@ __device__ __forceinline__ int padded(int m) { return m + m / n1; }  // node m =
 // value is read from LDS and written back once per line instead of being read
 // by all n1 nodes of its line together with a coefficient.
 template <class R, int NTHR>
-__device__ __forceinline__ void divergence_lines(const StageArgs& A, R (*sV)[SQP], int tid) {
+__device__ __forceinline__ void divergence_lines(const StageArgs& A, R (*sV)[LineLayout<R>::SQP], int tid) {
+  using LL = LineLayout<R>;
   const cdouble_ptr Dw = (cdouble_ptr)(uintptr_t)A.basis + BL.Dw();
   const int q = tid;
   static_assert(6 * nf <= NTHR, "one task per thread");
   if (q < 6 * nf) {
     const int cp = q >= 3 * nf ? 1 : 0, ql = q - cp * 3 * nf;
-    const int d = ql / nf, a = ql - d * nf;
-    const int st = pstride(d);
-    const int base = (a % n1) * pstride(d == 0 ? 1 : 0) + (a / n1) * pstride(d == 2 ? 1 : 2);
-    R* r0 = sV[4 * d + 2 * cp] + base;
-    R* r1 = r0 + SQP;
+    const int d = ql / nf;
+    int a = ql - d * nf;
+    // PAD16, y-lines: planes k and k + 2 side by side (bits 3 and 4 of the line
+    // index exchanged), whose 16 values fall on different banks
+    if (LL::PAD16 && d == 1) a = (a & 0x27) | ((a & 8) << 1) | ((a >> 1) & 8);
+    const int st = LL::stride(d), dy = LL::PAD16 && d == 1 ? 1 : 0;
+    const int m0 = (a % n1) * axis_stride(d == 0 ? 1 : 0) + (a / n1) * axis_stride(d == 2 ? 1 : 2);
+    R* r0 = sV[4 * d + 2 * cp] + LL::padded(m0);
+    R* r1 = r0 + LL::SQP;
     R v0[n1], v1[n1];
 #pragma unroll
     for (int l = 0; l < n1; ++l) {
-      v0[l] = r0[l * st];
-      v1[l] = r1[l * st];
+      v0[l] = r0[l * st + (l >> 1) * dy];
+      v1[l] = r1[l * st + (l >> 1) * dy];
     }
 #pragma unroll
     for (int i = 0; i < n1; ++i) {
@@ -1248,8 +1268,8 @@ __device__ __forceinline__ void divergence_lines(const StageArgs& A, R (*sV)[SQP
         s0 = fmaR(c, v0[l], s0);
         s1 = fmaR(c, v1[l], s1);
       }
-      r0[i * st] = s0;
-      r1[i * st] = s1;
+      r0[i * st + (i >> 1) * dy] = s0;
+      r1[i * st + (i >> 1) * dy] = s1;
     }
   }
 }
@@ -1267,7 +1287,7 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
   constexpr bool OWN_LDS = DEFER && !BLEND;
   constexpr bool ROT = !MX;  // partner order of the volume loop (the mixed bits stay)
   constexpr bool LINES = N >= 5 && N % 2 == 1;  // viscous divergence by lines
-  constexpr int SVP = LINES ? SQP : nnp;        // its LDS row
+  constexpr int SVP = LINES ? LineLayout<R>::SQP : nnp;        // its LDS row
   static_assert(!(BLEND && MX), "the blended operator is FP64 only");
   static_assert(!WALL || (NS && !MX && DEFER), "walls: FP64 Navier-Stokes");
   static_assert(!DEFER || (NS && !MX), "deferred viscous exchange: FP64 Navier-Stokes");
@@ -1276,11 +1296,15 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
   // viscous fluxes sFn[6][4][nf].  The twelve viscous-flux components of all
   // nodes are later exchanged through sV[12][SVP], which overlays sP, sF and sQ
   // (all consumed by then) but not sFn.  With OWN_LDS the element's completed
-  // conservative state sU[5][nn] passes through the space of sF and sQ.
+  // conservative state sU[5][UROW] passes through the space of sF and sQ.
   constexpr int oF = 7 * nnp, oQ = oF + 30 * nf, oFn = std::max(oQ + 24 * nf, 12 * SVP);
   constexpr int POOL = NS ? oFn + 24 * nf : oQ;
   static_assert(!NS || 12 * SVP <= oFn, "viscous exchange must not overlay sFn");
-  static_assert(!OWN_LDS || 5 * nn <= 54 * nf, "sU in the space of sF and sQ");
+  // N = 7: one entry after every 16 nodes, else 16 nodes of an x-face share two
+  // banks (64^3 step 40.63 -> 40.26 ms)
+  constexpr bool UPAD = N == 7;
+  constexpr int UROW = UPAD ? nn + nn / 16 : nn;
+  static_assert(!OWN_LDS || 5 * UROW <= 54 * nf, "sU in the space of sF and sQ");
   constexpr int EPB = PS::EPB, TPE = PS::TPE, FI = PS::FI;
   __shared__ R sPoolAll[EPB][POOL];
   __shared__ R sB[NB_STAGE];
@@ -1366,7 +1390,7 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
     }
     if (t < nn) {
 #pragma unroll
-      for (int v = 0; v < 5; ++v) sPool[oF + v * nn + t] = u[v];
+      for (int v = 0; v < 5; ++v) sPool[oF + v * UROW + (UPAD ? t + (t >> 4) : t)] = u[v];
     }
   }
   if (t < nn) {
@@ -1385,7 +1409,10 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < FI; ++k)
-      if (t + k * TPE < 6 * nf) load_rotated(sPool + oF, fd[k].it.nown, fd[k].it, own[k]);
+      if (t + k * TPE < 6 * nf) {
+        const int m = fd[k].it.nown;
+        load_rotated<UROW>(sPool + oF, UPAD ? m + (m >> 4) : m, fd[k].it, own[k]);
+      }
     __syncthreads();  // sU read: sF and sQ may be written
 #pragma unroll
     for (int k = 0; k < FI; ++k)
@@ -1566,7 +1593,7 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
     // (150 tasks for 128 threads) 460 -> 477 us; the mixed N = 6 step on a small
     // mesh 71 -> 74 us.
     __syncthreads();
-    const int tp = LINES ? padded(t) : t;
+    const int tp = LINES ? LineLayout<R>::padded(t) : t;
     if (t < nn) {
 #pragma unroll
       for (int d = 0; d < 3; ++d)
