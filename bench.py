@@ -2,7 +2,8 @@
 
 Default workload: Taylor-Green vortex, Ma 0.1, Re 1600, Pr 0.72, N = 7 on
 64^3 periodic elements (134 M nodes), Pirozzoli split flux + Roe, BR1
-lifting (split: one lifting launch per step), FP64, LSERK4: the configuration
+lifting (split: no lifting launches, the neighbours' half of the viscous
+surface term follows one stage later), FP64, LSERK4: the configuration
 the metric is quoted on (FP64
 against the mixed-precision operator at its stated error; the adjoint of
 the N = 5, 16^3 TGV beside it).  A "step" is one Runge-Kutta step (5 stages) over the
@@ -116,18 +117,18 @@ def domain(name):
 # HBM bytes per launch of the stage kernel measured with rocprofv3 --pmc
 # FETCH_SIZE and WRITE_SIZE (separate runs), each scaled by the plain-copy
 # calibration (FETCH x 2.000, WRITE x 1.000); averages over the five stage
-# launches of one step (the TGV workloads with the split lifting); see
+# launches of one step (the Navier-Stokes workloads with the split lifting); see
 # profiles/k_stage_*.md.
 # Valid only for the kernel source they were taken on (sha256 prefix).
 MEASURED_TRAFFIC = {
-    "kernel_sha": "cc42175a04ddafbd",
-    "tgv_n7_64": {"bytes_per_launch": 26891.8e6, "fetch": 14651.1e6, "write": 12240.7e6},
-    "tgv_n5_32": {"bytes_per_launch": 1599.7e6, "fetch": 874.4e6, "write": 725.3e6},
-    "freestream_euler_n7_64": {"bytes_per_launch": 20721.4e6, "fetch": 11057.7e6, "write": 9663.7e6},
-    "tgv_curved_n5_32": {"bytes_per_launch": 2056.2e6, "fetch": 1521.0e6, "write": 535.2e6},
-    "channel_wm_n5_32": {"bytes_per_launch": 1389.6e6, "fetch": 864.3e6, "write": 525.3e6},
-    "sod_ns_n4_256x16x16": {"bytes_per_launch": 2302.3e6, "fetch": 1675.6e6, "write": 626.7e6},
-    "tgv_les_n5_32": {"bytes_per_launch": 1398.8e6, "fetch": 872.3e6, "write": 526.5e6},
+    "kernel_sha": "b166d066bd3a1de4",
+    "tgv_n7_64": {"bytes_per_launch": 33181.6e6, "fetch": 19673.2e6, "write": 13508.4e6},
+    "tgv_n5_32": {"bytes_per_launch": 1830.7e6, "fetch": 1026.4e6, "write": 804.3e6},
+    "freestream_euler_n7_64": {"bytes_per_launch": 20721.0e6, "fetch": 11057.3e6, "write": 9663.7e6},
+    "tgv_curved_n5_32": {"bytes_per_launch": 2281.8e6, "fetch": 1473.7e6, "write": 808.1e6},
+    "channel_wm_n5_32": {"bytes_per_launch": 1815.3e6, "fetch": 1011.8e6, "write": 803.4e6},
+    "sod_ns_n4_256x16x16": {"bytes_per_launch": 2590.5e6, "fetch": 1587.6e6, "write": 1002.9e6},
+    "tgv_les_n5_32": {"bytes_per_launch": 1831.4e6, "fetch": 1026.3e6, "write": 805.1e6},
 }
 
 
@@ -137,14 +138,14 @@ MEASURED_TRAFFIC = {
 # stage launches of one step; profiles/k_stage_*.md); valid only for the
 # kernel source they were counted on (sha256 prefix).
 KERNEL_FLOPS = {
-    "kernel_sha": "cc42175a04ddafbd",
-    "tgv_n7_64": {"stage_flops_per_dof": 1418.5},
-    "tgv_n5_32": {"stage_flops_per_dof": 1583.6},
-    "freestream_euler_n7_64": {"stage_flops_per_dof": 717.2},
-    "tgv_curved_n5_32": {"stage_flops_per_dof": 2062.5},
-    "channel_wm_n5_32": {"stage_flops_per_dof": 1416.3},
-    "sod_ns_n4_256x16x16": {"stage_flops_per_dof": 1068.3},
-    "tgv_les_n5_32": {"stage_flops_per_dof": 1403.3},
+    "kernel_sha": "b166d066bd3a1de4",
+    "tgv_n7_64": {"stage_flops_per_dof": 1202.5},
+    "tgv_n5_32": {"stage_flops_per_dof": 1303.7},
+    "freestream_euler_n7_64": {"stage_flops_per_dof": 656.2},
+    "tgv_curved_n5_32": {"stage_flops_per_dof": 1934.8},
+    "channel_wm_n5_32": {"stage_flops_per_dof": 1369.0},
+    "sod_ns_n4_256x16x16": {"stage_flops_per_dof": 1277.5},
+    "tgv_les_n5_32": {"stage_flops_per_dof": 1345.2},
 }
 
 
@@ -368,7 +369,8 @@ def face_flux_bytes_per_node(N, viscous, split):
     """Algorithmic bytes per node and stage launch of the normal viscous face
     flux (FP64, 4 values at each of the 6 (N+1)^2 face nodes of an element):
     the stage kernel reads the neighbours' (192/(N+1) B per node); with the
-    split lifting it also writes the own part of its output in stages 1-4."""
+    split lifting it writes its own in every stage and reads the neighbours' of
+    the stage before in stages 2-5."""
     if not viscous:
         return 0.0
     f = 192.0 / (N + 1)
@@ -545,10 +547,9 @@ def main():
     lifting = dg.LIFT_SPLIT if args.lifting == "split" else dg.LIFT_TWO_PASS
     op = dg.DG(nelem, N, gamma=1.4, mu=mu, lo=lo, hi=hi, equations=eq, vol_flux=vf, surf_flux=sf,
                blending=blend, Pr=0.72, Cs=cs, lifting=lifting)
-    # whether the split lifting runs here (the library uses it for the FP64
-    # Navier-Stokes operator on the box without eddy viscosity, blending or walls)
-    split = (lifting == dg.LIFT_SPLIT and eq == dg.NS and cs == 0.0 and not blend and name not in CURVED
-             and name not in WALLS)
+    # whether the split lifting runs here (with eddy viscosity, blending, curved
+    # elements or walls the library has no other)
+    split = eq == dg.NS and (lifting == dg.LIFT_SPLIT or cs != 0.0 or bool(blend) or name in CURVED or name in WALLS)
     if name in CURVED:
         op.set_geometry(torch.from_numpy(curved_nodes(name, N, nelem)).to("cuda:0"))
     if name in WALLS:

@@ -38,8 +38,8 @@
  * be device memory on the context's device and is never freed or retained.
  * The context owns all scratch (Runge-Kutta register, ping-pong state, face
  * buffers, blending arrays, reduction partials); dg_init allocates it (the
- * reverse-mode buffers and the split lifting's second face buffer on first
- * use, as noted at those calls) and dg_finalize releases it.
+ * reverse-mode buffers, the split lifting's second face buffer and a third
+ * state on first use, as noted at those calls) and dg_finalize releases it.
  *
  * Errors: every function returns DG_OK (0) or a negative code; it never
  * aborts or prints.  dg_last_error() gives a message.  Errors of asynchronous
@@ -250,9 +250,12 @@ int dg_time_derivative(dg_ctx* ctx, const double* U, double* Ut);
 int rk_step(dg_ctx* ctx, double* U, double dt);
 
 /* nsteps Runge-Kutta steps in place (same result as nsteps rk_step calls).
- * With the split lifting (dg_options.lifting) rk_step, dg_rk_steps,
+ * Where the split lifting runs (dg_options.lifting) rk_step, dg_rk_steps,
  * rk_step_record and rk_step_vjp allocate a second face buffer of
- * nElems * 6 * 4 * (N+1)^2 doubles on first use (DG_ENOMEM if that fails). */
+ * nElems * 6 * 4 * (N+1)^2 doubles on first use; elsewhere an odd number of
+ * steps allocates a third state where that is at most an eighth of the free
+ * memory.  Neither is allocated while the stream is captured, and without them
+ * (no memory, capture) the calls take an extra pass with the same results. */
 int dg_rk_steps(dg_ctx* ctx, double* U, double dt, int nsteps);
 
 /* Vector-Jacobian product of the operator: U_bar = (dL/dU)^T Ut_bar (the

@@ -81,6 +81,9 @@ struct StageArgs {
   double* Yout;
   double Bcarry;
   int carryU;
+  // values read once, by the next launch, bypass the caches (meshes whose data
+  // do not fit the Infinity Cache)
+  int stream;
 };
 
 struct ReduceArgs {

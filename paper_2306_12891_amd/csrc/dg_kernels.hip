@@ -12,12 +12,17 @@
 // order and the same code, which gives bitwise-identical interface fluxes and
 // hence discrete conservation to round-off.
 //
-// The Navier-Stokes stage kernel is bound by LDS traffic and issue rate, not
-// by HBM: the BR1 gradient is accumulated inside the split-form partner loop
-// (off the diagonal Dw = Dhat / 2, so partner values and coefficients are
-// shared), the twelve viscous-flux components are exchanged through LDS once,
-// and all global loads of a workgroup are issued in two rounds (indices,
-// state and basis; then the neighbours' face states) before any arithmetic.
+// The Navier-Stokes stage kernel is bound by LDS traffic and issue rate (each
+// about two thirds busy at N = 5 and 7), with HBM close behind (258 B per node at
+// 4.2 TB/s at N = 5): the BR1 gradient is accumulated inside the split-form
+// partner loop (off the diagonal Dw = Dhat / 2, so partner values and
+// coefficients are shared), the twelve viscous-flux components are exchanged
+// through LDS once, partners and LDS rows are ordered for the banks, and all
+// global loads of a workgroup are issued in two rounds (indices, state and
+// basis; then the neighbours' face states and fluxes) before any arithmetic.
+// The viscous coupling of neighbours needs no pass of its own: each stage
+// writes its normal viscous flux at its face nodes, and the neighbour's half of
+// the surface term follows in the next stage kernel (the carry, further below).
 //
 // Equations (paper: Blind et al., FLEXI; Sec. 2 and Sec. 4.1 for the split
 // form on LGL nodes and the DG/FV blend, Sec. 4.2 for the alpha bounds):
@@ -65,11 +70,6 @@ constexpr int NTP2 = NT <= 64 ? 64 : (NT <= 128 ? 128 : (NT <= 256 ? 256 : 512))
 constexpr BasisLayout BL(n1);
 constexpr int NB_STAGE = 2 * n1 * n1 + 3 * n1 + 1;  // Dhat, Dw, winv, xi, edge
 
-// Tuning: minimum waves per SIMD requested from the register allocator for
-// the stage kernel (0 = compiler default).
-#ifndef DG_STAGE_MIN_WAVES
-#define DG_STAGE_MIN_WAVES 0
-#endif
 // Accumulate the BR1 gradient inside the split-form volume loop, reusing its
 // partner values and coefficients (1), or in a separate pass (0).  The fused
 // loop is kept rolled: fully unrolled, the partner loads in flight need more
@@ -129,8 +129,35 @@ __device__ __forceinline__ double fmaR(double a, double b, double c) { return fm
 __device__ __forceinline__ float fmaR(float a, float b, float c) { return fmaf(a, b, c); }
 __device__ __forceinline__ double absR(double a) { return fabs(a); }
 __device__ __forceinline__ float absR(float a) { return fabsf(a); }
-__device__ __forceinline__ double maxR(double a, double b) { return fmax(a, b); }
-__device__ __forceinline__ float maxR(float a, float b) { return fmaxf(a, b); }
+
+// Stores and loads of values that are used once, by the next launch (C rows of
+// distance row): streaming (nontemporal) or ordinary (StageArgs.stream, uniform;
+// rule and figures at streaming() on the host side).  The empty asms keep the
+// compiler from merging the two branches into one without the hint.
+template <int C, class R>
+__device__ __forceinline__ void put(R* p, int row, const R* v, int stream) {
+  if (stream) {
+    asm volatile("");
+#pragma unroll
+    for (int c = 0; c < C; ++c) __builtin_nontemporal_store(v[c], &p[c * row]);
+    asm volatile("");
+  } else {
+#pragma unroll
+    for (int c = 0; c < C; ++c) p[c * row] = v[c];
+  }
+}
+template <int C>
+__device__ __forceinline__ void get(const double* p, int row, double* v, int stream) {
+  if (stream) {
+    asm volatile("");
+#pragma unroll
+    for (int c = 0; c < C; ++c) v[c] = __builtin_nontemporal_load(&p[c * row]);
+    asm volatile("");
+  } else {
+#pragma unroll
+    for (int c = 0; c < C; ++c) v[c] = p[c * row];
+  }
+}
 
 // Constant reference state subtracted in the mixed-precision operator
 // (all zero for FP64): pressure, total enthalpy h = (E + p)/rho, theta = p/rho.
@@ -869,21 +896,26 @@ __device__ __forceinline__ void wall_face_loads(const double* U, int e, const Fa
 #ifndef DG_EPB_LIFT
 #define DG_EPB_LIFT (DG_N == 5 ? 2 : 1)
 #endif
-template <int E>
+template <int E, bool FACES = true>
 struct Pack {
   static constexpr int EPB = E;
   // one element: whole waves, enough of them for one face item per thread (at N
   // = 3 and 4 the element has more face nodes than nodes: with NT threads a
-  // second, mostly empty round of face items doubles the face data in registers)
-  static constexpr int ITEMS = nn > 6 * nf ? nn : 6 * nf;
+  // second, mostly empty round of face items doubles the face data in registers).
+  // Not the blended Euler kernels (FACES false): their subcell passes are work by
+  // nodes and an idle wave costs more than the second round.  Measured, shock
+  // tube of 3e6 nodes: N = 3 873 us with the additional wave, 743 without, N = 4
+  // 836 and 778; blended Navier-Stokes at N = 3 and 4 gains 1 to 7 %.
+  static constexpr int ITEMS = FACES && nn < 6 * nf ? 6 * nf : nn;
   static constexpr int TPE = E == 1 ? (ITEMS + 63) / 64 * 64 : ITEMS;
   static constexpr int NTB = ((E * TPE + 63) / 64) * 64;
   // face items handled by one thread of a slot (item q = t + k TPE, k < FI)
   static constexpr int FI = (6 * nf + TPE - 1) / TPE;
   static_assert(E >= 1 && NTB <= 1024, "workgroup size");
 };
-using PS = Pack<DG_EPB_STAGE>;
-using PL = Pack<DG_EPB_LIFT>;
+template <int EQ, bool BLEND>
+using PSK = Pack<DG_EPB_STAGE, !(BLEND && EQ == 0)>;
+using PL = Pack<DG_EPB_LIFT, true>;
 
 // Slot of the calling thread: element e (clamped to a valid one), its thread
 // index t within the slot, and t = TPE (beyond every per-thread bound: nodes,
@@ -1105,7 +1137,7 @@ __device__ __forceinline__ void face_item(const StageArgs& A, const FaceItem& it
 // none or two spilled registers.  Measured: STD N = 5 Smagorinsky step 1882 ->
 // 1763 us; N = 7 24^3 step, KG 3392 -> 2219 us, STD 3361 -> 2172 us.  Not imposed
 // on the CH flux and at N = 1, which would spill much more.
-#define DG_STAGE_BOUNDS __launch_bounds__(PS::NTB, EQ >= 1 && VF != VF_CH && N >= 2 && (!BLEND || N <= 4) ? 4 : 1)
+#define DG_STAGE_BOUNDS __launch_bounds__((PSK<EQ, BLEND>::NTB), EQ >= 1 && VF != VF_CH && N >= 2 && (!BLEND || N <= 4) ? 4 : 1)
 // Indicator quantity q = rho p of a conservative node state.
 __device__ __forceinline__ double indicator_q(const double u[5], double gm1) {
   const double ir = 1.0 / u[0];
@@ -1305,6 +1337,7 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
   constexpr bool UPAD = N == 7;
   constexpr int UROW = UPAD ? nn + nn / 16 : nn;
   static_assert(!OWN_LDS || 5 * UROW <= 54 * nf, "sU in the space of sF and sQ");
+  using PS = PSK<EQ, BLEND>;
   constexpr int EPB = PS::EPB, TPE = PS::TPE, FI = PS::FI;
   __shared__ R sPoolAll[EPB][POOL];
   __shared__ R sB[NB_STAGE];
@@ -1579,8 +1612,7 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
   // that its latency is hidden (earlier, its registers would be live across
   // the volume loop, the kernel's register peak).
   if (t < nn && A.mode != MODE_UT && A.A != 0.0) {
-#pragma unroll
-    for (int v = 0; v < 5; ++v) gprev[v] = __builtin_nontemporal_load(&A.G[(size_t)e * 5 * nn + t + v * nn]);
+    get<5>(A.G + (size_t)e * 5 * nn + t, nn, gprev, A.stream);
   }
   if (NS && !(BLEND && A.mode == MODE_DIFF)) {  // uniform over the workgroup
     // Viscous divergence: all twelve flux components go through LDS once.
@@ -1647,8 +1679,7 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
             s3 = fmaR((R)2 * w, sFn[f][3][a], s3);
           } else {  // the own half; the neighbour's follows with the carry
             R* Fo = reinterpret_cast<R*>(A.Fvf_out) + ((size_t)e * 6 + f) * 4 * nf + a;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) __builtin_nontemporal_store(Fv[d][c], &Fo[c * nf]);
+            put<4>(Fo, nf, Fv[d], A.stream);
             s0 = fmaR(w, Fv[d][0], s0);
             s1 = fmaR(w, Fv[d][1], s1);
             s2 = fmaR(w, Fv[d][2], s2);
@@ -1680,14 +1711,13 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
     } else {
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
-        double gv = ut[v];
-        if (A.A != 0.0) gv = A.A * gprev[v] + ut[v];
-        // streaming stores (the register is read once, by this element's next
-        // stage; the state by the next stage kernel)
-        if (A.writeG) __builtin_nontemporal_store(gv, &A.G[o + v * nn]);
-        u[v] = u[v] + A.Bdt * gv;  // the stage output, kept for the indicator below
-        __builtin_nontemporal_store(u[v], &A.Uout[o + v * nn]);
+        if (A.A != 0.0) ut[v] = A.A * gprev[v] + ut[v];
+        u[v] = u[v] + A.Bdt * ut[v];  // the stage output, kept for the indicator below
       }
+      // the register is read once, by this element's next stage; the state by
+      // the next stage kernel
+      if (A.writeG) put<5>(A.G + o, nn, ut, A.stream);
+      put<5>(A.Uout + o, nn, u, A.stream);
     }
   }
   // Euler only: measured on the blended Navier-Stokes stage (N = 4, its
@@ -1829,10 +1859,19 @@ __device__ __forceinline__ void lift_face_node(const StageArgs& A, int e, const 
   const R ud = sq[d][n], ua = sq[ja][n], ub = sq[jb][n];
   const R FE = ud * Fd + ua * Fa + ub * Fb + kap * g3;
   R* out = reinterpret_cast<R*>(A.Fvf) + ((size_t)e * 6 + it.f) * 4 * nf + it.a;
-  __builtin_nontemporal_store(Fd, &out[d * nf]);  // streaming: read once, by the neighbour
-  __builtin_nontemporal_store(Fa, &out[ja * nf]);
-  __builtin_nontemporal_store(Fb, &out[jb * nf]);
-  __builtin_nontemporal_store(FE, &out[3 * nf]);
+  if (A.stream) {  // as put(), rows in the element's frame
+    asm volatile("");
+    __builtin_nontemporal_store(Fd, &out[d * nf]);
+    __builtin_nontemporal_store(Fa, &out[ja * nf]);
+    __builtin_nontemporal_store(Fb, &out[jb * nf]);
+    __builtin_nontemporal_store(FE, &out[3 * nf]);
+    asm volatile("");
+  } else {
+    out[d * nf] = Fd;
+    out[ja * nf] = Fa;
+    out[jb * nf] = Fb;
+    out[3 * nf] = FE;
+  }
 }
 
 // Register budget of the lifting kernel: 8 waves per SIMD (64 VGPRs) with one
@@ -2782,8 +2821,11 @@ __device__ __forceinline__ void gradient_transpose_dir(const double (*sX)[nn], c
 // Main reverse kernel.  Writes U_bar (or U_acc + U_bar when A.Uacc is set).
 // EQ: 0 Euler, 1 Navier-Stokes, 2 with the Smagorinsky eddy viscosity; WALL:
 // wall-modelled faces (neighbour -1).
-// Three waves per SIMD (at most 168 registers; a few spill) run the reverse
-// kernel faster than two without spills; the wall variants keep their
+// Bound by latency and LDS: at N = 5, 16^3, 96 us (121 with one pass over the
+// partners for each of the two-point flux, the viscous-flux cotangent and the
+// forward gradient), LDS 0.55 and VALU 0.52 busy with 2.3 waves per SIMD in
+// flight.  Three waves per SIMD (at most 168 registers; a few spill) run it
+// faster than two without spills; the wall variants keep their
 // registers, and so does N = 7, where the LDS admits one workgroup per CU.
 template <int VF, int EQ, bool WALL = false>
 __global__ __launch_bounds__(NTV, WALL || N > 6 ? 1 : 3) void k_vjp(VjpArgs A) {
@@ -4111,8 +4153,7 @@ __global__ __launch_bounds__(NT, N == 5 || N == 6 ? 3 : 1) void k_stage_curved(S
   }
 
   if (t < nn && A.mode != MODE_UT && A.A != 0.0) {
-#pragma unroll
-    for (int v = 0; v < 5; ++v) gprev[v] = __builtin_nontemporal_load(&A.G[(size_t)e * 5 * nn + t + v * nn]);
+    get<5>(A.G + (size_t)e * 5 * nn + t, nn, gprev, A.stream);
   }
   if (NS) {
     __syncthreads();  // sP, sM and sQ consumed
@@ -4156,10 +4197,8 @@ __global__ __launch_bounds__(NT, N == 5 || N == 6 ? 3 : 1) void k_stage_curved(S
           double* Fo = A.Fvf_out + ((size_t)e * 6 + f) * 4 * nf + a;
           double p[4];
 #pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            p[c] = jx * Fv[0][c] + jy * Fv[1][c] + jz * Fv[2][c];
-            __builtin_nontemporal_store(p[c], &Fo[c * nf]);
-          }
+          for (int c = 0; c < 4; ++c) p[c] = jx * Fv[0][c] + jy * Fv[1][c] + jz * Fv[2][c];
+          put<4>(Fo, nf, p, A.stream);
           s0 = fma(w, p[0], s0);
           s1 = fma(w, p[1], s1);
           s2 = fma(w, p[2], s2);
@@ -4186,14 +4225,16 @@ __global__ __launch_bounds__(NT, N == 5 || N == 6 ? 3 : 1) void k_stage_curved(S
 #pragma unroll
       for (int v = 0; v < 5; ++v) A.Ut[o + v * nn] = acc[v] * iJ;
     } else {
+      double gv[5];
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
         const double ut = acc[v] * iJ;
-        double gv = ut;
-        if (A.A != 0.0) gv = A.A * gprev[v] + ut;
-        if (A.writeG) __builtin_nontemporal_store(gv, &A.G[o + v * nn]);  // streaming, as in k_stage
-        __builtin_nontemporal_store(u[v] + A.Bdt * gv, &A.Uout[o + v * nn]);
+        gv[v] = ut;
+        if (A.A != 0.0) gv[v] = A.A * gprev[v] + ut;
+        u[v] = u[v] + A.Bdt * gv[v];
       }
+      if (A.writeG) put<5>(A.G + o, nn, gv, A.stream);
+      put<5>(A.Uout + o, nn, u, A.stream);
     }
   }
 }
@@ -4770,7 +4811,7 @@ inline StageArgs grouped(const StageArgs& A) {
 
 template <int VF, bool BLEND, bool WALL, bool DEFER>
 hipError_t launch_stage_ns(const StageArgs& A, int eq, hipStream_t s) {
-  const dim3 grid(blocks_for(A)), block(PS::NTB);
+  const dim3 grid(blocks_for(A)), block((PSK<1, BLEND>::NTB));
   if (eq == 2) {
     if constexpr (VF != VF_CH && DEFER) hipLaunchKernelGGL((k_stage<VF, 2, BLEND, double, WALL, DEFER>), grid, block, 0, s, A);
     else return hipErrorInvalidValue;
@@ -4784,12 +4825,12 @@ hipError_t launch_stage_ns(const StageArgs& A, int eq, hipStream_t s) {
 // for the two-pass lifting (no eddy viscosity, walls or blending).
 template <int VF>
 hipError_t launch_stage_vf(const StageArgs& A0, int eq, hipStream_t s) {
-  const StageArgs A = grouped<PS>(A0);
-  const dim3 grid(blocks_for(A)), block(PS::NTB);
+  const StageArgs A = grouped<PSK<1, false>>(A0);
+  const dim3 grid(blocks_for(A));
   if (eq == 0) {
     if (A.wall_dir >= 0) return hipErrorInvalidValue;
-    if (A.blend) hipLaunchKernelGGL((k_stage<VF, 0, true, double>), grid, block, 0, s, A);
-    else hipLaunchKernelGGL((k_stage<VF, 0, false, double>), grid, block, 0, s, A);
+    if (A.blend) hipLaunchKernelGGL((k_stage<VF, 0, true, double>), grid, dim3(PSK<0, true>::NTB), 0, s, A);
+    else hipLaunchKernelGGL((k_stage<VF, 0, false, double>), grid, dim3(PSK<0, false>::NTB), 0, s, A);
     return hipGetLastError();
   }
   if (A.Fvf) return A.blend || A.wall_dir >= 0 ? hipErrorInvalidValue : launch_stage_ns<VF, false, false, false>(A, eq, s);
@@ -4800,8 +4841,8 @@ hipError_t launch_stage_vf(const StageArgs& A0, int eq, hipStream_t s) {
 
 template <int VF>
 hipError_t launch_stage_mixed_vf(const StageArgs& A0, int eq, hipStream_t s) {
-  const StageArgs A = grouped<PS>(A0);
-  const dim3 grid(blocks_for(A)), block(PS::NTB);
+  const StageArgs A = grouped<PSK<1, false>>(A0);
+  const dim3 grid(blocks_for(A)), block((PSK<1, false>::NTB));
   if (A.wall_dir >= 0 || A.blend) return hipErrorInvalidValue;
   if (eq == 2) hipLaunchKernelGGL((k_stage<VF, 2, false, float>), grid, block, 0, s, A);
   else if (eq == 1) hipLaunchKernelGGL((k_stage<VF, 1, false, float>), grid, block, 0, s, A);
