@@ -121,14 +121,14 @@ def domain(name):
 # profiles/k_stage_*.md.
 # Valid only for the kernel source they were taken on (sha256 prefix).
 MEASURED_TRAFFIC = {
-    "kernel_sha": "b166d066bd3a1de4",
-    "tgv_n7_64": {"bytes_per_launch": 33181.6e6, "fetch": 19673.2e6, "write": 13508.4e6},
-    "tgv_n5_32": {"bytes_per_launch": 1830.7e6, "fetch": 1026.4e6, "write": 804.3e6},
-    "freestream_euler_n7_64": {"bytes_per_launch": 20721.0e6, "fetch": 11057.3e6, "write": 9663.7e6},
-    "tgv_curved_n5_32": {"bytes_per_launch": 2281.8e6, "fetch": 1473.7e6, "write": 808.1e6},
-    "channel_wm_n5_32": {"bytes_per_launch": 1815.3e6, "fetch": 1011.8e6, "write": 803.4e6},
-    "sod_ns_n4_256x16x16": {"bytes_per_launch": 2590.5e6, "fetch": 1587.6e6, "write": 1002.9e6},
-    "tgv_les_n5_32": {"bytes_per_launch": 1831.4e6, "fetch": 1026.3e6, "write": 805.1e6},
+    "kernel_sha": "c80a67d467d54fe2",
+    "tgv_n7_64": {"bytes_per_launch": 32730.8e6, "fetch": 19203.4e6, "write": 13527.3e6},
+    "tgv_n5_32": {"bytes_per_launch": 1830.1e6, "fetch": 1026.1e6, "write": 804.0e6},
+    "freestream_euler_n7_64": {"bytes_per_launch": 20719.6e6, "fetch": 11056.0e6, "write": 9663.7e6},
+    "tgv_curved_n5_32": {"bytes_per_launch": 2282.7e6, "fetch": 1473.6e6, "write": 809.1e6},
+    "channel_wm_n5_32": {"bytes_per_launch": 1818.1e6, "fetch": 1011.9e6, "write": 806.2e6},
+    "sod_ns_n4_256x16x16": {"bytes_per_launch": 2580.2e6, "fetch": 1569.1e6, "write": 1011.1e6},
+    "tgv_les_n5_32": {"bytes_per_launch": 1830.8e6, "fetch": 1026.0e6, "write": 804.8e6},
 }
 
 
@@ -138,7 +138,7 @@ MEASURED_TRAFFIC = {
 # stage launches of one step; profiles/k_stage_*.md); valid only for the
 # kernel source they were counted on (sha256 prefix).
 KERNEL_FLOPS = {
-    "kernel_sha": "b166d066bd3a1de4",
+    "kernel_sha": "c80a67d467d54fe2",
     "tgv_n7_64": {"stage_flops_per_dof": 1202.5},
     "tgv_n5_32": {"stage_flops_per_dof": 1303.7},
     "freestream_euler_n7_64": {"stage_flops_per_dof": 656.2},
