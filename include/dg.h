@@ -39,7 +39,7 @@
  * The context owns all scratch (Runge-Kutta register, ping-pong state, face
  * buffers, blending arrays, reduction partials); dg_init allocates it (the
  * reverse-mode buffers, the split lifting's second face buffer and a third
- * state on first use, as noted at those calls) and dg_finalize releases it.
+ * state on first use or in dg_set_options, as noted at those calls) and dg_finalize releases it.
  *
  * Errors: every function returns DG_OK (0) or a negative code; it never
  * aborts or prints.  dg_last_error() gives a message.  Errors of asynchronous
@@ -254,7 +254,8 @@ int rk_step(dg_ctx* ctx, double* U, double dt);
  * rk_step_record and rk_step_vjp allocate a second face buffer of
  * nElems * 6 * 4 * (N+1)^2 doubles on first use; elsewhere an odd number of
  * steps allocates a third state where that is at most an eighth of the free
- * memory.  Neither is allocated while the stream is captured, and without them
+ * memory.  dg_set_options allocates either beforehand where it is at most an
+ * eighth of the free memory.  Neither is allocated while the stream is captured, and without them
  * (no memory, capture) the calls take an extra pass with the same results. */
 int dg_rk_steps(dg_ctx* ctx, double* U, double dt, int nsteps);
 
