@@ -121,14 +121,14 @@ def domain(name):
 # profiles/k_stage_*.md.
 # Valid only for the kernel source they were taken on (sha256 prefix).
 MEASURED_TRAFFIC = {
-    "kernel_sha": "c80a67d467d54fe2",
-    "tgv_n7_64": {"bytes_per_launch": 32730.8e6, "fetch": 19203.4e6, "write": 13527.3e6},
-    "tgv_n5_32": {"bytes_per_launch": 1830.1e6, "fetch": 1026.1e6, "write": 804.0e6},
-    "freestream_euler_n7_64": {"bytes_per_launch": 20719.6e6, "fetch": 11056.0e6, "write": 9663.7e6},
-    "tgv_curved_n5_32": {"bytes_per_launch": 2282.7e6, "fetch": 1473.6e6, "write": 809.1e6},
-    "channel_wm_n5_32": {"bytes_per_launch": 1818.1e6, "fetch": 1011.9e6, "write": 806.2e6},
-    "sod_ns_n4_256x16x16": {"bytes_per_launch": 2580.2e6, "fetch": 1569.1e6, "write": 1011.1e6},
-    "tgv_les_n5_32": {"bytes_per_launch": 1830.8e6, "fetch": 1026.0e6, "write": 804.8e6},
+    "kernel_sha": "94c9ef4621e6587d",
+    "tgv_n7_64": {"bytes_per_launch": 34708.0e6, "fetch": 20624.5e6, "write": 14083.6e6},
+    "tgv_n5_32": {"bytes_per_launch": 1905.1e6, "fetch": 1063.4e6, "write": 841.7e6},
+    "freestream_euler_n7_64": {"bytes_per_launch": 20719.7e6, "fetch": 11056.0e6, "write": 9663.7e6},
+    "tgv_curved_n5_32": {"bytes_per_launch": 2382.1e6, "fetch": 1482.6e6, "write": 899.5e6},
+    "channel_wm_n5_32": {"bytes_per_launch": 1887.1e6, "fetch": 1048.2e6, "write": 838.9e6},
+    "sod_ns_n4_256x16x16": {"bytes_per_launch": 2624.5e6, "fetch": 1570.1e6, "write": 1054.3e6},
+    "tgv_les_n5_32": {"bytes_per_launch": 1905.1e6, "fetch": 1063.3e6, "write": 841.7e6},
 }
 
 
@@ -138,14 +138,14 @@ MEASURED_TRAFFIC = {
 # stage launches of one step; profiles/k_stage_*.md); valid only for the
 # kernel source they were counted on (sha256 prefix).
 KERNEL_FLOPS = {
-    "kernel_sha": "c80a67d467d54fe2",
-    "tgv_n7_64": {"stage_flops_per_dof": 1202.5},
-    "tgv_n5_32": {"stage_flops_per_dof": 1303.7},
+    "kernel_sha": "94c9ef4621e6587d",
+    "tgv_n7_64": {"stage_flops_per_dof": 1241.7},
+    "tgv_n5_32": {"stage_flops_per_dof": 1352.1},
     "freestream_euler_n7_64": {"stage_flops_per_dof": 656.2},
-    "tgv_curved_n5_32": {"stage_flops_per_dof": 1934.8},
-    "channel_wm_n5_32": {"stage_flops_per_dof": 1369.0},
-    "sod_ns_n4_256x16x16": {"stage_flops_per_dof": 1277.5},
-    "tgv_les_n5_32": {"stage_flops_per_dof": 1345.2},
+    "tgv_curved_n5_32": {"stage_flops_per_dof": 1967.9},
+    "channel_wm_n5_32": {"stage_flops_per_dof": 1417.4},
+    "sod_ns_n4_256x16x16": {"stage_flops_per_dof": 1306.2},
+    "tgv_les_n5_32": {"stage_flops_per_dof": 1393.5},
 }
 
 

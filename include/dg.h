@@ -85,7 +85,8 @@ enum { DG_FP64 = 0, DG_MIXED = 1 };
  *     split into the element's own half, which the stage kernel adds and
  *     leaves at its face nodes, and the neighbour's half, which the next stage
  *     adds where it reads the state and the register (at the end of a call a
- *     completion kernel does).  Runs for every FP64 Navier-Stokes operator; with
+ *     completion kernel does); a state is rounded once per stage as with
+ *     TWO_PASS.  Runs for every FP64 Navier-Stokes operator; with
  *     the eddy viscosity, blending, walls or curved geometry both choices run
  *     it, and the mixed operator always runs TWO_PASS. */
 enum { DG_LIFT_TWO_PASS = 0, DG_LIFT_SPLIT = 1 };
@@ -252,7 +253,7 @@ int rk_step(dg_ctx* ctx, double* U, double dt);
 /* nsteps Runge-Kutta steps in place (same result as nsteps rk_step calls).
  * Where the split lifting runs (dg_options.lifting) rk_step, dg_rk_steps,
  * rk_step_record and rk_step_vjp allocate a second face buffer of
- * nElems * 6 * 4 * (N+1)^2 doubles on first use; elsewhere an odd number of
+ * nElems * (24 (N+1)^2 + (N+1)^3 / 2) doubles on first use; elsewhere an odd number of
  * steps allocates a third state where that is at most an eighth of the free
  * memory.  dg_set_options allocates either beforehand where it is at most an
  * eighth of the free memory.  Neither is allocated while the stream is captured, and without them

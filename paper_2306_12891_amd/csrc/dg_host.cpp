@@ -181,6 +181,7 @@ struct dg_ctx {
   int device = 0;
   const KernelTable* kt = nullptr;
   size_t nstate = 0;  // doubles per state
+  size_t face_bytes() const { return face_buffer(nelem, nf, nn) * sizeof(double); }  // Fvf, Fvf2
   int32_t* nbr = nullptr;
   double* basis = nullptr;
   double* G = nullptr;
@@ -397,7 +398,8 @@ bool streaming(const dg_ctx* c) {
   const bool deferred = deferred_on(c);
   size_t set = (deferred ? 3 : 4) * state;
   if (eq_code(c) != 0)
-    set += (deferred ? 2 : 1) * (size_t)c->nelem * 24 * c->nf * (c->opt.precision == DG_MIXED ? sizeof(float) : sizeof(double));
+    set += deferred ? 2 * c->face_bytes()
+                    : face_fluxes(c->nelem, c->nf) * (c->opt.precision == DG_MIXED ? sizeof(float) : sizeof(double));
   if (c->M) set += 2 * state;  // ten rows against five
   return set < 40000000u || set > 320000000u;
 }
@@ -425,7 +427,7 @@ bool capturing(dg_ctx* c) {
 
 void ensure_carry_buffer(dg_ctx* c, bool only_small = false) {
   if (!deferred_on(c) || c->Fvf2 || capturing(c)) return;
-  const size_t bytes = (size_t)c->nelem * 6 * 4 * c->nf * sizeof(double);
+  const size_t bytes = c->face_bytes();
   size_t avail = 0, total = 0;
   if (only_small && (hipMemGetInfo(&avail, &total) != hipSuccess || bytes > avail / 8)) return;
   if (hipMalloc((void**)&c->Fvf2, bytes) != hipSuccess) {
@@ -450,9 +452,11 @@ void ensure_third_state(dg_ctx* c) {
   }
 }
 
-// X = Xin + B S (X may be Xin), and G += S where given.
-int complete_state(dg_ctx* c, const double* Xin, double* X, const double* F, double B, double* G) {
+// X = Xin + B S (X may be Xin), with the remainders of a stage's state (MODE_RK; not
+// of U_t, MODE_UT), and G += S where given.
+int complete_state(dg_ctx* c, int mode, const double* Xin, double* X, const double* F, double B, double* G) {
   StageArgs a = stage_args(c);
+  a.mode = mode;
   a.U = Xin;
   a.G = G;
   a.Fcarry = F;
@@ -463,7 +467,7 @@ int complete_state(dg_ctx* c, const double* Xin, double* X, const double* F, dou
 
 // The state that a chain of stages left in cur, complete, in U.
 int settle(dg_ctx* c, const Carry& k, const double* cur, double* U, const char* where) {
-  if (k.state) return complete_state(c, cur, U, k.F, k.B, nullptr);
+  if (k.state) return complete_state(c, MODE_RK, cur, U, k.F, k.B, nullptr);
   if (cur != U) {
     const hipError_t e = hipMemcpyAsync(U, cur, c->nstate * sizeof(double), hipMemcpyDeviceToDevice, c->stream);
     if (e != hipSuccess) return hip_fail(c, e, where);
@@ -487,7 +491,7 @@ int run_stage(dg_ctx* c, const double* Xin, double* Xout, double* Ut, int mode, 
   Carry& k = carry ? *carry : none;
   if (k.F && (!c->Fvf2 || (k.state && c->M))) {
     if (k.state || !c->Fvf2) {
-      const int rc = complete_state(c, Xin, const_cast<double*>(Xin), k.F, k.B, c->Fvf2 ? nullptr : c->G);
+      const int rc = complete_state(c, MODE_RK, Xin, const_cast<double*>(Xin), k.F, k.B, c->Fvf2 ? nullptr : c->G);
       if (rc) return rc;
     }
     k.state = false;
@@ -537,7 +541,7 @@ int run_stage(dg_ctx* c, const double* Xin, double* Xout, double* Ut, int mode, 
     return mixed ? c->kt->stage_mixed(a, eq, c->stream) : c->kt->stage(a, eq, c->stream);
   });
   if (e != hipSuccess) return hip_fail(c, e, "stage kernel");
-  if (deferred && mode == MODE_UT) return complete_state(c, Ut, Ut, a.Fvf_out, 1.0, nullptr);
+  if (deferred && mode == MODE_UT) return complete_state(c, MODE_UT, Ut, Ut, a.Fvf_out, 1.0, nullptr);
   if (deferred && mode == MODE_RK) {
     k.F = a.Fvf_out;
     k.B = Bdt;
@@ -849,7 +853,7 @@ int dg_init(const dg_mesh* mesh, int N, double gamma, double mu, dg_ctx** out) {
   alloc((void**)&c->alpha1, (size_t)c->nelem * sizeof(double));
   alloc((void**)&c->alpha1b, (size_t)c->nelem * sizeof(double));
   alloc((void**)&c->alpha, (size_t)c->nelem * sizeof(double));
-  alloc((void**)&c->Fvf, (size_t)c->nelem * 6 * 4 * c->nf * sizeof(double));
+  alloc((void**)&c->Fvf, c->face_bytes());
   alloc((void**)&c->partial, kRedBlocks * 5 * sizeof(double));
   if (e == hipSuccess) e = hipHostMalloc((void**)&c->h_partial, kRedBlocks * 5 * sizeof(double), hipHostMallocDefault);
   if (e == hipSuccess) e = hipMemcpy(c->nbr, nbr.data(), nbr.size() * sizeof(int32_t), hipMemcpyHostToDevice);

@@ -26,6 +26,14 @@ struct BasisLayout {
   __host__ __device__ constexpr int size() const { return 4 * n1 * n1 + 4 * n1 + 1; }
 };
 
+// Doubles of a face buffer of the deferred exchange: normal viscous fluxes
+// [nelem][6][4][nf], then the packed remainders [nelem][nn], four bytes a node
+// (pack_remainders in the kernels).
+__host__ __device__ constexpr size_t face_fluxes(int nelem, int nf) { return (size_t)nelem * 24 * nf; }
+__host__ __device__ constexpr size_t face_buffer(int nelem, int nf, int nn) {
+  return face_fluxes(nelem, nf) + ((size_t)nelem * nn + 1) / 2;
+}
+
 struct StageArgs {
   const double* U;      // stage input state
   double* Uout;         // RK: output state (ping-pong, never aliases U)
@@ -71,9 +79,10 @@ struct StageArgs {
   // Deferred viscous exchange (FP64 Navier-Stokes; Fvf NULL): the stage kernel
   // adds its own half of the viscous surface term and writes its normal viscous
   // flux at its face nodes to Fvf_out, laid out as Fvf (wall faces: the wall
-  // model's flux, written there by wall_flux before it).  Fcarry: the fluxes the
-  // stage that wrote the input state and the register left there (NULL: both
-  // are complete); the register is completed with them, and with carryU != 0
+  // model's flux, written there by wall_flux before it), and in MODE_RK the
+  // remainders of its rounded output state behind them (face_buffer).  Fcarry:
+  // what the stage that wrote the input state and the register left there (NULL:
+  // both are complete); the register is completed with it, and with carryU != 0
   // the input state too, Bcarry being that stage's B_k dt.  Yout (or NULL):
   // the completed input state is also written there.
   const double* Fcarry;
@@ -144,8 +153,8 @@ struct KernelTable {
   hipError_t (*stage_mixed)(const StageArgs&, int eq, hipStream_t);
   hipError_t (*lift)(const StageArgs&, int eq, hipStream_t);
   hipError_t (*lift_mixed)(const StageArgs&, int eq, hipStream_t);
-  // X = U + Bcarry S with the carry S of Fcarry (X may be U), and G += S where
-  // G is set; box or curved
+  // X = U + Bcarry S with the carry S of Fcarry (X may be U) and, in MODE_RK, the
+  // remainders there; G += S where G is set; box or curved
   hipError_t (*complete)(const StageArgs&, double* X, hipStream_t);
   hipError_t (*alpha1)(const StageArgs&, hipStream_t);
   hipError_t (*spread)(const StageArgs&, hipStream_t);

@@ -429,11 +429,9 @@ __device__ __forceinline__ void surface_flux_dir(int d, int sf, const double L[5
 // ---------------------------------------------------------------------------
 // Volume integral along direction D for node n (index id along D).
 // ---------------------------------------------------------------------------
-// ROT: the N partners l != id of a node, fully unrolled, in an order in which
-// the lanes of a wave spread over the LDS banks and step m adds compile-time
-// offsets: l = id ^ m where N + 1 is a power of two, else l = line_order(m) where
-// id's own position comes first, line_order(m - 1) where it comes later.  The
-// coefficients Dhat_{id l} lie in LDS in the same order (sDhat[m][id], see
+// SKIP: the N partners l != id of a node in ascending order, fully unrolled, step
+// m adding compile-time offsets: l = m - 1 before the own position, m after it.
+// The coefficients Dhat_{id l} lie in LDS in the same order (sDhat[m][id], see
 // dhat_index).  Before each partner
 // tie(k, ic) makes the next indices depend on all running sums (an empty asm),
 // so that a partner's values are loaded only once the sums of the one before
@@ -446,26 +444,22 @@ __device__ __forceinline__ void surface_flux_dir(int d, int sf, const double L[5
 // line read in a step (most of them the same one) do at N = 5 and 6, where a
 // rotation l = (id + m) mod (N + 1) of every line loses more cycles to conflicts
 // than the omitted diagonal saves.  Cycles per wave and value at N = 5, sum over
-// directions: every l 75, rotated 80, this order 59.  At N = 4 (rows of 5) plain
-// ascending order conflicts along x (76; every l 70), the order 3 1 2 0 4 does
-// less (64).
-// Measured at 32^3: every l -> without the diagonal, Euler N = 7 step 3213 -> 3155
-// us; rotated -> this order, N = 5 Smagorinsky step 2320 -> 2284 us, N = 6 186 ->
-// 178 us (small mesh); blended Navier-Stokes N = 6 620 -> 606 us.
-constexpr bool kPow2 = (n1 & (n1 - 1)) == 0;
-// Line positions in the order in which partners are visited (its own inverse).
-__host__ __device__ constexpr int line_order(int m) { return N == 4 && (m == 0 || m == 3) ? 3 - m : m; }
-template <bool ROT, bool ROLLED, int ST, class R, class F, class T>
+// directions: every l 75, rotated 80, this order 59.  Measured at 32^3: rotated ->
+// this order, N = 5 Smagorinsky step 2320 -> 2284 us, N = 6 186 -> 178 us (small
+// mesh); blended Navier-Stokes N = 6 620 -> 606 us.
+// Orders with fewer conflicts at N = 3, 4 and 7 (id ^ m; 3 1 2 0 4) gain 1 to 3 % at
+// N = 3 only (Euler N = 7 32^3 2913 us with id ^ m, 2845 ascending; blended
+// Navier-Stokes N = 4 4084 with 3 1 2 0 4, 4075 ascending), and round otherwise than
+// sums in ascending order: relative difference to plain sums in 64 bits, U_t of a
+// density wave at N = 3, 3.5 % larger, one step of the shock tube at N = 4 2.5 %.
+template <bool SKIP, bool ROLLED, int ST, class R, class F, class T>
 __device__ __forceinline__ void partner_loop(int id, int n, const R* sDhat, F&& body, T&& tie) {
-  if (ROT) {
-    const int base = n - id * ST, pos = line_order(id);
+  if (SKIP) {
+    const int base = n - id * ST;
     int ic = id;
 #pragma unroll
     for (int m = 1; m <= N; ++m) {
-      const int la = line_order(m - 1), lb = line_order(m);
-      int k;
-      if (kPow2) k = n ^ (m * ST);
-      else k = (pos < m ? base + (lb - la) * ST : base) + la * ST;
+      int k = (id < m ? base + ST : base) + (m - 1) * ST;
       if (m == 1) asm volatile("" : "+v"(k), "+v"(ic));
       else tie(k, ic);
       body(sDhat[m * n1 + ic], k);
@@ -485,18 +479,17 @@ __device__ __forceinline__ void partner_loop(int id, int n, const R* sDhat, F&& 
   }
 }
 // Entry of the basis' Dhat block that belongs at position t < (N + 1)^2 of the
-// rotated table.
+// table by steps (step 0: the diagonal, not read).
 __device__ __forceinline__ int dhat_index(int t) {
   const int m = t / n1, id = t - m * n1;
-  if (kPow2) return id * n1 + (id ^ m);
-  return id * n1 + (m == 0 ? id : line_order(line_order(id) < m ? m : m - 1));
+  return id * n1 + (m == 0 ? id : (id < m ? m : m - 1));
 }
 
 // With GRAD, also returns gs[c] = sum_{l != id} Dw_{id l} q_c(l) along the line
 // (q = u, v, w, theta): the off-diagonal part of the BR1 gradient, which
 // reuses the partner values and coefficients the flux loop reads anyway
 // (off the diagonal Dw = D = Dhat / 2 exactly).
-template <int VF, int D, class R, bool GRAD, bool ROT>
+template <int VF, int D, class R, bool GRAD, bool SKIP>
 __device__ __forceinline__ void volume_dir(const R (*sP)[nnp], const R* sDhat, R wb, int n, int id, const R me[7],
                                            R invJ, R gm1, R acc[5], const R* sDw = nullptr, R* gs = nullptr) {
   constexpr int st = D == 0 ? 1 : (D == 1 ? n1 : nf);
@@ -545,7 +538,7 @@ __device__ __forceinline__ void volume_dir(const R (*sP)[nnp], const R* sDhat, R
       else asm volatile("" : "+v"(k), "+v"(ic), "+v"(s_A), "+v"(s_u), "+v"(s_v), "+v"(s_w), "+v"(s_x), "+v"(s_p));
       if (GRAD) asm volatile("" : "+v"(k), "+v"(g0), "+v"(g1), "+v"(g2), "+v"(g3));
     };
-    partner_loop<ROT, GRAD, st>(id, n, sDhat, pair, tie);
+    partner_loop<SKIP, GRAD, st>(id, n, sDhat, pair, tie);
     const R q4 = (R)0.25, q8 = (R)0.125, h2 = (R)0.5;
     R P = s_p;
     if (VF != VF_KG) {
@@ -576,7 +569,7 @@ __device__ __forceinline__ void volume_dir(const R (*sP)[nnp], const R* sDhat, R
       asm volatile("" : "+v"(k), "+v"(ic), "+v"(s0), "+v"(s1), "+v"(s2), "+v"(s3), "+v"(s4), "+v"(sp));
       if (GRAD) asm volatile("" : "+v"(k), "+v"(g0), "+v"(g1), "+v"(g2), "+v"(g3));
     };
-    partner_loop<ROT, GRAD, st>(id, n, sDhat, pair, tie);
+    partner_loop<SKIP, GRAD, st>(id, n, sDhat, pair, tie);
     const R rowsum = id == 0 ? wb : (id == N ? -wb : (R)0);
     const R mr = mA * rowsum;
     s0 += mr;
@@ -610,7 +603,7 @@ __device__ __forceinline__ void volume_dir(const R (*sP)[nnp], const R* sDhat, R
       s[4] = fma(c, f[4], s[4]);
     };
     auto tie = [&](int& k, int& ic) { asm volatile("" : "+v"(k), "+v"(ic), "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]), "+v"(s[4])); };
-    partner_loop<ROT, GRAD, st>(id, n, sDhat, pair, tie);
+    partner_loop<SKIP, GRAD, st>(id, n, sDhat, pair, tie);
     for (int v = 0; v < 5; ++v) acc[v] -= invJ * (R)s[v];
   }
   if (GRAD) {
@@ -949,7 +942,16 @@ __device__ __forceinline__ Slot slot_of_thread(int e0, int nelem) {
 // states it reads, u = u~ + B S, and the register, G = G~ + S, with F_nb of the
 // stage before (StageArgs.Fcarry), and k_complete does the same for a state
 // that is handed out.  S is formed from rounded products as (x + y) + z over the
-// directions and added by one fma, so every reader of a node gets the same bits.
+// directions, so every reader of a node gets the same bits.
+// A state value is rounded once per stage all the same: the stage also leaves the
+// remainder r of its own rounding, u~ + r = u + B_k dt G~, in bytes, and every
+// reader adds B S + r in one piece; u~ + B S alone would round a boundary node's
+// state a second time.  Relative error of one step against 64 bits without and with
+// the remainders (in brackets two-pass lifting, one rounding): Taylor-Green N = 5
+// 1.53e-16, 1.26e-16 (1.26e-16); wall-modelled channel N = 5 1.86e-16, 1.42e-16
+// (1.42e-16); viscous shock tube N = 4 1.58e-16, 0.72e-16 (0.71e-16).  They take 4 to
+// 5 % of a step: N = 7 64^3 40.5 -> 42.2 ms, N = 5 32^3 2320 -> 2420 us (bytes, because
+// with 16 bits, or at the face nodes instead of the nodes, 7 to 9 %).
 // A node of the neighbour's face needs, besides the element's own flux there,
 // those of the neighbour's lateral neighbours where it lies on an edge of the
 // face: on the structured box the element across the neighbour's lateral face
@@ -963,13 +965,74 @@ __device__ __forceinline__ double half_winv(const double* basis) {
   return 0.5 * ((cdouble_ptr)(uintptr_t)basis)[BL.winv()];
 }
 
+// What a rounded state update lost: r with s + r = u + b g, for s = fma(b, g, u).
+__device__ __forceinline__ double remainder_of(double u, double b, double g, double s) {
+#pragma clang fp contract(off)
+  const double d = s - u;
+  return (u - (s - d)) + fma(b, g, -d);
+}
+
+// Remainders are kept as bytes, biased by 128, in units of 2^-8 of s's last place
+// (|r| is at most half of that place; 128 units become 127): the low bits of the
+// mantissa of K + r, K = 1.5 x 2^52 + 128 such units.  s below 2^-1013 takes the
+// units of that.
+__device__ __forceinline__ int remainder_base(double s) {  // high word of K
+  return max(__double2hiint(s) & 0x7ff00000, 9 << 20) - (8 << 20) + (1 << 19);
+}
+constexpr unsigned kNoRemainders = 0x80808080u;
+
+__device__ __forceinline__ unsigned pack_remainders(const double s[4], const double r[4]) {
+#pragma clang fp contract(off)
+  unsigned w = 0;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const unsigned q = (unsigned)__double2loint(__hiloint2double(remainder_base(s[c]), 128) + r[c]);
+    w |= min(q, 255u) << (8 * c);
+  }
+  return w;
+}
+
+// The bytes of rows d, d + 1, d + 2 (mod 3) and 3, the order of a rotated state.
+__device__ __forceinline__ unsigned rotate_remainders(unsigned w, int d) {
+  const unsigned lo = __builtin_amdgcn_perm(w, w, 0x00020100u), hi = __builtin_amdgcn_perm(w, w, 0x00000201u);
+  return __builtin_amdgcn_perm(w, __builtin_amdgcn_alignbyte(hi, lo, (unsigned)d), 0x07020100u);
+}
+
+__device__ __forceinline__ double unpack_remainder(unsigned w, int c, double s) {
+#pragma clang fp contract(off)
+  const int hi = remainder_base(s);
+  return __hiloint2double(hi, (int)((w >> (8 * c)) & 0xffu)) - __hiloint2double(hi, 128);
+}
+
+// The completed value: u~ + (B S + r).
+__device__ __forceinline__ double carried(double u, double B, double S, unsigned rem, int c) {
+#pragma clang fp contract(off)
+  return u + fma(B, S, unpack_remainder(rem, c, u));
+}
+
+__device__ __forceinline__ bool on_boundary(const int ijk[3]) {
+  return ((unsigned)(ijk[0] - 1) >= N - 1u) | ((unsigned)(ijk[1] - 1) >= N - 1u) | ((unsigned)(ijk[2] - 1) >= N - 1u);
+}
+
+// The remainders behind the fluxes of a face buffer, one word a node.
+__device__ __forceinline__ const unsigned* remainders(const double* F, int nelem) {
+  return reinterpret_cast<const unsigned*>(F + face_fluxes(nelem, nf));
+}
+// Stores those of a state s (none at inner nodes, which await nothing).
+__device__ __forceinline__ void store_remainders(const StageArgs& A, int e, int t, const int ijk[3], const double* s,
+                                                 const double* r) {
+  const unsigned w = on_boundary(ijk) ? pack_remainders(s, r) : kNoRemainders;
+  put<1>(const_cast<unsigned*>(remainders(A.Fvf_out, A.nelem)) + (size_t)e * nn + t, 0, &w, A.stream);
+}
+
 // Carry loads of a face item: the neighbour's flux fn and the element's own fo
 // at the shared face, and those across the neighbour's lateral faces, fl[0]
 // along the lower tangential direction, fl[1] along the higher (rotated
 // components; weight cl, 0 where the node is not on that edge or the lateral
-// face is a wall).
+// face is a wall); the neighbour's remainders.
 struct CarryLoads {
   double fn[4], fo[4], fl[2][4], cl[2];
+  unsigned rem;
 };
 
 __device__ __forceinline__ void load_flux_rotated(const double* F, const FaceItem& it, double f[4]) {
@@ -984,6 +1047,7 @@ __device__ __forceinline__ void carry_issue(const StageArgs& A, const FaceItem& 
                                             bool nbrU, CarryLoads& c) {
   load_flux_rotated(A.Fcarry + ((size_t)it.nb * 6 + (it.f ^ 1)) * 4 * nf + it.a, it, c.fn);
   if (!nbrU) return;
+  c.rem = remainders(A.Fcarry, A.nelem)[(size_t)it.nb * nn + it.nnb];
   load_flux_rotated(A.Fcarry + ((size_t)e * 6 + it.f) * 4 * nf + it.a, it, c.fo);
   const int da = it.d == 0 ? 1 : 0, db = it.d == 2 ? 1 : 2;  // tangential directions, t1 along da
   const int t1 = it.a % n1, t2 = it.a / n1, ln = it.side ? 0 : N;  // ln: the neighbour's node along d
@@ -1017,11 +1081,12 @@ __device__ __forceinline__ void carry_neighbour(const StageArgs& A, const FaceIt
 #pragma clang fp contract(off)
   const double hw = half_winv(A.basis);
   const double cd = pick3(A.invJ, it.d) * (it.side ? -hw : hw);
+  const unsigned rem = rotate_remainders(c.rem, it.d);
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const double pd = cd * c.fo[k], pa = c.cl[0] * c.fl[0][k], pb = c.cl[1] * c.fl[1][k];
     const double S = ((it.d == 2 ? pb : pd) + pa) + (it.d == 2 ? pd : pb);
-    X[1 + k] = fma(A.Bcarry, S, X[1 + k]);
+    X[1 + k] = carried(X[1 + k], A.Bcarry, S, rem, k);
   }
 }
 
@@ -1317,7 +1382,7 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
   constexpr bool MX = sizeof(R) == 4;
   // the element's own face state comes through LDS (completed by the carry)
   constexpr bool OWN_LDS = DEFER && !BLEND;
-  constexpr bool ROT = !MX;  // partner order of the volume loop (the mixed bits stay)
+  constexpr bool SKIP = !MX;  // partner order of the volume loop (the mixed bits stay)
   constexpr bool LINES = N >= 5 && N % 2 == 1;  // viscous divergence by lines
   constexpr int SVP = LINES ? LineLayout<R>::SQP : nnp;        // its LDS row
   static_assert(!(BLEND && MX), "the blended operator is FP64 only");
@@ -1377,7 +1442,7 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
     for (int v = 0; v < 5; ++v) u[v] = Ue[v * nn + t];
   }
   static_assert(NB_STAGE <= PS::NTB, "one basis entry per thread");
-  const double bval = tid < NB_STAGE ? A.basis[ROT && tid < nf ? dhat_index(tid) : tid] : 0.0;
+  const double bval = tid < NB_STAGE ? A.basis[SKIP && tid < nf ? dhat_index(tid) : tid] : 0.0;
   // V^-1 for the indicator of the stage output (blended Euler runs)
   const double vval = (BLEND && !NS && kFusedAlpha1 && tid >= NB_STAGE && tid < NB_STAGE + nf) ? A.basis[tid] : 0.0;
   const Ref ref = MX ? reference_state(A.U, gm1) : Ref{0.0, 0.0, 0.0};
@@ -1385,6 +1450,8 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
 #pragma unroll
   for (int k = 0; k < FI; ++k)
     if (t + k * TPE < 6 * nf) face_issue<NS, R, WALL, DEFER, !OWN_LDS>(A, e, fd[k], nb6);
+  unsigned rem = kNoRemainders;
+  if (OWN_LDS && A.carryU && t < nn) rem = remainders(A.Fcarry, A.nelem)[(size_t)e * nn + t];
   if (tid < NB_STAGE) {
     sB[tid] = (R)bval;
     if (BLEND) sB64[tid] = bval;
@@ -1418,7 +1485,7 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
         if (t < nn) carry_own(sFn, A.invJ, hw, ijk, wmask, S);
       if (A.carryU && t < nn) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) u[1 + c] = fma(A.Bcarry, S[c], u[1 + c]);
+        for (int c = 0; c < 4; ++c) u[1 + c] = carried(u[1 + c], A.Bcarry, S[c], rem, c);
       }
     }
     if (t < nn) {
@@ -1488,9 +1555,9 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
   if (t < nn) {
     constexpr bool FG = NS && DG_FUSED_GRAD && !BLEND;
     R gs[3][4];
-    volume_dir<VF, 0, R, FG, ROT>(sP, sDhat, swinv[0], t, ijk[0], me, invJ[0], (R)gm1, acc, sDw, gs[0]);
-    volume_dir<VF, 1, R, FG, ROT>(sP, sDhat, swinv[0], t, ijk[1], me, invJ[1], (R)gm1, acc, sDw, gs[1]);
-    volume_dir<VF, 2, R, FG, ROT>(sP, sDhat, swinv[0], t, ijk[2], me, invJ[2], (R)gm1, acc, sDw, gs[2]);
+    volume_dir<VF, 0, R, FG, SKIP>(sP, sDhat, swinv[0], t, ijk[0], me, invJ[0], (R)gm1, acc, sDw, gs[0]);
+    volume_dir<VF, 1, R, FG, SKIP>(sP, sDhat, swinv[0], t, ijk[1], me, invJ[1], (R)gm1, acc, sDw, gs[1]);
+    volume_dir<VF, 2, R, FG, SKIP>(sP, sDhat, swinv[0], t, ijk[2], me, invJ[2], (R)gm1, acc, sDw, gs[2]);
     // one branch per direction: advective surface terms and, with the fused
     // gradient, the diagonal of Dw (zero inside) and the lifting terms
     const R qo[4] = {me[1], me[2], me[3], me[6]};
@@ -1709,15 +1776,19 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
 #pragma unroll
       for (int v = 0; v < 5; ++v) A.Ut[o + v * nn] = ut[v];
     } else {
+      double r[5];
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
         if (A.A != 0.0) ut[v] = A.A * gprev[v] + ut[v];
-        u[v] = u[v] + A.Bdt * ut[v];  // the stage output, kept for the indicator below
+        const double s = fma(A.Bdt, ut[v], u[v]);
+        if (DEFER) r[v] = remainder_of(u[v], A.Bdt, ut[v], s);
+        u[v] = s;  // the stage output, kept for the indicator below
       }
       // the register is read once, by this element's next stage; the state by
       // the next stage kernel
       if (A.writeG) put<5>(A.G + o, nn, ut, A.stream);
       put<5>(A.Uout + o, nn, u, A.stream);
+      if (DEFER) store_remainders(A, e, t, ijk, u + 1, r + 1);
     }
   }
   // Euler only: measured on the blended Navier-Stokes stage (N = 4, its
@@ -1983,8 +2054,9 @@ __global__ __launch_bounds__(256) void k_wall_flux(StageArgs A) {
   if (A.carryU) {  // complete the exchange node's momenta (density has no carry)
     double S[4];
     carry_node(A, e, it.nnb, S);
-    m1 = fma(A.Bcarry, pick3(S, it.k1 - 1), m1);
-    m2 = fma(A.Bcarry, pick3(S, it.k2 - 1), m2);
+    const unsigned rem = rotate_remainders(remainders(A.Fcarry, A.nelem)[(size_t)e * nn + it.nnb], it.d);
+    m1 = carried(m1, A.Bcarry, pick3(S, it.k1 - 1), rem, 1);
+    m2 = carried(m2, A.Bcarry, pick3(S, it.k2 - 1), rem, 2);
   }
   wall_model_flux(A, Ue[it.nown], Ue[it.nnb], m1, m2, p ? -1.0 : 1.0, g);
   double* out = A.Fvf_out + ((size_t)e * 6 + f) * 4 * nf + a;
@@ -3397,16 +3469,21 @@ __device__ __forceinline__ int load_carry(const StageArgs& A, int e, int t, doub
   return wmask;
 }
 
-// u += B S at the element's node; stores momentum and energy of the boundary
+// The remainders of node t that a completion adds (U_t has none).
+__device__ __forceinline__ unsigned completion_remainders(const StageArgs& A, int e, int t) {
+  return A.mode == MODE_RK ? remainders(A.Fcarry, A.nelem)[(size_t)e * nn + t] : kNoRemainders;
+}
+
+// u += B S + r at the element's node; stores momentum and energy of the boundary
 // nodes to out (in place), or the whole state (copy).
 __device__ __forceinline__ void complete_node(const StageArgs& A, const double (*sFn)[4][nf], int wmask,
-                                              const int ijk[3], double u[5], double* out, bool copy) {
-  const bool boundary = ijk[0] == 0 || ijk[0] == N || ijk[1] == 0 || ijk[1] == N || ijk[2] == 0 || ijk[2] == N;
+                                              const int ijk[3], unsigned rem, double u[5], double* out, bool copy) {
+  const bool boundary = on_boundary(ijk);
   if (boundary) {
     double S[4];
     carry_own(sFn, A.invJ, half_winv(A.basis), ijk, wmask, S);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) u[1 + c] = fma(A.Bcarry, S[c], u[1 + c]);
+    for (int c = 0; c < 4; ++c) u[1 + c] = carried(u[1 + c], A.Bcarry, S[c], rem, c);
   }
   if (copy) {
 #pragma unroll
@@ -3417,11 +3494,11 @@ __device__ __forceinline__ void complete_node(const StageArgs& A, const double (
   }
 }
 
-// X = U + B S (S: the carry of the stage that wrote U), with X = U or another
-// array, and with A.G its register G += S.  Bound by HBM: in place it reads and
-// writes the momentum and energy rows and reads the neighbours' fluxes, 64 +
-// 192/(N+1) B per node; with the copy of a state that ends in the other buffer
-// 80 + 192/(N+1) B.
+// X = U + B S + r (S: the carry of the stage that wrote U, r its remainders), with
+// X = U or another array, and with A.G its register G += S.  Bound by HBM: in place
+// it reads and writes the momentum and energy rows and reads the remainders and the
+// neighbours' fluxes, 68 + 192/(N+1) B per node; with the copy of a state that ends
+// in the other buffer 84 + 192/(N+1) B.
 __global__ __launch_bounds__(NT) void k_complete(StageArgs A, double* X) {
   __shared__ double sFn[6][4][nf];
   const int e = element_of_block(blockIdx.x, A.chunk);
@@ -3430,8 +3507,10 @@ __global__ __launch_bounds__(NT) void k_complete(StageArgs A, double* X) {
   const bool copy = X != A.U;
   const size_t o = (size_t)e * 5 * nn + t;
   double u[5];
+  unsigned rem = kNoRemainders;
   int ijk[3] = {0, 0, 0};
   if (t < nn) {
+    rem = completion_remainders(A, e, t);
 #pragma unroll
     for (int v = 0; v < 5; ++v)
       if (v > 0 || copy) u[v] = A.U[o + v * nn];
@@ -3442,7 +3521,7 @@ __global__ __launch_bounds__(NT) void k_complete(StageArgs A, double* X) {
   const int wmask = load_carry(A, e, t, sFn);
   __syncthreads();
   if (t >= nn) return;
-  complete_node(A, sFn, wmask, ijk, u, X + o, copy);
+  complete_node(A, sFn, wmask, ijk, rem, u, X + o, copy);
   if (A.G) {
     double S[4];
     carry_own(sFn, A.invJ, half_winv(A.basis), ijk, wmask, S);
@@ -3459,7 +3538,7 @@ __global__ __launch_bounds__(NT) void k_complete(StageArgs A, double* X) {
 // a1 = min(a0, a_max), 0 below a_min.
 // ---------------------------------------------------------------------------
 // FIX (blended Navier-Stokes): first completes the state in place with the
-// carry of the stage before (40 B + 192/(N+1) B read and 32 B written per node
+// carry of the stage before (44 B + 192/(N+1) B read and 32 B written per node
 // instead of a completion pass and an indicator pass).
 template <bool FIX>
 __global__ __launch_bounds__(NT) void k_alpha1(StageArgs A) {
@@ -3476,7 +3555,9 @@ __global__ __launch_bounds__(NT) void k_alpha1(StageArgs A) {
   int ijk[3] = {0, 0, 0};
   double qt = 0.0;
   double u[5];
+  unsigned rem = kNoRemainders;
   if (t < nn) {
+    if (FIX) rem = completion_remainders(A, e, t);
 #pragma unroll
     for (int v = 0; v < 5; ++v) u[v] = Ue[v * nn + t];
     ijk[0] = t % n1;
@@ -3486,7 +3567,7 @@ __global__ __launch_bounds__(NT) void k_alpha1(StageArgs A) {
   if (FIX) {
     const int wmask = load_carry(A, e, t, sFn);
     __syncthreads();
-    if (t < nn) complete_node(A, sFn, wmask, ijk, u, const_cast<double*>(Ue) + t, false);
+    if (t < nn) complete_node(A, sFn, wmask, ijk, rem, u, const_cast<double*>(Ue) + t, false);
   }
   if (t < nn) qt = indicator_q(u, A.gamma - 1.0);
   const double a1 = element_alpha1(A, sV, sq, st, sred, t, ijk, qt);
@@ -3836,7 +3917,9 @@ __global__ __launch_bounds__(NT) void k_complete_curved(StageArgs A, double* X) 
   const bool copy = X != A.U;
   const size_t o = (size_t)e * 5 * nn + t;
   double u[5], iJ = 0.0;
+  unsigned rem = kNoRemainders;
   if (t < nn) {
+    rem = completion_remainders(A, e, t);
 #pragma unroll
     for (int v = 0; v < 5; ++v)
       if (v > 0 || copy) u[v] = A.U[o + v * nn];
@@ -3851,13 +3934,13 @@ __global__ __launch_bounds__(NT) void k_complete_curved(StageArgs A, double* X) 
   __syncthreads();
   if (t >= nn) return;
   const int ijk[3] = {t % n1, (t / n1) % n1, t / nf};
-  const bool boundary = ijk[0] == 0 || ijk[0] == N || ijk[1] == 0 || ijk[1] == N || ijk[2] == 0 || ijk[2] == N;
+  const bool boundary = on_boundary(ijk);
   if (!boundary && !copy) return;
   double S[4];
   carry_own_curved(sFn, 2.0 * half_winv(A.basis), ijk, S);
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
-    u[1 + c] = fma(A.Bcarry, iJ * S[c], u[1 + c]);
+    u[1 + c] = carried(u[1 + c], A.Bcarry, iJ * S[c], rem, c);
     X[o + (1 + c) * nn] = u[1 + c];
     if (A.G && boundary) A.G[o + (1 + c) * nn] = fma(iJ, S[c], A.G[o + (1 + c) * nn]);
   }
@@ -4225,16 +4308,19 @@ __global__ __launch_bounds__(NT, N == 5 || N == 6 ? 3 : 1) void k_stage_curved(S
 #pragma unroll
       for (int v = 0; v < 5; ++v) A.Ut[o + v * nn] = acc[v] * iJ;
     } else {
-      double gv[5];
+      double gv[5], r[5];
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
         const double ut = acc[v] * iJ;
         gv[v] = ut;
         if (A.A != 0.0) gv[v] = A.A * gprev[v] + ut;
-        u[v] = u[v] + A.Bdt * gv[v];
+        const double s = fma(A.Bdt, gv[v], u[v]);
+        if (NS) r[v] = remainder_of(u[v], A.Bdt, gv[v], s);
+        u[v] = s;
       }
       if (A.writeG) put<5>(A.G + o, nn, gv, A.stream);
       put<5>(A.Uout + o, nn, u, A.stream);
+      if (NS) store_remainders(A, e, t, ijk, u + 1, r + 1);
     }
   }
 }
