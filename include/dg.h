@@ -255,9 +255,10 @@ int rk_step(dg_ctx* ctx, double* U, double dt);
  * rk_step_record and rk_step_vjp allocate a second face buffer of
  * nElems * (24 (N+1)^2 + (N+1)^3 / 2) doubles on first use; elsewhere an odd number of
  * steps allocates a third state where that is at most an eighth of the free
- * memory.  dg_set_options allocates either beforehand where it is at most an
- * eighth of the free memory.  Neither is allocated while the stream is captured, and without them
- * (no memory, capture) the calls take an extra pass with the same results. */
+ * memory.  dg_set_options allocates either beforehand, on the context's device,
+ * where it is at most an eighth of the free memory.  Neither is allocated while
+ * the context's stream is captured (set it first, dg_set_stream), and without
+ * them (no memory, capture) the calls take an extra pass with the same results. */
 int dg_rk_steps(dg_ctx* ctx, double* U, double dt, int nsteps);
 
 /* Vector-Jacobian product of the operator: U_bar = (dL/dU)^T Ut_bar (the

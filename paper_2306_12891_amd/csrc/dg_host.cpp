@@ -414,10 +414,7 @@ struct Carry {
   bool state = false;
 };
 
-// The second face buffer, which lets a stage read the fluxes of the stage
-// before while it writes its own.  Without it (no memory, or the stream is
-// being captured and the first call did not come before) every stage completes
-// its state and register by a pass of its own: the same results.
+// Whether the context's stream is being captured (or cannot be asked).
 bool capturing(dg_ctx* c) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(c->stream, &st) == hipSuccess && st == hipStreamCaptureStatusNone) return false;
@@ -425,15 +422,36 @@ bool capturing(dg_ctx* c) {
   return true;
 }
 
+// A buffer that a call can do without: *p stays NULL if there is no memory, or
+// (eighth) if it would take more than an eighth of the free memory.  On the
+// context's device, whichever is current: dg_set_options launches nothing and may
+// be called with another.  And legal while some other stream is captured, which
+// else forbids allocations to this thread and would break that capture.
+void try_alloc(const dg_ctx* c, double** p, size_t bytes, bool eighth) {
+  int dev = c->device;
+  (void)hipGetDevice(&dev);
+  if (dev != c->device && hipSetDevice(c->device) != hipSuccess) {
+    (void)hipGetLastError();
+    return;
+  }
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  size_t avail = 0, total = 0;
+  if ((!eighth || (hipMemGetInfo(&avail, &total) == hipSuccess && bytes <= avail / 8)) &&
+      hipMalloc((void**)p, bytes) != hipSuccess)
+    *p = nullptr;
+  if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (dev != c->device) (void)hipSetDevice(dev);
+  (void)hipGetLastError();
+}
+
+// The second face buffer, which lets a stage read the fluxes of the stage
+// before while it writes its own.  Without it (no memory, or the stream is
+// being captured and the first call did not come before) every stage completes
+// its state and register by a pass of its own: the same results.
 void ensure_carry_buffer(dg_ctx* c, bool only_small = false) {
   if (!deferred_on(c) || c->Fvf2 || capturing(c)) return;
-  const size_t bytes = c->face_bytes();
-  size_t avail = 0, total = 0;
-  if (only_small && (hipMemGetInfo(&avail, &total) != hipSuccess || bytes > avail / 8)) return;
-  if (hipMalloc((void**)&c->Fvf2, bytes) != hipSuccess) {
-    (void)hipGetLastError();
-    c->Fvf2 = nullptr;
-  }
+  try_alloc(c, &c->Fvf2, c->face_bytes(), only_small);
 }
 
 // The third state of an odd number of stages: U -> U2 -> U3 -> U and then U and
@@ -443,13 +461,7 @@ void ensure_carry_buffer(dg_ctx* c, bool only_small = false) {
 // most an eighth of the free memory; without it the copy remains.
 void ensure_third_state(dg_ctx* c) {
   if (c->U3 || deferred_on(c) || capturing(c)) return;
-  const size_t bytes = c->nstate * sizeof(double);
-  size_t avail = 0, total = 0;
-  if (hipMemGetInfo(&avail, &total) != hipSuccess || bytes > avail / 8 ||
-      hipMalloc((void**)&c->U3, bytes) != hipSuccess) {
-    (void)hipGetLastError();
-    c->U3 = nullptr;
-  }
+  try_alloc(c, &c->U3, c->nstate * sizeof(double), true);
 }
 
 // X = Xin + B S (X may be Xin), with the remainders of a stage's state (MODE_RK; not

@@ -152,6 +152,7 @@ class DG:
             if not hasattr(o, k):
                 raise KeyError(k)
             setattr(o, k, v)
+        self._stream()  # it may allocate, but not while that stream is captured
         self._check(lib().dg_set_options(self._ctx, ctypes.byref(o)))
         self.options = o
 
