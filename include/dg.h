@@ -258,7 +258,10 @@ int rk_step(dg_ctx* ctx, double* U, double dt);
  * memory.  dg_set_options allocates either beforehand, on the context's device,
  * where it is at most an eighth of the free memory.  Neither is allocated while
  * the context's stream is captured (set it first, dg_set_stream), and without
- * them (no memory, capture) the calls take an extra pass with the same results. */
+ * them (no memory, capture) the calls take an extra pass with the same results;
+ * a call that could not get one does not ask again until the options, geometry,
+ * walls or coefficients are set.  Both stay until dg_finalize (captured steps
+ * hold their addresses). */
 int dg_rk_steps(dg_ctx* ctx, double* U, double dt, int nsteps);
 
 /* Vector-Jacobian product of the operator: U_bar = (dL/dU)^T Ut_bar (the

@@ -192,6 +192,9 @@ struct dg_ctx {
   double* alpha = nullptr;
   double* Fvf = nullptr;
   double* Fvf2 = nullptr;  // deferred viscous exchange: the other of the pair (allocated on first use)
+  // a step call could not get Fvf2 / U3: not asked for again until a call that
+  // changes the operator (a driver query or a failing allocation in every step)
+  bool no_Fvf2 = false, no_U3 = false;
   double* cs_field = nullptr;  // per-element Smagorinsky coefficients (dg_set_cs_field)
   int has_cs_field = 0;
   double* M = nullptr;         // curved mesh metrics [nelem][10][nn] (dg_set_geometry), NULL: box
@@ -449,9 +452,10 @@ void try_alloc(const dg_ctx* c, double** p, size_t bytes, bool eighth) {
 // before while it writes its own.  Without it (no memory, or the stream is
 // being captured and the first call did not come before) every stage completes
 // its state and register by a pass of its own: the same results.
-void ensure_carry_buffer(dg_ctx* c, bool only_small = false) {
-  if (!deferred_on(c) || c->Fvf2 || capturing(c)) return;
-  try_alloc(c, &c->Fvf2, c->face_bytes(), only_small);
+void ensure_carry_buffer(dg_ctx* c) {
+  if (!deferred_on(c) || c->Fvf2 || c->no_Fvf2 || capturing(c)) return;
+  try_alloc(c, &c->Fvf2, c->face_bytes(), false);
+  c->no_Fvf2 = !c->Fvf2;
 }
 
 // The third state of an odd number of stages: U -> U2 -> U3 -> U and then U and
@@ -460,8 +464,23 @@ void ensure_carry_buffer(dg_ctx* c, bool only_small = false) {
 // completion at the end of the call goes from U2 to U.  Taken only where it is at
 // most an eighth of the free memory; without it the copy remains.
 void ensure_third_state(dg_ctx* c) {
-  if (c->U3 || deferred_on(c) || capturing(c)) return;
+  if (c->U3 || deferred_on(c) || c->no_U3 || capturing(c)) return;
   try_alloc(c, &c->U3, c->nstate * sizeof(double), true);
+  c->no_U3 = !c->U3;
+}
+
+// At set-up (the options): the buffer of the first step, where it is small
+// against the free memory; else that step tries.
+void prepare_step_buffer(dg_ctx* c) {
+  if (capturing(c)) return;
+  if (!deferred_on(c) && !c->U3) try_alloc(c, &c->U3, c->nstate * sizeof(double), true);
+  if (deferred_on(c) && !c->Fvf2) try_alloc(c, &c->Fvf2, c->face_bytes(), true);
+}
+
+// After a change of the operator: the next step may ask for its buffer again.
+int operator_changed(dg_ctx* c) {
+  c->no_Fvf2 = c->no_U3 = false;
+  return DG_OK;
 }
 
 // X = Xin + B S (X may be Xin), with the remainders of a stage's state (MODE_RK; not
@@ -925,11 +944,8 @@ int dg_set_options(dg_ctx* c, const dg_options* o) {
     if (rc) return rc;
   }
   c->opt = *o;
-  // the buffers of the first step, where they are small against the free memory
-  // (else that step allocates them): they belong to the set-up
-  ensure_third_state(c);
-  ensure_carry_buffer(c, true);
-  return DG_OK;
+  prepare_step_buffer(c);
+  return operator_changed(c);
 }
 
 int dg_set_connectivity(dg_ctx* c, const int32_t* conn) {
@@ -983,7 +999,7 @@ int dg_set_wall_model(dg_ctx* c, int wall_dir, double u_inf, double ma_inf) {
   c->wall_dir = wall_dir;
   c->wm_uinf = wall_dir >= 0 && ma_inf > 0.0 ? u_inf : 1.0;
   c->wm_mainf = wall_dir >= 0 ? ma_inf : 0.0;
-  return DG_OK;
+  return operator_changed(c);
 }
 
 int dg_set_geometry(dg_ctx* c, const double* X) {
@@ -993,7 +1009,7 @@ int dg_set_geometry(dg_ctx* c, const double* X) {
     c->M = nullptr;
     hipFree(c->d2e);
     c->d2e = nullptr;
-    return DG_OK;
+    return operator_changed(c);
   }
   if (!is_device_ptr(X)) return fail(c, DG_EINVAL, "dg_set_geometry: X must be a device pointer");
   if (c->wall_dir >= 0) return fail(c, DG_EUNSUPPORTED, "dg_set_geometry: walls are built for the Cartesian box");
@@ -1025,14 +1041,14 @@ int dg_set_geometry(dg_ctx* c, const double* X) {
   c->M = M;
   hipFree(c->d2e);
   c->d2e = d2;
-  return DG_OK;
+  return operator_changed(c);
 }
 
 int dg_set_cs_field(dg_ctx* c, const double* cs) {
   if (check_ctx(c)) return DG_EINVAL;
   if (!cs) {
     c->has_cs_field = 0;
-    return DG_OK;
+    return operator_changed(c);
   }
   if (!is_device_ptr(cs)) return fail(c, DG_EINVAL, "dg_set_cs_field: cs must be a device pointer");
   if (c->opt.vol_flux == DG_VF_CH)
@@ -1046,7 +1062,7 @@ int dg_set_cs_field(dg_ctx* c, const double* cs) {
     return fail(c, (e == hipErrorOutOfMemory) ? DG_ENOMEM : DG_EHIP, "dg_set_cs_field: %s", hipGetErrorString(e));
   }
   c->has_cs_field = 1;
-  return DG_OK;
+  return operator_changed(c);
 }
 
 int dg_get_options(const dg_ctx* c, dg_options* o) {

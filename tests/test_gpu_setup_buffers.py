@@ -1,5 +1,6 @@
 """The buffers that dg_set_options takes beforehand: options may change inside
-the capture of a stream, whether the library was told of that stream or not."""
+the capture of a stream, whether the library was told of that stream or not; a
+buffer that a step could not get is not asked for in every later step."""
 import ctypes
 
 import pytest
@@ -42,3 +43,29 @@ def test_options_inside_a_capture(torch_cuda, told, equations):  # noqa: F811
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(U, want)
+
+
+def test_refused_buffer_is_not_asked_for_again(torch_cuda):  # noqa: F811
+    """The third state is taken where it is at most an eighth of the free memory;
+    a step that found less does not look again, until the options are set."""
+    torch = torch_cuda
+    from paper_2306_12891_amd import dg
+    N, nelem = 7, (24, 24, 24)
+    op = dg.DG(nelem, N, gamma=G)
+    U = torch.from_numpy(I.density_wave(N, nelem)).cuda()
+    state = U.numel() * 8
+    op.time_derivative(U)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    free = lambda: (torch.cuda.synchronize(), torch.cuda.mem_get_info()[0])[1]  # noqa: E731
+    rest = torch.empty(free() - 4 * state, dtype=torch.uint8, device="cuda")
+    before = free()
+    op.rk_step(U, 1e-4)
+    assert before - free() < state // 2
+    del rest
+    torch.cuda.empty_cache()
+    before = free()
+    op.rk_step(U, 1e-4)
+    assert before - free() < state // 2
+    op.set_options()
+    assert before - free() >= state
