@@ -121,14 +121,14 @@ def domain(name):
 # profiles/k_stage_*.md.
 # Valid only for the kernel source they were taken on (sha256 prefix).
 MEASURED_TRAFFIC = {
-    "kernel_sha": "94c9ef4621e6587d",
-    "tgv_n7_64": {"bytes_per_launch": 34708.0e6, "fetch": 20624.5e6, "write": 14083.6e6},
-    "tgv_n5_32": {"bytes_per_launch": 1905.1e6, "fetch": 1063.4e6, "write": 841.7e6},
-    "freestream_euler_n7_64": {"bytes_per_launch": 20719.7e6, "fetch": 11056.0e6, "write": 9663.7e6},
-    "tgv_curved_n5_32": {"bytes_per_launch": 2382.1e6, "fetch": 1482.6e6, "write": 899.5e6},
-    "channel_wm_n5_32": {"bytes_per_launch": 1887.1e6, "fetch": 1048.2e6, "write": 838.9e6},
-    "sod_ns_n4_256x16x16": {"bytes_per_launch": 2624.5e6, "fetch": 1570.1e6, "write": 1054.3e6},
-    "tgv_les_n5_32": {"bytes_per_launch": 1905.1e6, "fetch": 1063.3e6, "write": 841.7e6},
+    "kernel_sha": "61bde5543d213c91",
+    "tgv_n7_64": {"bytes_per_launch": 34712.7e6, "fetch": 20639.5e6, "write": 14073.2e6},
+    "tgv_n5_32": {"bytes_per_launch": 1900.3e6, "fetch": 1063.5e6, "write": 836.9e6},
+    "freestream_euler_n7_64": {"bytes_per_launch": 20719.7e6, "fetch": 11056.1e6, "write": 9663.7e6},
+    "tgv_curved_n5_32": {"bytes_per_launch": 2381.5e6, "fetch": 1482.5e6, "write": 898.9e6},
+    "channel_wm_n5_32": {"bytes_per_launch": 1883.4e6, "fetch": 1048.2e6, "write": 835.2e6},
+    "sod_ns_n4_256x16x16": {"bytes_per_launch": 2622.9e6, "fetch": 1570.0e6, "write": 1052.9e6},
+    "tgv_les_n5_32": {"bytes_per_launch": 1899.5e6, "fetch": 1063.3e6, "write": 836.2e6},
 }
 
 
@@ -138,7 +138,7 @@ MEASURED_TRAFFIC = {
 # stage launches of one step; profiles/k_stage_*.md); valid only for the
 # kernel source they were counted on (sha256 prefix).
 KERNEL_FLOPS = {
-    "kernel_sha": "94c9ef4621e6587d",
+    "kernel_sha": "61bde5543d213c91",
     "tgv_n7_64": {"stage_flops_per_dof": 1241.7},
     "tgv_n5_32": {"stage_flops_per_dof": 1352.1},
     "freestream_euler_n7_64": {"stage_flops_per_dof": 656.2},

@@ -83,15 +83,15 @@ struct StageArgs {
   // remainders of its rounded output state behind them (face_buffer).  Fcarry:
   // what the stage that wrote the input state and the register left there (NULL:
   // both are complete); the register is completed with it, and with carryU != 0
-  // the input state too, Bcarry being that stage's B_k dt.  Yout (or NULL):
-  // the completed input state is also written there.
+  // (the unblended box: always) the input state too, Bcarry being that stage's
+  // B_k dt.  Yout (or NULL): the completed input state is also written there.
   const double* Fcarry;
   double* Fvf_out;
   double* Yout;
   double Bcarry;
   int carryU;
-  // values read once, by the next launch, bypass the caches (meshes whose data
-  // do not fit the Infinity Cache)
+  // values read once, by the next launch, bypass the caches (streaming() on the
+  // host: meshes whose data exceed the Infinity Cache or fit the L2s)
   int stream;
 };
 

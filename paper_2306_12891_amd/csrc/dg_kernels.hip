@@ -3,7 +3,8 @@
 // translation unit exports dgmi::table_N<N>() with its launchers.
 //
 // Work decomposition: one workgroup per element, one thread per node
-// ((N+1)^3 nodes, rounded up to whole 64-wide wavefronts).  The element's
+// ((N+1)^3 nodes, rounded up to whole 64-wide wavefronts; at N = 3 and 4, where
+// the six faces have more nodes, mostly one per face node).  The element's
 // state is staged through LDS as primitive variables; face fluxes are
 // computed by the workgroup for all six faces of its element from its own
 // face layer and the neighbour's (read from global memory, mostly L2/MALL
@@ -12,9 +13,11 @@
 // order and the same code, which gives bitwise-identical interface fluxes and
 // hence discrete conservation to round-off.
 //
-// The Navier-Stokes stage kernel is bound by LDS traffic and issue rate (each
-// about two thirds busy at N = 5 and 7), with HBM close behind (258 B per node at
-// 4.2 TB/s at N = 5): the BR1 gradient is accumulated inside the split-form
+// The Navier-Stokes stage kernel is bound by LDS traffic and issue rate (0.55 to
+// 0.75 busy at N = 5 and 7) and by the latency between its load, compute and store
+// phases, which few workgroups per CU overlap: 269 B per node at 3.8 TB/s at N = 5,
+// 259 B at 4.3 TB/s at N = 7, where the completion kernel streams at 6.4 to 6.9 TB/s.
+// The BR1 gradient is accumulated inside the split-form
 // partner loop (off the diagonal Dw = Dhat / 2, so partner values and
 // coefficients are shared), the twelve viscous-flux components are exchanged
 // through LDS once, partners and LDS rows are ordered for the banks, and all
@@ -71,9 +74,7 @@ constexpr BasisLayout BL(n1);
 constexpr int NB_STAGE = 2 * n1 * n1 + 3 * n1 + 1;  // Dhat, Dw, winv, xi, edge
 
 // Accumulate the BR1 gradient inside the split-form volume loop, reusing its
-// partner values and coefficients (1), or in a separate pass (0).  The fused
-// loop is kept rolled: fully unrolled, the partner loads in flight need more
-// than 200 registers.
+// partner values and coefficients (1), or in a separate pass (0).
 #ifndef DG_FUSED_GRAD
 #define DG_FUSED_GRAD 1
 #endif
@@ -509,9 +510,8 @@ __device__ __forceinline__ void volume_dir(const R (*sP)[nnp], const R* sDhat, R
     //   sum_l c_l (p_n + p_l) = p_n rowsum + sum_l c_l p_l,
     // rowsum = sum_l Dhat_{id l} (1/w_0 in row 0, -1/w_N in row N, 0 inside).
     // Then f_rho = A/4, f_m = (u_n A + s_u)/8 + P/2 e_D, f_E = (x_n A + s_x)/8
-    // (+ sum_l c_l (p_n + p_l)(und_n + und_l)/4 for KG).  Every partner
-    // including l = id (Dhat has a zero diagonal) is visited with a
-    // compile-time offset from the line start.
+    // (+ sum_l c_l (p_n + p_l)(und_n + und_l)/4 for KG); l = id, the zero
+    // diagonal of Dhat, adds nothing (partner_loop).
     const R und_n = me[1 + D];
     R s_A = 0, s_u = 0, s_v = 0, s_w = 0, s_x = 0, s_p = 0, s_E2 = 0;
     auto pair = [&](R c, int m) {
@@ -733,9 +733,11 @@ struct FaceItem {
 // the face-state loads that need them); pick() selects face f's.
 struct Nbr6 {
   int n[6];
-  __device__ __forceinline__ int pick(int f) const {  // selects, not an indexed (scratch) array
+  // selects of values, not of addresses in an indexed (scratch or LDS) array
+  __device__ __forceinline__ int pick(int f) const {
+    const int b0 = n[0], b1 = n[1], b2 = n[2], b3 = n[3], b4 = n[4], b5 = n[5];
     const bool odd = (f & 1) != 0;
-    const int a01 = odd ? n[1] : n[0], a23 = odd ? n[3] : n[2], a45 = odd ? n[5] : n[4];
+    const int a01 = odd ? b1 : b0, a23 = odd ? b3 : b2, a45 = odd ? b5 : b4;
     return f < 2 ? a01 : (f < 4 ? a23 : a45);
   }
 };
@@ -875,17 +877,14 @@ __device__ __forceinline__ void wall_face_loads(const double* U, int e, const Fa
   else L[1] = -X[1];
 }
 
-// Elements per workgroup (EPB) of the stage and lifting kernels.  With one
-// element per workgroup, N = 5 fills 216 of 256 lanes (the last wave is 3/8
-// full) and a wave instruction costs the same whatever its active lanes; two
-// elements fill 432 of 448.  Each element owns a slot of TPE consecutive
-// threads (node t and face item t of slot s is thread s TPE + t); the slots
-// share the basis in LDS and every barrier.  Measured at N = 5: the lifting
-// kernel gains 6 % with two elements; the stage kernel loses 17 % (its LDS then
-// admits two workgroups per CU instead of four), so it keeps one.
-#ifndef DG_EPB_STAGE
-#define DG_EPB_STAGE 1
-#endif
+// Elements per workgroup (EPB): one in the stage kernel, one or two in the
+// lifting kernel.  With one element per workgroup, N = 5 fills 216 of 256 lanes
+// (the last wave is 3/8 full) and a wave instruction costs the same whatever its
+// active lanes; two elements fill 432 of 448.  Each element owns a slot of TPE
+// consecutive threads (node t and face item t of slot s is thread s TPE + t); the
+// slots share the basis in LDS and every barrier.  Measured at N = 5: the lifting
+// kernel gains 6 % with two elements; the stage kernel lost 17 % (its LDS then
+// admits two workgroups per CU instead of four).
 #ifndef DG_EPB_LIFT
 #define DG_EPB_LIFT (DG_N == 5 ? 2 : 1)
 #endif
@@ -907,7 +906,7 @@ struct Pack {
   static_assert(E >= 1 && NTB <= 1024, "workgroup size");
 };
 template <int EQ, bool BLEND>
-using PSK = Pack<DG_EPB_STAGE, !(BLEND && EQ == 0)>;
+using PSK = Pack<1, !(BLEND && EQ == 0)>;
 using PL = Pack<DG_EPB_LIFT, true>;
 
 // Slot of the calling thread: element e (clamped to a valid one), its thread
@@ -915,8 +914,7 @@ using PL = Pack<DG_EPB_LIFT, true>;
 // face items) for threads without an element: the padding of the last wave
 // and the second slot of a workgroup past the last element.
 struct Slot {
-  int s, e, t, traw;
-  bool live;
+  int s, e, t;
 };
 template <class P>
 __device__ __forceinline__ Slot slot_of_thread(int e0, int nelem) {
@@ -924,10 +922,9 @@ __device__ __forceinline__ Slot slot_of_thread(int e0, int nelem) {
   const int tid = threadIdx.x;
   const int s0 = P::EPB == 1 ? 0 : tid / P::TPE;
   r.s = s0 < P::EPB ? s0 : P::EPB - 1;
-  r.live = s0 < P::EPB && e0 + r.s < nelem;
-  r.e = r.live ? e0 + r.s : e0;
-  r.traw = tid - s0 * P::TPE;
-  r.t = r.live ? r.traw : P::TPE;
+  const bool live = s0 < P::EPB && e0 + r.s < nelem;
+  r.e = live ? e0 + r.s : e0;
+  r.t = live ? tid - s0 * P::TPE : P::TPE;
   return r;
 }
 
@@ -1042,11 +1039,9 @@ __device__ __forceinline__ void load_flux_rotated(const double* F, const FaceIte
   f[3] = F[3 * nf];
 }
 
-// nbrU: the states read need the carry too (else only fn, for the register).
 __device__ __forceinline__ void carry_issue(const StageArgs& A, const FaceItem& it, const Nbr6 nb6, int e,
-                                            bool nbrU, CarryLoads& c) {
+                                            CarryLoads& c) {
   load_flux_rotated(A.Fcarry + ((size_t)it.nb * 6 + (it.f ^ 1)) * 4 * nf + it.a, it, c.fn);
-  if (!nbrU) return;
   c.rem = remainders(A.Fcarry, A.nelem)[(size_t)it.nb * nn + it.nnb];
   load_flux_rotated(A.Fcarry + ((size_t)e * 6 + it.f) * 4 * nf + it.a, it, c.fo);
   const int da = it.d == 0 ? 1 : 0, db = it.d == 2 ? 1 : 2;  // tangential directions, t1 along da
@@ -1140,7 +1135,7 @@ __device__ __forceinline__ void face_issue(const StageArgs& A, int e, FaceData<N
       return;
     }
     load_rotated(A.U + (size_t)it.nb * 5 * nn, it.nnb, it, fd.X);
-    if (A.Fcarry) carry_issue(A, it, nb6, e, A.carryU, fd.c);
+    if (A.Fcarry) carry_issue(A, it, nb6, e, fd.c);
   } else {
     if (WALL && it.nb < 0) {
       wall_face_loads(A.U, e, it, fd.L, fd.R_);
@@ -1284,7 +1279,7 @@ __device__ __forceinline__ double element_alpha1(const StageArgs& A, const doubl
 // The blended Euler stage kernel's epilogue computes the next stage's first
 // coefficient (StageArgs.alpha1_next) when its LDS pool holds the indicator's
 // scratch and one pass of threads loads the basis with V^-1.
-constexpr bool kFusedAlpha1 = N >= 2 && DG_EPB_STAGE == 1 && 7 * nnp + 30 * nf >= 2 * nn + 3 * NWAVE &&
+constexpr bool kFusedAlpha1 = N >= 2 && 7 * nnp + 30 * nf >= 2 * nn + 3 * NWAVE &&
                                NB_STAGE + nf <= NT;
 
 // Viscous fluxes at a node from its lifted gradient g (with the Smagorinsky
@@ -1403,18 +1398,15 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
   constexpr int UROW = UPAD ? nn + nn / 16 : nn;
   static_assert(!OWN_LDS || 5 * UROW <= 54 * nf, "sU in the space of sF and sQ");
   using PS = PSK<EQ, BLEND>;
-  constexpr int EPB = PS::EPB, TPE = PS::TPE, FI = PS::FI;
-  __shared__ R sPoolAll[EPB][POOL];
+  constexpr int TPE = PS::TPE, FI = PS::FI;
+  __shared__ R sPool[POOL];
   __shared__ R sB[NB_STAGE];
-  __shared__ double sXAll[EPB][BLEND ? 5 : 1][BLEND ? nn : 1];
+  __shared__ double sX[BLEND ? 5 : 1][BLEND ? nn : 1];
   __shared__ double sB64[BLEND ? NB_STAGE + nf : 1];  // with V^-1 (Vinv follows edge in the basis)
 
-  const int e0 = EPB * element_of_block(blockIdx.x, A.chunk);
-  if (e0 >= A.nelem) return;  // uniform over the workgroup
-  const Slot sl = slot_of_thread<PS>(e0, A.nelem);
-  const int e = sl.e, t = sl.t, tid = threadIdx.x;
-  R* sPool = sPoolAll[sl.s];
-  double (*sX)[BLEND ? nn : 1] = sXAll[sl.s];
+  const int e = element_of_block(blockIdx.x, A.chunk);
+  if (e >= A.nelem) return;  // uniform over the workgroup
+  const int t = threadIdx.x;  // node and face item
   R (*sP)[nnp] = reinterpret_cast<R (*)[nnp]>(sPool);
   R (*sF)[5][nf] = reinterpret_cast<R (*)[5][nf]>(sPool + oF);
   R (*sQ)[4][nf] = reinterpret_cast<R (*)[4][nf]>(sPool + (NS ? oQ : 0));
@@ -1423,7 +1415,6 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
   const double gm1 = A.gamma - 1.0;
   // Memory round trip 1: neighbour indices of the thread's face items, the
   // node state and the basis.
-  static_assert(EPB == 1, "one element per workgroup: its neighbours are uniform");
   const Nbr6 nb6 = uniform_nbr6(A.nbr, e);
   FaceData<NS, R, WALL, DEFER, !OWN_LDS> fd[FI];
 #pragma unroll
@@ -1442,22 +1433,22 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
     for (int v = 0; v < 5; ++v) u[v] = Ue[v * nn + t];
   }
   static_assert(NB_STAGE <= PS::NTB, "one basis entry per thread");
-  const double bval = tid < NB_STAGE ? A.basis[SKIP && tid < nf ? dhat_index(tid) : tid] : 0.0;
+  const double bval = t < NB_STAGE ? A.basis[SKIP && t < nf ? dhat_index(t) : t] : 0.0;
   // V^-1 for the indicator of the stage output (blended Euler runs)
-  const double vval = (BLEND && !NS && kFusedAlpha1 && tid >= NB_STAGE && tid < NB_STAGE + nf) ? A.basis[tid] : 0.0;
+  const double vval = (BLEND && !NS && kFusedAlpha1 && t >= NB_STAGE && t < NB_STAGE + nf) ? A.basis[t] : 0.0;
   const Ref ref = MX ? reference_state(A.U, gm1) : Ref{0.0, 0.0, 0.0};
   // Round trip 2: the face states (needs the neighbour indices).
 #pragma unroll
   for (int k = 0; k < FI; ++k)
     if (t + k * TPE < 6 * nf) face_issue<NS, R, WALL, DEFER, !OWN_LDS>(A, e, fd[k], nb6);
   unsigned rem = kNoRemainders;
-  if (OWN_LDS && A.carryU && t < nn) rem = remainders(A.Fcarry, A.nelem)[(size_t)e * nn + t];
-  if (tid < NB_STAGE) {
-    sB[tid] = (R)bval;
-    if (BLEND) sB64[tid] = bval;
+  if (OWN_LDS && A.Fcarry && t < nn) rem = remainders(A.Fcarry, A.nelem)[(size_t)e * nn + t];
+  if (t < NB_STAGE) {
+    sB[t] = (R)bval;
+    if (BLEND) sB64[t] = bval;
   }
   if constexpr (BLEND && !NS && kFusedAlpha1)
-    if (tid >= NB_STAGE && tid < NB_STAGE + nf) sB64[tid] = vval;
+    if (t >= NB_STAGE && t < NB_STAGE + nf) sB64[t] = vval;
   const R* sDhat = sB + BL.Dhat();
   const R* sDw = sB + BL.Dw();
   const R* swinv = sB + BL.winv();
@@ -1481,9 +1472,9 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
       for (int k = 0; k < FI; ++k)
         if (t + k * TPE < 6 * nf && !(WALL && fd[k].it.nb < 0)) store_q(fd[k].it, fd[k].c.fn, sFn);
       __syncthreads();
-      if (KEEP_S || A.carryU)
-        if (t < nn) carry_own(sFn, A.invJ, hw, ijk, wmask, S);
-      if (A.carryU && t < nn) {
+      // (N = 7: every thread has a node, and the branch would spill two registers)
+      if (nn == TPE || t < nn) {
+        carry_own(sFn, A.invJ, hw, ijk, wmask, S);
 #pragma unroll
         for (int c = 0; c < 4; ++c) u[1 + c] = carried(u[1 + c], A.Bcarry, S[c], rem, c);
       }
@@ -1527,7 +1518,7 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
         } else {
 #pragma unroll
           for (int v = 0; v < 5; ++v) X[v] = fd[k].X[v];
-          if (A.carryU) carry_neighbour(A, it, fd[k].c, X);
+          if (A.Fcarry) carry_neighbour(A, it, fd[k].c, X);
         }
 #pragma unroll
         for (int v = 0; v < 5; ++v) {
@@ -1606,18 +1597,7 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
       if (al < A.amin) al = 0.0;
       if (t == 0 && A.alpha_out) A.alpha_out[e] = al;
     }
-    // The subcell pass holds barriers: it runs when any element of the
-    // workgroup is blended, each slot doing its work only if its own is.
-    bool run = al > 0.0;
-    if (EPB > 1) {
-      __shared__ int sAny[EPB];
-      if (sl.traw == 0 && threadIdx.x < EPB * TPE) sAny[sl.s] = sl.live && al > 0.0;
-      __syncthreads();
-      run = false;
-#pragma unroll
-      for (int k = 0; k < EPB; ++k) run = run || sAny[k] != 0;
-    }
-    if (run) {  // uniform over the workgroup
+    if (al > 0.0) {  // uniform over the workgroup
       const double* sxi = sB64 + BL.xi();
       const double* sedge = sB64 + BL.edge();
       const double* swinv64 = sB64 + BL.winv();
@@ -1628,7 +1608,7 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
       for (int d = 0; d < 3; ++d) {
         const int st = d == 0 ? 1 : (d == 1 ? n1 : nf);
         __syncthreads();
-        if (t < nn && ijk[d] < N && al > 0.0) {
+        if (t < nn && ijk[d] < N) {
           const int base = t - ijk[d] * st;
           double wl[5], wr[5], UL[5], UR[5], fs[5];
           subcell_face_state(sP64, base, st, ijk[d], true, A.recon, sxi, sedge, wl);
@@ -1640,7 +1620,7 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
           for (int v = 0; v < 5; ++v) sX[v][t] = fs[v];
         }
         __syncthreads();
-        if (t < nn && al > 0.0) {
+        if (t < nn) {
           const int id = ijk[d];
           const int a = d == 0 ? ijk[1] + n1 * ijk[2] : (d == 1 ? ijk[0] + n1 * ijk[2] : ijk[0] + n1 * ijk[1]);
           const double c = A.invJ[d] * swinv64[id];
@@ -1652,12 +1632,7 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
           }
         }
       }
-      if (!(al > 0.0)) {
-        if (A.mode == MODE_DIFF) {
-#pragma unroll
-          for (int v = 0; v < 5; ++v) acc[v] = (R)0;
-        }
-      } else if (A.mode == MODE_DIFF) {
+      if (A.mode == MODE_DIFF) {
 #pragma unroll
         for (int v = 0; v < 5; ++v) acc[v] = (R)(fv[v] - (double)acc[v]);
       } else {
@@ -1701,7 +1676,7 @@ __global__ DG_STAGE_BOUNDS void k_stage(StageArgs A) {
     }
     __syncthreads();
     if constexpr (LINES) {
-      divergence_lines<R, PS::NTB>(A, sV, tid);
+      divergence_lines<R, PS::NTB>(A, sV, t);
       __syncthreads();
     }
     if (t < nn) {
@@ -2893,10 +2868,10 @@ __device__ __forceinline__ void gradient_transpose_dir(const double (*sX)[nn], c
 // Main reverse kernel.  Writes U_bar (or U_acc + U_bar when A.Uacc is set).
 // EQ: 0 Euler, 1 Navier-Stokes, 2 with the Smagorinsky eddy viscosity; WALL:
 // wall-modelled faces (neighbour -1).
-// Bound by latency and LDS: at N = 5, 16^3, 96 us (121 with one pass over the
-// partners for each of the two-point flux, the viscous-flux cotangent and the
-// forward gradient), LDS 0.55 and VALU 0.52 busy with 2.3 waves per SIMD in
-// flight.  Three waves per SIMD (at most 168 registers; a few spill) run it
+// Bound by latency and LDS: at N = 5, 16^3, 78 us, LDS 0.48 and VALU 0.54 busy with
+// 2.1 waves per SIMD in flight (121 -> 106 us by one pass over the partners instead
+// of one for each of the two-point flux, the viscous-flux cotangent and the forward
+// gradient).  Three waves per SIMD (at most 168 registers; a few spill) run it
 // faster than two without spills; the wall variants keep their
 // registers, and so does N = 7, where the LDS admits one workgroup per CU.
 template <int VF, int EQ, bool WALL = false>
