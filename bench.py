@@ -369,12 +369,13 @@ def face_flux_bytes_per_node(N, viscous, split):
     """Algorithmic bytes per node and stage launch of the normal viscous face
     flux (FP64, 4 values at each of the 6 (N+1)^2 face nodes of an element):
     the stage kernel reads the neighbours' (192/(N+1) B per node); with the
-    split lifting it writes its own in every stage and reads the neighbours' of
-    the stage before in stages 2-5."""
+    split lifting it writes its own in every stage, with the remainders of its
+    state (4 B per node), and reads the neighbours' and the remainders of the
+    stage before in stages 2-5."""
     if not viscous:
         return 0.0
     f = 192.0 / (N + 1)
-    return f * (1.0 + (0.8 if split else 0.0))
+    return 1.8 * (f + 4.0) if split else f
 
 
 def roofline(name, nodes, steps, prof, N=None, viscous=False, split=False):
