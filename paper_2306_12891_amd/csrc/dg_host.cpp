@@ -193,7 +193,7 @@ struct dg_ctx {
   double* Fvf = nullptr;
   double* Fvf2 = nullptr;  // deferred viscous exchange: the other of the pair (allocated on first use)
   // a step call could not get Fvf2 / U3: not asked for again until a call that
-  // changes the operator (a driver query or a failing allocation in every step)
+  // changes the operator (a memory query or a failing allocation in every step)
   bool no_Fvf2 = false, no_U3 = false;
   double* cs_field = nullptr;  // per-element Smagorinsky coefficients (dg_set_cs_field)
   int has_cs_field = 0;
